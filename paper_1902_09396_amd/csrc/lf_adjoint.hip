@@ -24,9 +24,11 @@
 //     fractions and applies the colour transpose, writing the sample
 //     gradients into the level-0 node planes;
 //  4. node gradients are summed up the tree level by level in fixed order;
-//  5. each reference residual pulls the phase-signed bilinear transpose of
-//     its predictive siblings' gradients;
-//  6. each block's shift gradient is a fixed-order wave64 reduction.
+//  5. each block's shift gradient is a fixed-order reduction over its pixels,
+//     and the block leaves a record: phase, split shift, and whether any of
+//     its gradients is non-zero;
+//  6. each reference residual pulls the phase-signed bilinear transpose of
+//     its predictive siblings' gradients, from the recorded blocks.
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
@@ -36,13 +38,21 @@
 
 #define AD_MAX_PARTS 1024  // partial maxima of the shift reduction
 #define AD_TILE 16         // reference tile side of the pull kernel
-#define AD_PPT 1           // pixels per thread (rows AD_TILE * k / AD_PPT apart)
-// LDS of the reference pull: 23.5 KB, six workgroups per CU (the budgets
-// fit tiles whose reach is up to 11 pixels; beyond, the unstaged paths)
-#define AD_CAND_MAX 192    // candidate blocks a tile stages in LDS
-#define AD_WIN_MAX 4336    // sibling gradient values a tile stages in LDS (3 windows of up to 38 x 38)
+#define AD_FAR 48          // reach up to which positions outside the image are folded (three tiles)
+
+// n / d for 0 <= n <= 3072, 1 <= d <= 1024: the quotient of n + 1/2 is at
+// least 1 / (2 d) from an integer, the rounded reciprocal and product are off
+// by less than n 2^-22
+__device__ __forceinline__ int lf_small_div(int n, int d)
+{
+    return (int)(((float)n + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+}
 
 __device__ __forceinline__ float ad_lerp(float p, float q, float f) { return fmaf(f, q - p, p); }
+
+// four (two) consecutive floats at any 4-byte aligned address, one load
+typedef float ad_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float ad_f2 __attribute__((ext_vector_type(2), aligned(4)));
 
 struct AdRay {
     int a0, a1, b0, b1, x0, x1, y0, y1;
@@ -67,11 +77,16 @@ __device__ __forceinline__ int64_t ad_record(const LfGeom& g, int c, int l, int 
     return g.rec_base[c][l] + (int64_t)pred_ordinal(g.na_l[l], B, A) * g.nblk + blk;
 }
 
+// phase of record j of (channel c, level l): 2-bit codes, sixteen to a word
+__device__ __forceinline__ int ad_phase_at(const LfGeom& g, const LfPtrs& p, int c, int l, uint32_t j)
+{
+    const uint32_t code = (p.mv[g.sig_word[c][l] + (j >> 4)] >> (2u * (j & 15u))) & 3u;
+    return code == 0u ? 1 : (code == 1u ? -1 : 0);
+}
+
 __device__ __forceinline__ int ad_phase(const LfGeom& g, const LfPtrs& p, int c, int l, int B, int A, int blk)
 {
-    int mx, my, sg;
-    lf_motion(g, p, c, l, (uint32_t)(pred_ordinal(g.na_l[l], B, A) * g.nblk + blk), mx, my, sg);
-    return sg;
+    return ad_phase_at(g, p, c, l, (uint32_t)(pred_ordinal(g.na_l[l], B, A) * g.nblk + blk));
 }
 
 // ---------------------------------------------------------------------------
@@ -481,28 +496,18 @@ __device__ __forceinline__ AdRec ad_unpack(int4 v)
     return AdRec{v.x, (int)(int16_t)(v.y & 0xFFFF), v.y >> 16, __int_as_float(v.z), __int_as_float(v.w)};
 }
 
-// phase and split shift of every predictive block, in record order, decoded
-// once for the reference pull (each block is a candidate of several tiles)
-__global__ void k_ad_blockrec(LfGeom g, LfPtrs p, const float2* __restrict__ shift, int64_t n_rec,
-                              int4* __restrict__ brec)
+// Split shift of a block with phase sg; sg 0 leaves it empty.
+__device__ __forceinline__ AdRec ad_split(const LfGeom& g, int sg, float2 s)
 {
-    const int64_t rec = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (rec >= n_rec) return;
-    int c = 0, l = g.H - 1;
-    while (c < 2 && rec >= g.rec_base[c + 1][g.H - 1]) c++;
-    while (l > 0 && rec >= g.rec_base[c][l - 1]) l--;
-    int mx, my, sg;
-    lf_motion(g, p, c, l, (uint32_t)(rec - g.rec_base[c][l]), mx, my, sg);
     AdRec d{sg, 0, 0, 0.0f, 0.0f};
     if (sg) {
-        const float2 s = shift[rec];
         const float fdx = floorf(s.x), fdy = floorf(s.y);
         d.fx = s.x - fdx;
         d.fy = s.y - fdy;
         d.ix = (int)fminf(fmaxf(fdx, (float)(-g.w - 1)), (float)g.w);
         d.iy = (int)fminf(fmaxf(fdy, (float)(-g.h - 1)), (float)g.h);
     }
-    brec[rec] = ad_pack(d);
+    return d;
 }
 
 // What reference pixel (X, Y) pulls from one predictive block (row ky,
@@ -551,293 +556,373 @@ __device__ __forceinline__ float ad_block_pull(const LfGeom& g, Get get, int X, 
     return acc + (d.sg > 0 ? blk_acc : -blk_acc);
 }
 
-// Gradient that reference pixel (X, Y) of the cluster with reference node
-// (Br, Ar) pulls from its predictive siblings' gradients: for every sibling
-// block whose shifted taps can reach the pixel, the bilinear weights of the
-// taps that land on it (phase-signed), added in sibling, block-row,
-// block-column order.  fetch(sib, B, A, ky, kx) returns the block's AdRec.
-template <class Fetch>
-__device__ inline float ad_pull(const LfGeom& g, const float* __restrict__ gres, int c, int l, int Br, int Ar, int X,
-                                int Y, int reach, int lky0, int lky1, int lkx0, int lkx1, Fetch fetch, float acc)
-{
-    // the loops run over [lky0, lky1] x [lkx0, lkx1] (a tile's shared range,
-    // uniform across its pixels) and skip the blocks outside this pixel's range
-    const int64_t plane = (int64_t)g.w * g.h;
-    const int kx0 = max(0, (X - reach) / g.bs), kx1 = min(g.nbx - 1, (X + reach) / g.bs);
-    const int nby = g.h / g.bs;
-    const int ky0 = max(0, (Y - reach) / g.bs), ky1 = min(nby - 1, (Y + reach) / g.bs);
-    for (int sib = 1; sib < 4; sib++) {
-        const int B = Br + (sib >> 1), A = Ar + (sib & 1);
-        if (B >= g.nb_l[l] || A >= g.na_l[l]) continue;
-        const float* gp = gres + ((int64_t)c * g.n_nodes + g.node_base[l] + B * g.na_l[l] + A) * plane;
-        for (int ky = lky0; ky <= lky1; ky++)
-            for (int kx = lkx0; kx <= lkx1; kx++) {
-                if (ky < ky0 || ky > ky1 || kx < kx0 || kx > kx1) continue;
-                const AdRec d = fetch(sib, B, A, ky, kx);
-                if (!d.sg) continue;
-                acc = ad_block_pull(g, [&](int y, int x) { return gp[y * g.w + x]; }, X, Y, ky, kx, d, acc);
-            }
+// One kept block of the reference pull: its record and place (scalar, from
+// lane src of the candidates) and the five rows by two columns of source
+// gradients that the four positions (Y0 + k, X) of a lane read.  The tap
+// (oy, ox) landing on position (Y0 + k, X) comes from source pixel
+// (Y0 + k - iy - oy, X - ix - ox) alone, when that lies in the block: rows
+// ys .. ys + 4, columns xs - 1 and xs; others count as zero.
+struct AdTaps {
+    AdRec q;
+    int bx, by;  // the block's first column and row
+    float s0[5], s1[5];
+
+    __device__ __forceinline__ void load(const LfGeom& g, const float* gp, int4 v, int kx, int ky, int src, int X, int Y0)
+    {
+        bx = __builtin_amdgcn_readlane(kx, src) << g.bsl;
+        by = __builtin_amdgcn_readlane(ky, src) << g.bsl;
+        q = ad_unpack(make_int4(__builtin_amdgcn_readlane(v.x, src), __builtin_amdgcn_readlane(v.y, src),
+                                __builtin_amdgcn_readlane(v.z, src), __builtin_amdgcn_readlane(v.w, src)));
+        const int xs = X - q.ix, ys = Y0 - q.iy - 1;
+        const bool x0 = (unsigned)(xs - bx) < (unsigned)g.bs, x1 = (unsigned)(xs - 1 - bx) < (unsigned)g.bs;
+        const int first = ys * g.w + xs;
+#pragma unroll
+        for (int t = 0; t < 5; t++) {
+            const bool y = (unsigned)(ys + t - by) < (unsigned)g.bs;
+            // both columns in one load: (xs - 1, xs), or (xs - 2, xs - 1) when
+            // xs is past the block (a predictive plane is never the buffer's
+            // first, so an element before it is still inside the buffer)
+            const int at = y && (x0 || x1) ? first + t * g.w - (x0 ? 1 : 2) : 0;
+            const ad_f2 a = *reinterpret_cast<const ad_f2*>(gp + at);
+            s0[t] = y && x0 ? a.y : 0.0f;
+            s1[t] = y && x1 ? (x0 ? a.x : a.y) : 0.0f;
+        }
     }
-    return acc;
-}
 
+    // far: pixels on the image border (live, not inner) collect every tap
+    // clamped onto them here, instead of from the positions outside the image
+    __device__ __forceinline__ void add(const LfGeom& g, const float* gp, bool far, const bool (&live)[4],
+                                        const bool (&inner)[4], int X, int Y0, float (&acc)[4]) const
+    {
+        const float sg = (float)q.sg, gx = 1.0f - q.fx, gy = 1.0f - q.fy;
+        const float w00 = sg * (gy * gx), w01 = sg * (gy * q.fx), w10 = sg * (q.fy * gx), w11 = sg * (q.fy * q.fx);
+        float blk[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            blk[k] = w00 * s0[k + 1];
+            blk[k] = fmaf(w01, s1[k + 1], blk[k]);
+            blk[k] = fmaf(w10, s0[k], blk[k]);
+            blk[k] = fmaf(w11, s1[k], blk[k]);
+        }
+        if (!far && w00 * 0.0f == 0.0f && w11 * 0.0f == 0.0f) {  // uniform: finite weights, so a tap outside adds zero
+#pragma unroll
+            for (int k = 0; k < 4; k++) acc[k] += blk[k];
+            return;
+        }
+        const int cx = X - q.ix - bx, cy = Y0 - q.iy - by;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            // covered: one of the two columns and one of the two rows in the block
+            const bool in = (unsigned)cx <= (unsigned)g.bs && (unsigned)(cy + k) <= (unsigned)g.bs;
+            if (in && (!far || inner[k])) acc[k] += blk[k];
+        }
+        if (!far) return;
+#pragma unroll 1
+        for (int k = 0; k < 4; k++) {
+            if (!live[k] || inner[k]) continue;
+            const float t = ad_block_pull(g, [&](int y, int x) { return gp[y * g.w + x]; }, X, Y0 + k, by >> g.bsl,
+                                          bx >> g.bsl, q, 0.0f);
+            if (k == 0) acc[0] += t;
+            if (k == 1) acc[1] += t;
+            if (k == 2) acc[2] += t;
+            if (k == 3) acc[3] += t;
+        }
+    }
+};
 
-// reference residual gradient: own node gradient plus the phase-signed
-// bilinear transpose of every predictive sibling's gradient (pull form).  A
-// workgroup takes 16x16 tiles of one reference plane.  The candidate blocks
-// (those within the largest shift of the tile) are read from the decoded
-// block records; the ones whose shifted taps land inside the tile are kept, in
-// (sibling, block-row, block-column) order, in an LDS list that every pixel
-// of the tile walks (the blocks left out add exactly zero to every pixel of
-// the tile).  The three sibling gradient windows the taps can come from are
-// staged in LDS when they fit; their loads, the candidates' and the pixel's
-// own gradient are issued together.  With more candidates than the LDS
-// budget holds, every pixel reads its own candidates instead.
+// Reference residual gradient: own node gradient plus the phase-signed
+// bilinear transpose of every predictive sibling's gradient (pull form).  One
+// wave64 takes a 16x16 tile of one reference plane, each lane four rows of
+// one column.  The candidate blocks (those within the largest shift of the
+// tile) are examined one per lane; the ones whose shifted taps land in the
+// tile and that hold a non-zero gradient are walked in (sibling, block row,
+// block column) order with their record in scalar registers, and every lane
+// reads the five rows by two columns of source pixels its four taps need.
+// A block left out adds exactly zero to every pixel of the tile.
+//
+// Bound by latency and issue (a tile's prologue and candidate test take about
+// 300 instructions, a kept block 80 and five loads).  Staging the siblings'
+// windows (tile plus the largest shift on every side) in LDS instead read 17
+// values per pixel where the kept blocks hold about four, and two thirds of a
+// tile's time went into waiting for them.  17x17 views of 512x512, 16
+// rendered views (a quarter of the gradients non-zero): 3.77 -> 0.57 ms;
+// 9x9 views of 256x256, three views: 0.288 -> 0.040 ms.  Four tiles per wave
+// in sequence: 0.55 and 0.059 ms (too few waves on the small field).
 __global__ void __launch_bounds__(256) k_ad_reference(LfGeom g, const int4* __restrict__ brec,
-                                                      const float* __restrict__ maxshift, float* __restrict__ gres)
+                                                      const float* __restrict__ maxshift, float* gres)
 {
-    // kept block i: windowed tiles: lst_a = (x origin kx bs + ix, y origin
-    // ky bs + iy, window offset of source pixel (Y - iy, X - ix) less
-    // Y ww + X, packed (sibling, ky, kx)), lst_b = the tap weights (1-fy)(1-fx),
-    // (1-fy) fx, fy (1-fx), fy fx times the phase (float bits); otherwise
-    // lst_a = the block record, lst_b.x = packed (sibling, ky, kx)
-    __shared__ int4 lst_a[AD_CAND_MAX], lst_b[AD_CAND_MAX];
-    __shared__ float win[AD_WIN_MAX];  // [sibling - 1][window row][window column]
-    __shared__ int wcount[4];
-    const int64_t plane = (int64_t)g.w * g.h;
+    const int plane = g.w * g.h;  // at most 2^28
     const int tiles_x = (g.w + AD_TILE - 1) / AD_TILE, tiles_y = (g.h + AD_TILE - 1) / AD_TILE;
-    // 32-bit tile indices (the host bounds the tile count by 2^31 - 1)
+    // 32-bit indices (the host bounds the tile count by 2^31 - 1)
     const int per_plane = tiles_x * tiles_y;
     const int n_tiles = 3 * g.n_refs * per_plane;
-    const int reach = (int)ceilf(fminf(maxshift[0], (float)(g.w + g.h))) + 2;
-    const int nby = g.h / g.bs;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int T = blockIdx.x; T < n_tiles; T += gridDim.x) {
-        const int rp = T / per_plane;
-        const int tt = T - rp * per_plane;
-        const int c = rp / g.n_refs, r = rp - c * g.n_refs;
-        int l = 0;
-        while (l + 1 < g.H && r >= g.ref_base[l + 1]) l++;
-        const int loc = r - g.ref_base[l];
-        const int Br = 2 * (loc / g.na_l[l + 1]), Ar = 2 * (loc % g.na_l[l + 1]);
-        const int tx0 = (tt % tiles_x) * AD_TILE, ty0 = (tt / tiles_x) * AD_TILE;
-        const int tx1 = min(tx0 + AD_TILE - 1, g.w - 1), ty1 = min(ty0 + AD_TILE - 1, g.h - 1);
-        const int ckx0 = max(0, (tx0 - reach) / g.bs), ckx1 = min(g.nbx - 1, (tx1 + reach) / g.bs);
-        const int cky0 = max(0, (ty0 - reach) / g.bs), cky1 = min(nby - 1, (ty1 + reach) / g.bs);
-        const int nkx = ckx1 - ckx0 + 1, nk = nkx * (cky1 - cky0 + 1);
-        const bool staged = 3 * nk <= AD_CAND_MAX;  // uniform
-        // Every tap a pixel of the tile pulls comes from within `reach` of the tile.
-        const int wx0 = max(0, tx0 - reach), wx1 = min(g.w - 1, tx1 + reach);
-        const int wy0 = max(0, ty0 - reach), wy1 = min(g.h - 1, ty1 + reach);
-        const int ww = wx1 - wx0 + 1, nr = wy1 - wy0 + 1, wa = ww * nr;
-        const bool windowed = staged && ww <= 64 && 3 * wa <= AD_WIN_MAX;  // uniform
-
-        // loads in flight together: candidate records, the pixel's own
-        // gradient, the sibling windows
-        constexpr int CR = (AD_CAND_MAX + 255) / 256;
-        int4 cv[CR];
-        bool cok[CR];
+    // workgroup ids go round-robin over the 8 XCDs: each XCD takes a
+    // contiguous range of tiles, so neighbouring tiles share its L2
+    const int wg = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    const int T = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+    if (T >= n_tiles) return;  // uniform per wave
+    const int lane = threadIdx.x & 63;
+    const int reach = __builtin_amdgcn_readfirstlane((int)ceilf(fminf(maxshift[0], (float)(g.w + g.h))) + 2);
+    const int rp = T / per_plane, tt = T - rp * per_plane;
+    const int c = rp / g.n_refs, r = rp - c * g.n_refs;
+    int l = 0;
+    while (l + 1 < g.H && r >= g.ref_base[l + 1]) l++;
+    const int loc = r - g.ref_base[l], nar = g.na_l[l + 1], na = g.na_l[l];
+    const int Bp = loc / nar, Br = 2 * Bp, Ar = 2 * (loc - Bp * nar);
+    const int trow = tt / tiles_x;
+    // siblings 1 (right), 2 (below) and 3: present or not, gradient plane, first record
+    const bool h1 = Ar + 1 < na, h2 = Br + 1 < g.nb_l[l], h3 = h1 && h2;
+    float* own = gres + ((int64_t)c * g.n_nodes + g.node_base[l] + Br * na + Ar) * plane;
+    const float *gp1 = own + plane, *gp2 = own + (int64_t)na * plane, *gp3 = gp2 + plane;
+    const int4* rec = brec + g.rec_base[c][l];
+    const uint32_t r1 = (uint32_t)(pred_ordinal(na, Br, Ar + 1) * g.nblk), r2 = (uint32_t)(pred_ordinal(na, Br + 1, Ar) * g.nblk),
+                   r3 = r2 + (uint32_t)g.nblk;  // the sibling below's right neighbour is the next node of its row
+    const int ty0 = trow * AD_TILE, ty1 = min(ty0 + AD_TILE - 1, g.h - 1);
+    const int cky0 = max(0, ty0 - reach) >> g.bsl, nky = min(g.h - 1, ty1 + reach) / g.bs - cky0 + 1;
+    const int Y0 = ty0 + (lane >> 4) * 4;
+    // shifts too far for the sets of outside positions: a border pixel walks
+    // the source pixels of every tap clamped onto it instead
+    const bool far = reach > AD_FAR;
+    const int nv = (reach + AD_TILE - 1) / AD_TILE;
+    const int tx0 = (tt - trow * tiles_x) * AD_TILE, tx1 = min(tx0 + AD_TILE - 1, g.w - 1);
+    const int ckx0 = max(0, tx0 - reach) >> g.bsl, nkx = (min(g.w - 1, tx1 + reach) >> g.bsl) - ckx0 + 1;
+    const int nk = nkx * nky;
+    const int X = tx0 + (lane & 15);
+    bool live[4], inner[4];
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int k2 = 0; k2 < CR; k2++) {
-            const int e = k2 * 256 + (int)threadIdx.x;
-            cok[k2] = false;
-            cv[k2] = make_int4(0, 0, 0, 0);
-            if (staged && e < 3 * nk) {
-                const int sib = 1 + e / nk, k = e - (sib - 1) * nk;
-                const int B = Br + (sib >> 1), A = Ar + (sib & 1);
-                if (B < g.nb_l[l] && A < g.na_l[l]) {
-                    cok[k2] = true;
-                    cv[k2] = brec[ad_record(g, c, l, B, A, (cky0 + k / nkx) * g.nbx + ckx0 + k % nkx)];
-                }
-            }
-        }
-        // pixel k of this thread: column tid % AD_TILE, row tid / AD_TILE + k AD_TILE / AD_PPT
-        constexpr int RSTEP = AD_TILE / AD_PPT;
-        const int X = tx0 + (int)threadIdx.x % AD_TILE, Y0 = ty0 + (int)threadIdx.x / AD_TILE;
-        const int64_t own0 = ((int64_t)c * g.n_nodes + g.node_base[l] + Br * g.na_l[l] + Ar) * plane + X;
-        float own_g[AD_PPT];
-#pragma unroll
-        for (int k = 0; k < AD_PPT; k++) {
-            const int Y = Y0 + k * RSTEP;
-            own_g[k] = (X <= tx1 && Y <= ty1) ? gres[own0 + (int64_t)Y * g.w] : 0.0f;
-        }
-        if (windowed) {
-            // all of the three windows' loads in flight at once: value e of
-            // the concatenation is value rr of sibling window sw (row rr / ww,
-            // column rr % ww; the row from a float reciprocal, exact for
-            // rr < 2^13 and ww <= 64)
-            constexpr int WL = (AD_WIN_MAX + 255) / 256;
-            const float rw = 1.0f / (float)ww;
-            const int64_t nb0 = (int64_t)c * g.n_nodes + g.node_base[l];
-            const bool h1 = Ar + 1 < g.na_l[l], h2 = Br + 1 < g.nb_l[l], h3 = h1 && h2;
-            const float* s1 = gres + (nb0 + Br * g.na_l[l] + Ar + 1) * plane;
-            const float* s2 = gres + (nb0 + (Br + 1) * g.na_l[l] + Ar) * plane;
-            const float* s3 = gres + (nb0 + (Br + 1) * g.na_l[l] + Ar + 1) * plane;
-            float v[WL];
-#pragma unroll
-            for (int u = 0; u < WL; u++) {
-                const int e = u * 256 + (int)threadIdx.x;
-                const int sw = e >= 2 * wa ? 2 : (e >= wa ? 1 : 0);
-                const int rr = e - sw * wa;
-                const int yy = (int)(((float)rr + 0.5f) * rw), xx = rr - yy * ww;
-                const bool has = sw == 0 ? h1 : (sw == 1 ? h2 : h3);
-                const float* sp = sw == 0 ? s1 : (sw == 1 ? s2 : s3);
-                v[u] = (e < 3 * wa && has) ? sp[(int64_t)(wy0 + yy) * g.w + wx0 + xx] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < WL; u++) {
-                const int e = u * 256 + (int)threadIdx.x;
-                if (e < 3 * wa) win[e] = v[u];
-            }
-        }
-        // keep the candidates whose taps reach the tile, in order
-        int n_list = 0;
-        if (staged) {
-#pragma unroll
-            for (int k2 = 0; k2 < CR; k2++) {
-                if (k2 * 256 >= 3 * nk) break;  // uniform
-                const int e = k2 * 256 + (int)threadIdx.x;
-                const AdRec d = ad_unpack(cv[k2]);
-                const int sib = 1 + e / nk, k = e - (sib - 1) * nk;
-                const int ky = cky0 + k / nkx, kx = ckx0 + k % nkx;
-                // taps of the block's pixels: [k bs + i, k bs + bs + i] per axis, clamped
-                const int xlo = lf_clampi(kx * g.bs + d.ix, 0, g.w - 1);
-                const int xhi = lf_clampi(kx * g.bs + g.bs + d.ix, 0, g.w - 1);
-                const int ylo = lf_clampi(ky * g.bs + d.iy, 0, g.h - 1);
-                const int yhi = lf_clampi(ky * g.bs + g.bs + d.iy, 0, g.h - 1);
-                const bool keep = cok[k2] && d.sg != 0 && xlo <= tx1 && xhi >= tx0 && ylo <= ty1 && yhi >= ty0;
-                const uint64_t m = __ballot(keep);
-                if (lane == 0) wcount[wv] = __popcll(m);
-                __syncthreads();
-                int pos = n_list;
-                for (int q = 0; q < wv; q++) pos += wcount[q];
-                pos += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                if (keep) {
-                    const int at = (sib << 28) | (ky << 14) | kx;
-                    if (windowed) {
-                        const float sg = (float)d.sg, gx = 1.0f - d.fx, gy = 1.0f - d.fy;
-                        lst_a[pos] = make_int4(kx * g.bs + d.ix, ky * g.bs + d.iy,
-                                               (sib - 1) * wa - (d.iy + wy0) * ww - (d.ix + wx0), at);
-                        lst_b[pos] = make_int4(__float_as_int(sg * (gy * gx)), __float_as_int(sg * (gy * d.fx)),
-                                               __float_as_int(sg * (d.fy * gx)), __float_as_int(sg * (d.fy * d.fx)));
-                    } else {
-                        lst_a[pos] = cv[k2];
-                        lst_b[pos] = make_int4(at, 0, 0, 0);
-                    }
-                }
-                for (int q = 0; q < 4; q++) n_list += wcount[q];
-                __syncthreads();  // wcount is rewritten by the next round; lists and window complete
-            }
-        }
-#pragma unroll
-        for (int kp = 0; kp < AD_PPT; kp++) {
-        const int Y = Y0 + kp * RSTEP;
-        if (X <= tx1 && Y <= ty1) {
-            float acc = own_g[kp];
-            if (windowed && X > 0 && X < g.w - 1 && Y > 0 && Y < g.h - 1) {
-                // away from the image border each tap (oy, ox) landing on the
-                // pixel comes from source pixel (Y - iy - oy, X - ix - ox) alone,
-                // when it lies in the block: the same products, in the same
-                // order, as the general form
-                const int base = Y * ww + X;
-                for (int i = 0; i < n_list; i++) {
-                    const int4 e = lst_a[i];
-                    const int dx = X - e.x, dy = Y - e.y;
-                    const bool x0 = (unsigned)dx < (unsigned)g.bs, x1 = (unsigned)(dx - 1) < (unsigned)g.bs;
-                    const bool y0 = (unsigned)dy < (unsigned)g.bs, y1 = (unsigned)(dy - 1) < (unsigned)g.bs;
-                    if (!((x0 || x1) && (y0 || y1))) continue;
-                    const int4 wb = lst_b[i];
-                    const float* src = win + base + e.z;
-                    float blk = 0.0f;
-                    if (y0 && x0) blk = fmaf(__int_as_float(wb.x), src[0], blk);
-                    if (y0 && x1) blk = fmaf(__int_as_float(wb.y), src[-1], blk);
-                    if (y1 && x0) blk = fmaf(__int_as_float(wb.z), src[-ww], blk);
-                    if (y1 && x1) blk = fmaf(__int_as_float(wb.w), src[-ww - 1], blk);
-                    acc += blk;
-                }
-            } else if (staged) {
-                for (int i = 0; i < n_list; i++) {
-                    const int at = windowed ? lst_a[i].w : lst_b[i].x;
-                    const int sib = at >> 28, ky = (at >> 14) & 0x3FFF, kx = at & 0x3FFF;
-                    const int B = Br + (sib >> 1), A = Ar + (sib & 1);
-                    if (windowed) {  // a border pixel
-                        const AdRec d = ad_unpack(brec[ad_record(g, c, l, B, A, ky * g.nbx + kx)]);
-                        const float* ws = win + (sib - 1) * wa - wy0 * ww - wx0;
-                        acc = ad_block_pull(g, [&](int y, int x) { return ws[y * ww + x]; }, X, Y, ky, kx, d, acc);
-                    } else {
-                        const AdRec d = ad_unpack(lst_a[i]);
-                        const float* gp =
-                            gres + ((int64_t)c * g.n_nodes + g.node_base[l] + B * g.na_l[l] + A) * plane;
-                        acc = ad_block_pull(g, [&](int y, int x) { return gp[y * g.w + x]; }, X, Y, ky, kx, d, acc);
-                    }
-                }
-            } else {
-                acc = ad_pull(g, gres, c, l, Br, Ar, X, Y, reach, max(0, (Y - reach) / g.bs),
-                              min(nby - 1, (Y + reach) / g.bs), max(0, (X - reach) / g.bs),
-                              min(g.nbx - 1, (X + reach) / g.bs),
-                              [&](int, int B, int A, int ky, int kx) {
-                                  return ad_unpack(brec[ad_record(g, c, l, B, A, ky * g.nbx + kx)]);
-                              },
-                              acc);
-            }
-            gres[own0 + (int64_t)Y * g.w] = acc;
-        }
-        }
-        __syncthreads();  // lists and window are rewritten for the next tile
+    for (int k = 0; k < 4; k++) {
+        live[k] = X <= tx1 && Y0 + k <= ty1;
+        inner[k] = X > 0 && X < g.w - 1 && Y0 + k > 0 && Y0 + k < g.h - 1;
     }
+    bool touched = false;  // a tile that no block reaches is left as it is
+    // A tile on the image border also takes the 16x16 sets of positions
+    // outside the image next to it that taps can reach, and folds them
+    // onto its border pixels (where the forward clamps those taps).
+    const int vx0 = !far && tx0 == 0 ? -nv : 0, vx1 = !far && tx1 == g.w - 1 ? nv : 0;
+    const int vy0 = !far && ty0 == 0 ? -nv : 0, vy1 = !far && ty1 == g.h - 1 ? nv : 0;
+    for (int vy = vy0; vy <= vy1; vy++)
+        for (int vx = vx0; vx <= vx1; vx++) {
+            const int px0 = tx0 + vx * AD_TILE, py0 = ty0 + vy * AD_TILE;  // positions of this set
+            const int PX = X + vx * AD_TILE, PY = Y0 + vy * AD_TILE;
+            float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            bool some = false;
+            for (int k0 = 0; k0 < 3 * nk; k0 += 64) {
+                // one candidate block per lane, (sibling, row, column) order
+                const int e = k0 + lane;
+                const int sib = e >= 2 * nk ? 3 : (e >= nk ? 2 : 1), es = e - (sib - 1) * nk;
+                const int ey = nk <= 1024 ? lf_small_div(es, nkx) : es / nkx;  // uniform choice
+                const int kx = ckx0 + es - ey * nkx, ky = cky0 + ey;
+                int4 v = make_int4(0, 0, 0, 0);
+                if (e < 3 * nk && (sib == 1 ? h1 : (sib == 2 ? h2 : h3)))
+                    v = rec[(sib == 1 ? r1 : (sib == 2 ? r2 : r3)) + (uint32_t)(ky * g.nbx + kx)];
+                const AdRec d = ad_unpack(v);
+                // taps of the block's pixels: [k bs + i, k bs + bs + i] per axis (far: clamped)
+                int xlo = (kx << g.bsl) + d.ix, ylo = (ky << g.bsl) + d.iy, xhi = xlo + g.bs, yhi = ylo + g.bs;
+                if (far) {
+                    xlo = lf_clampi(xlo, 0, g.w - 1);
+                    xhi = lf_clampi(xhi, 0, g.w - 1);
+                    ylo = lf_clampi(ylo, 0, g.h - 1);
+                    yhi = lf_clampi(yhi, 0, g.h - 1);
+                }
+                const bool keep = d.sg != 0 && xlo <= px0 + AD_TILE - 1 && xhi >= px0 && ylo <= py0 + AD_TILE - 1 &&
+                                  yhi >= py0;
+                uint64_t m = __ballot(keep);
+                some |= m != 0;
+                // two kept blocks at a time: the second's loads are in
+                // flight while the first's are used
+                while (m) {
+                    const int src0 = __builtin_ctzll(m);
+                    m &= m - 1;
+                    const bool two = m != 0;  // uniform
+                    const int src1 = two ? __builtin_ctzll(m) : src0;
+                    m &= m - 1;
+                    const int s0 = __builtin_amdgcn_readlane(sib, src0), s1 = __builtin_amdgcn_readlane(sib, src1);
+                    const float* p0 = s0 == 1 ? gp1 : (s0 == 2 ? gp2 : gp3);
+                    const float* p1 = s1 == 1 ? gp1 : (s1 == 2 ? gp2 : gp3);
+                    AdTaps t0, t1;
+                    t0.load(g, p0, v, kx, ky, src0, PX, PY);
+                    if (two) t1.load(g, p1, v, kx, ky, src1, PX, PY);
+                    t0.add(g, p0, far, live, inner, PX, PY, part);
+                    if (two) t1.add(g, p1, far, live, inner, PX, PY, part);
+                }
+            }
+            if (!some) continue;  // uniform
+            touched = true;
+            if (!far && (vx != 0 || vy != 0 || px0 + AD_TILE > g.w || py0 + AD_TILE > g.h)) {
+                // positions left and right of the image onto its first and
+                // last column, then those above and below onto its rows
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    float lo = PX < 0 ? part[k] : 0.0f, hi = PX >= g.w ? part[k] : 0.0f;
+#pragma unroll
+                    for (int o = 8; o >= 1; o >>= 1) {
+                        lo += __shfl_xor(lo, o, 64);
+                        hi += __shfl_xor(hi, o, 64);
+                    }
+                    part[k] = PX < 0 || PX >= g.w || vx != 0 ? 0.0f : part[k];
+                    if (X == 0) part[k] += lo;
+                    if (X == g.w - 1) part[k] += hi;
+                }
+                float lo = 0.0f, hi = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    lo += PY + k < 0 ? part[k] : 0.0f;
+                    hi += PY + k >= g.h ? part[k] : 0.0f;
+                    if (PY + k < 0 || PY + k >= g.h || vy != 0) part[k] = 0.0f;
+                }
+#pragma unroll
+                for (int o = 16; o <= 32; o <<= 1) {
+                    lo += __shfl_xor(lo, o, 64);
+                    hi += __shfl_xor(hi, o, 64);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    if (Y0 + k == 0) part[k] += lo;
+                    if (Y0 + k == g.h - 1) part[k] += hi;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k++) acc[k] += part[k];
+        }
+    if (!touched) return;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        if (live[k]) own[(Y0 + k) * g.w + X] += acc[k];
 }
 
-// shift gradients: one wave64 per motion record (four per workgroup), each
-// lane summing its pixels in order, then a fixed butterfly across the wave
-__global__ void __launch_bounds__(256) k_ad_shift(LfGeom g, LfPtrs p, const float* __restrict__ res,
-                                                  const float2* __restrict__ shift, const float* __restrict__ gres_pred,
-                                                  float2* __restrict__ gshift, int64_t n_rec)
+// Predictive nodes of a tree as the shift pass numbers them: per channel,
+// level H-1 first, raster order (the records' order); first[l] is the first
+// node of level l.
+struct AdPred {
+    int total, first[LF_MAX_LEVELS];
+};
+
+// Shift gradients and block records.  A workgroup takes consecutive blocks of
+// one predictive node, 2^LG lanes a block; each lane sums its pixels in
+// order, then a fixed tree adds the lanes.  QUADS: a lane takes rows of four
+// pixels (one 128-bit gradient load, five taps of each of two reference
+// rows), so a 16x16 block is one wave64, an 8x8 block 16 lanes and a 4x4
+// block four; with 16x16 blocks a wave takes AD_SHIFT_U blocks whose loads
+// are in flight together.  Bound by the two passes over memory it cannot do
+// without (every predictive gradient, every reference residual): 1.27 GB in
+// 0.42 ms for 17x17 views of 512x512 (0.79 ms with one pixel per lane and
+// load; 0.99 with five single loads per row of four).
+#define AD_SHIFT_U 4
+template <int LG, bool QUADS>
+__global__ void __launch_bounds__(256) k_ad_shift(LfGeom g, LfPtrs p, AdPred pn, int groups,
+                                                  const float* __restrict__ res, const float2* __restrict__ shift,
+                                                  const float* __restrict__ gres_pred, float2* __restrict__ gshift,
+                                                  int4* __restrict__ brec)
 {
-    const int64_t rec = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (rec >= n_rec) return;  // uniform per wave
-    int c = 0, l = g.H - 1;
-    while (c < 2 && rec >= g.rec_base[c + 1][g.H - 1]) c++;
-    while (l > 0 && rec >= g.rec_base[c][l - 1]) l--;
-    const int64_t j = rec - g.rec_base[c][l];
-    const int pord = (int)(j / g.nblk), blk = (int)(j % g.nblk);
-    // invert the predictive ordinal: rows with odd B hold na_l nodes, even rows na_l / 2
-    const int na = g.na_l[l], pair = na + na / 2;
-    int B = 2 * (pord / pair), rem = pord % pair, A;
-    if (rem < na / 2) {
+    constexpr int G = 1 << LG, U = LG == 6 ? AD_SHIFT_U : 1, PER = U * (256 / G);
+    // the node, scalar
+    const int cn = (int)blockIdx.x / groups;
+    const int c = cn / pn.total, np = cn - c * pn.total;
+    int l = g.H - 1;
+    while (l > 0 && np >= pn.first[l - 1]) l--;
+    const int pord = np - pn.first[l], na = g.na_l[l], pair = na + na / 2;
+    int B = 2 * (pord / pair), A;
+    const int rem = pord % pair;
+    if (rem < na / 2) {  // even rows hold the odd columns, odd rows every column
         A = 2 * rem + 1;
     } else {
         B += 1;
         A = rem - na / 2;
     }
     const int64_t plane = (int64_t)g.w * g.h;
-    int mx, my, sg;
-    lf_motion(g, p, c, l, (uint32_t)j, mx, my, sg);
-    float sx = 0.0f, sy = 0.0f;
-    if (sg) {
-        const float2 d = shift[rec];
-        const float fdx = floorf(d.x), fdy = floorf(d.y);
-        const float fx = d.x - fdx, fy = d.y - fdy;
-        const float* R = res + ((int64_t)c * g.n_nodes + g.node_base[l] + (B & ~1) * na + (A & ~1)) * plane;
-        const float* gp = gres_pred + ((int64_t)c * g.n_nodes + g.node_base[l] + B * na + A) * plane;
-        const int by0 = (blk / g.nbx) * g.bs, bx0 = (blk % g.nbx) * g.bs;
-        for (int q = lane; q < g.bs * g.bs; q += 64) {
-            const int y = by0 + q / g.bs, x = bx0 + q % g.bs;
-            const int x0 = x + (int)fdx, y0 = y + (int)fdy;
-            const int xa = lf_clampi(x0, 0, g.w - 1), xb = lf_clampi(x0 + 1, 0, g.w - 1);
-            const int ya = lf_clampi(y0, 0, g.h - 1), yb = lf_clampi(y0 + 1, 0, g.h - 1);
-            const float t00 = R[ya * g.w + xa], t01 = R[ya * g.w + xb], t10 = R[yb * g.w + xa], t11 = R[yb * g.w + xb];
-            const float gv = (float)sg * gp[y * g.w + x];
-            sx = fmaf(gv, (1.0f - fy) * (t01 - t00) + fy * (t11 - t10), sx);
-            sy = fmaf(gv, (1.0f - fx) * (t10 - t00) + fx * (t11 - t01), sy);
+    const float* R = res + ((int64_t)c * g.n_nodes + g.node_base[l] + (B & ~1) * na + (A & ~1)) * plane;
+    const float* gp = gres_pred + ((int64_t)c * g.n_nodes + g.node_base[l] + B * na + A) * plane;
+    const int64_t rec0 = g.rec_base[c][l] + (int64_t)pord * g.nblk;
+    const uint32_t* code = p.mv + g.sig_word[c][l];
+    const uint32_t j0 = (uint32_t)pord * (uint32_t)g.nblk;
+
+    const int lane = threadIdx.x & (G - 1);
+    const int sub = LG == 6 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> LG);
+    const int blk0 = ((int)blockIdx.x - cn * groups) * PER + sub * U;
+    constexpr int N = QUADS ? 4 : 1;           // pixels per item
+    const int rowl = g.bsl - (QUADS ? 2 : 0);  // log2 items per block row
+    const int items = 1 << (g.bsl + rowl);
+    AdRec d[U];
+    float sx[U], sy[U];
+    bool some[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int blk = min(blk0 + u, g.nblk - 1);  // past the end: the last block again, not stored
+        const uint32_t j = j0 + (uint32_t)blk, cw = (code[j >> 4] >> (2u * (j & 15u))) & 3u;
+        d[u] = ad_split(g, cw == 0u ? 1 : (cw == 1u ? -1 : 0), shift[rec0 + blk]);
+        sx[u] = sy[u] = 0.0f;
+        some[u] = false;
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int blk = min(blk0 + u, g.nblk - 1);
+        const int ky = blk / g.nbx;
+        const int by0 = ky << g.bsl, bx0 = (blk - ky * g.nbx) << g.bsl;
+        const float fx = d[u].fx, fy = d[u].fy, gx = 1.0f - fx, gy = 1.0f - fy, sg = (float)d[u].sg;
+        if (d[u].sg)
+            for (int q = lane; q < items; q += G) {
+                const int y = by0 + (q >> rowl), x = bx0 + (q & ((1 << rowl) - 1)) * N;
+                float gv[N];
+                if (QUADS) {
+                    const float4 t = *reinterpret_cast<const float4*>(gp + y * g.w + x);
+                    gv[0] = t.x;
+                    gv[N > 1 ? 1 : 0] = t.y;
+                    gv[N > 2 ? 2 : 0] = t.z;
+                    gv[N > 3 ? 3 : 0] = t.w;
+                } else {
+                    gv[0] = gp[y * g.w + x];
+                }
+                const int ra = lf_clampi(y + d[u].iy, 0, g.h - 1) * g.w, rb = lf_clampi(y + d[u].iy + 1, 0, g.h - 1) * g.w;
+                float ta[N + 1], tb[N + 1];
+                const int xt = x + d[u].ix;
+                if (QUADS && xt >= 0 && xt + 4 < g.w) {
+                    const ad_f4 a = *reinterpret_cast<const ad_f4*>(R + ra + xt), b = *reinterpret_cast<const ad_f4*>(R + rb + xt);
+                    ta[N] = R[ra + xt + N];
+                    tb[N] = R[rb + xt + N];
+#pragma unroll
+                    for (int t = 0; t < N; t++) {
+                        ta[t] = a[t];
+                        tb[t] = b[t];
+                    }
+                } else {
+#pragma unroll
+                    for (int t = 0; t <= N; t++) {
+                        const int xc = lf_clampi(xt + t, 0, g.w - 1);
+                        ta[t] = R[ra + xc];
+                        tb[t] = R[rb + xc];
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < N; t++) {
+                    some[u] |= gv[t] != 0.0f;
+                    const float v = sg * gv[t];
+                    sx[u] = fmaf(v, gy * (ta[t + 1] - ta[t]) + fy * (tb[t + 1] - tb[t]), sx[u]);
+                    sy[u] = fmaf(v, gx * (tb[t] - ta[t]) + fx * (tb[t + 1] - ta[t + 1]), sy[u]);
+                }
+            }
+    }
+    uint64_t any[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        any[u] = __ballot(some[u]);
+        if (LG < 6) any[u] = (any[u] >> (threadIdx.x & 63 & ~(G - 1))) & ((1ull << (G & 63)) - 1ull);
+#pragma unroll
+        for (int o = G / 2; o >= 1; o >>= 1) {
+            sx[u] += __shfl_xor(sx[u], o, 64);
+            sy[u] += __shfl_xor(sy[u], o, 64);
         }
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        sx += __shfl_xor(sx, o, 64);
-        sy += __shfl_xor(sy, o, 64);
-    }
-    if (lane == 0) gshift[rec] = make_float2(sx, sy);
+    for (int u = 0; u < U; u++)
+        if (lane == u && blk0 + u < g.nblk) {
+            gshift[rec0 + blk0 + u] = make_float2(sx[u], sy[u]);
+            // a block whose gradients are all zero adds zero to its reference
+            // through finite weights: its record is empty
+            AdRec e = d[u];
+            if (!any[u] && e.fx * 0.0f == 0.0f && e.fy * 0.0f == 0.0f) e.sg = 0;
+            brec[rec0 + blk0 + u] = ad_pack(e);
+        }
 }
 
 extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_residual, const float* d_shift,
@@ -882,19 +967,30 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     float* parts = (float*)(W + Bl.o_parts);
     hipLaunchKernelGGL(k_ad_maxshift, dim3(AD_MAX_PARTS), dim3(256), 0, s, (const float2*)d_shift, h->L.n_rec, parts);
     hipLaunchKernelGGL(k_ad_maxparts, dim3(1), dim3(256), 0, s, parts, AD_MAX_PARTS, mxs);
-    // shift gradients read the predictive nodes' gradients, which the
-    // reference pass leaves untouched; run them first to keep the order plain
-    if (h->L.n_rec > 0)
-        hipLaunchKernelGGL(k_ad_shift, dim3((unsigned)((h->L.n_rec + 3) / 4)), dim3(256), 0, s, g, h->p, d_residual,
-                           (const float2*)d_shift, d_grad_residual, (float2*)d_grad_shift, h->L.n_rec);
-    {
-        const int64_t n_tiles = 3 * (int64_t)g.n_refs * ((g.w + AD_TILE - 1) / AD_TILE) * ((g.h + AD_TILE - 1) / AD_TILE);
-        int4* brec = (int4*)(W + Bl.o_brec);
-        if (h->L.n_rec > 0)
-            hipLaunchKernelGGL(k_ad_blockrec, dim3((unsigned)((h->L.n_rec + 255) / 256)), dim3(256), 0, s, g, h->p,
-                               (const float2*)d_shift, h->L.n_rec, brec);
-        hipLaunchKernelGGL(k_ad_reference, dim3((unsigned)std::min<int64_t>(std::max<int64_t>(n_tiles, 1), 65536)),
-                           dim3(256), 0, s, g, (const int4*)brec, mxs, d_grad_residual);
+    // the shift pass reads the predictive nodes' gradients, which the
+    // reference pass leaves untouched, and writes the block records it pulls from
+    int4* brec = (int4*)(W + Bl.o_brec);
+    if (h->L.n_rec > 0) {
+        // rows of four pixels are read as one 128-bit load: blocks of at least
+        // 4x4 and a 16-byte aligned gradient buffer, else one pixel at a time
+        const bool quads = g.bs >= 4 && !(((uintptr_t)d_grad_residual) & 15);
+        const int lg = !quads ? 6 : (g.bs == 4 ? 2 : (g.bs == 8 ? 4 : 6));  // log2 lanes per block
+        const int per_wg = (lg == 6 ? AD_SHIFT_U : 1) * (256 >> lg), groups = (g.nblk + per_wg - 1) / per_wg;
+        AdPred pn = {};
+        for (int l = g.H - 1; l >= 0; l--) {
+            pn.first[l] = pn.total;
+            pn.total += (g.nb_l[l] / 2) * g.na_l[l] + ((g.nb_l[l] + 1) / 2) * (g.na_l[l] / 2);
+        }
+        const auto kern = !quads    ? k_ad_shift<6, false>
+                          : lg == 2 ? k_ad_shift<2, true>
+                          : lg == 4 ? k_ad_shift<4, true>
+                                    : k_ad_shift<6, true>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(3 * pn.total * groups)), dim3(256), 0, s, g, h->p, pn, groups,
+                           d_residual, (const float2*)d_shift, d_grad_residual, (float2*)d_grad_shift, brec);
     }
+    const int64_t n_tiles = 3 * (int64_t)g.n_refs * ((g.w + AD_TILE - 1) / AD_TILE) * ((g.h + AD_TILE - 1) / AD_TILE);
+    if (h->L.n_rec > 0)  // without predictive blocks the references keep their own gradients
+        hipLaunchKernelGGL(k_ad_reference, dim3((unsigned)((n_tiles + 31) / 32 * 8)), dim3(256), 0, s, g,
+                           (const int4*)brec, mxs, d_grad_residual);
     return lf_check_launch("render_backward");
 }

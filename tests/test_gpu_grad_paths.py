@@ -1,0 +1,81 @@
+"""The adjoint's kernels at the sizes where their paths change, against the oracle.
+
+Tolerances are those of the FP32 adjoint against the oracle's FP64 reverse
+mode: 1e-3 of each element plus 1e-6 (residuals) or 1e-5 (shifts) of the
+largest one.
+"""
+
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import lfscene
+import oracle
+from conftest import crop_lf
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+
+    assert torch.cuda.is_available()
+    return torch
+
+
+def _field(na, nb, h, w, block, levels=2, **enc):
+    from paper_1902_09396_amd import lf
+
+    cfg = lfscene.get_config("tiny", levels=levels, step=[4] * levels, win=[4] * levels, t_ref=[0] * levels,
+                             t_pred=[0] * levels, block=block, **enc)
+    stream = oracle.encode(crop_lf("tiny", na, nb, h, w), cfg["enc"])
+    return oracle.OracleLF(stream), lf.LightField(stream)
+
+
+def _params(torch, field, seed, spread):
+    rng = np.random.default_rng(seed)
+    res, sh = field.export_params()
+    far = sh.cpu().numpy() + rng.uniform(-spread, spread, size=tuple(sh.shape)).astype(np.float32)
+    return rng, res, torch.from_numpy(far.astype(np.float32)).cuda()
+
+
+def _compare(o, res, sh, cams, wo, ho, g, got_r, got_s):
+    o_r, o_s = o.relaxed_grad(res.cpu().numpy(), sh.cpu().numpy(), cams, wo, ho, g.astype(np.float64))
+    got_r, got_s = got_r.cpu().numpy().astype(np.float64), got_s.cpu().numpy().astype(np.float64)
+    for got, ref, floor in ((got_r, o_r, 1e-6), (got_s, o_s, 1e-5)):
+        err = np.abs(got - ref)
+        assert np.all(err <= 1e-3 * np.abs(ref) + floor * np.abs(ref).max() + 1e-12), err.max()
+
+
+@pytest.mark.parametrize("block,h,w,views", [(1, 5, 7, 2), (4, 28, 36, 1), (8, 40, 48, 2), (16, 48, 32, 1), (32, 32, 64, 2)])
+def test_reference_and_shift_passes(torch, block, h, w, views):
+    """Blocks of one pixel, of one to several lanes' quads and of several
+    rounds of a wave; planes that are not whole 16x16 tiles; one view only,
+    which leaves most blocks without a gradient."""
+    o, field = _field(5, 3, h, w, block, no_mc=block == 1)
+    rng, res, sh = _params(torch, field, block, 3.0)
+    cams = lfscene.random_pinhole_cameras(views, 5, 3, w, h, 21, 17, seed=block)
+    g = rng.normal(size=(views, 3, 17, 21)).astype(np.float32)
+    got = field.render_backward(res, sh, torch.from_numpy(cams).cuda(), 21, 17, torch.from_numpy(g).cuda())
+    _compare(o, res, sh, cams, 21, 17, g, *got)
+
+
+def test_gradient_buffer_alignment(torch):
+    """A gradient buffer that is not 16-byte aligned gives the same gradients."""
+    from paper_1902_09396_amd import lf
+
+    o, field = _field(4, 3, 32, 48, 8)
+    rng, res, sh = _params(torch, field, 7, 1.0)
+    cams = lfscene.random_pinhole_cameras(2, 4, 3, 48, 32, 30, 20, seed=3)
+    g = rng.normal(size=(2, 3, 20, 30)).astype(np.float32)
+    dc, dg = torch.from_numpy(cams).cuda(), torch.from_numpy(g).cuda()
+    need = C.c_int64()
+    lf.check(lf.lib().lf_backward_workspace(field.handle, 2, 30, 20, C.byref(need)))
+    ws = torch.empty(need.value, dtype=torch.uint8, device="cuda")
+    buf = torch.empty(res.numel() + 1, device="cuda")
+    g_res, g_sh = buf[1:].view(res.shape), torch.empty_like(sh)
+    lf.check(lf.lib().lf_render_backward(field.handle, lf._ptr(res), lf._ptr(sh), lf._ptr(dc), 2, 30, 20, lf._ptr(dg),
+                                         lf._ptr(g_res), lf._ptr(g_sh), lf._ptr(ws), need.value, lf._stream()))
+    _compare(o, res, sh, cams, 30, 20, g, g_res, g_sh)
