@@ -13,30 +13,32 @@
 // fraction (floor(x + dx) = x + floor(dx)), which both directions use.
 //
 // Adjoint, deterministic and without atomics:
-//  1. every ray emits one record per light-field view it blends, keyed by
-//     the sample at the top-left of its 2x2 pixel footprint in that view
-//     (ray * 4 + view corner), and its four blend fractions;
-//  2. a stable radix sort groups the records by key, and a table gives the
-//     first record of each key;
-//  3. every sample gathers the records keyed at itself and at its left, upper
-//     and upper-left neighbours (the footprints that cover it), in that order
-//     and in ray order within each, forms each ray's blend weight from its
-//     fractions and applies the colour transpose, writing the sample
-//     gradients into the level-0 node planes;
-//  4. node gradients are summed up the tree level by level in fixed order;
+//  1. views whose homographies separate by axis get per-view tables of the
+//     columns and rows that reach each light-field column, row and view;
+//  2. if some view does not separate, its rays emit one record per
+//     light-field view they blend, keyed by the sample at the top-left of
+//     their 2x2 pixel footprint (ray * 4 + view corner), which a stable radix
+//     sort groups by key;
+//  3. every sample gathers the rays that reach it, view by view from the
+//     tables, then from the records keyed at itself and at its left, upper
+//     and upper-left neighbours in ray order, and applies the colour
+//     transpose, writing the level-0 node gradients and, from registers, up
+//     to two levels of their sums;
+//  4. the remaining levels are summed level by level in fixed order;
 //  5. each block's shift gradient is a fixed-order reduction over its pixels,
 //     and the block leaves a record: phase, split shift, and whether any of
 //     its gradients is non-zero;
 //  6. each reference residual pulls the phase-signed bilinear transpose of
 //     its predictive siblings' gradients, from the recorded blocks.
 #include <hip/hip_runtime.h>
-#include <hipcub/hipcub.hpp>
 
 #include <algorithm>
 
 #include "lf_internal.h"
 
 #define AD_MAX_PARTS 1024  // partial maxima of the shift reduction
+#define AD_SORT_WG 512     // workgroups of the record sort, each owning a range of the records
+#define AD_SORT_T 1024     // threads of each
 #define AD_TILE 16         // reference tile side of the pull kernel
 #define AD_FAR 48          // reach up to which positions outside the image are folded (three tiles)
 
@@ -275,9 +277,10 @@ extern "C" lf_status lf_render_relaxed(const lf_handle* h, const float* d_residu
 
 struct BwdLayout {
     int64_t n_recs, n_samples;
-    int end_bit;
-    size_t sort_bytes;
-    int64_t o_kin, o_kout, o_vin, o_vout, o_sort, o_start, o_max, o_parts, o_rayf, o_brec, total;
+    int passes;     // of the record sort, 8 bits each
+    bool use_axes;  // build the separable views' tables
+    int64_t o_kin, o_kout, o_vin, o_vout, o_hist, o_start, o_max, o_parts, o_rayf, o_brec;
+    int64_t o_sep, o_col, o_row, o_rx, o_ry, o_ra, o_rb, o_count, o_list, total;
 };
 
 static int64_t al256(int64_t v) { return (v + 255) & ~(int64_t)255; }
@@ -287,32 +290,50 @@ static lf_status bwd_layout(const lf_handle* h, int nv, int wo, int ho, BwdLayou
     const LfGeom& g = h->L.g;
     B->n_recs = (int64_t)nv * wo * ho * 4;
     B->n_samples = (int64_t)g.na * g.nb * g.w * g.h;
-    // the record sort takes an int count: at most 2^31 - 1 records (2^29 - 1 rays per call)
+    // records are numbered with 32 bits: at most 2^31 - 1 (2^29 - 1 rays per call)
     if (B->n_recs > 0x7FFFFFFFll) return lf_fail(LF_EINVAL, "too many rays for one backward call (at most 2^29 - 1)");
     if (B->n_samples >= 0xFFFFFFFFll) return lf_fail(LF_EINVAL, "too many light-field samples");
     // the reference pull indexes its 16x16 tiles with 32-bit integers
     if (3 * (int64_t)g.n_refs * ((g.w + AD_TILE - 1) / AD_TILE) * ((g.h + AD_TILE - 1) / AD_TILE) > 0x7FFFFFFFll)
         return lf_fail(LF_EINVAL, "too many reference tiles for the adjoint");
-    int eb = 1;
-    while (eb < 32 && ((int64_t)1 << eb) < B->n_samples) eb++;
-    B->end_bit = eb;
-    size_t sb = 0;
-    if (hipcub::DeviceRadixSort::SortPairs(nullptr, sb, (uint32_t*)nullptr, (uint32_t*)nullptr, (uint32_t*)nullptr,
-                                           (uint32_t*)nullptr, (int)B->n_recs, 0, eb) != hipSuccess)
-        return lf_fail(LF_EDEVICE, "sort workspace query failed");
-    B->sort_bytes = sb;
-    const int64_t pb = al256(B->n_recs * 4);
-    B->o_kin = 0;
-    B->o_kout = B->o_kin + pb;
-    B->o_vin = B->o_kout + pb;
-    B->o_vout = B->o_vin + pb;
-    B->o_sort = B->o_vout + pb;
-    B->o_start = B->o_sort + al256((int64_t)sb);
-    B->o_max = B->o_start + al256(B->n_samples * 4);
-    B->o_parts = B->o_max + 256;
-    B->o_rayf = B->o_parts + al256(AD_MAX_PARTS * 4);
-    B->o_brec = B->o_rayf + al256(B->n_recs / 4 * 16);  // one float4 per ray
-    B->total = B->o_brec + al256(h->L.n_rec * 16);         // one split shift per predictive block
+    int eb = 1;  // keys 0 .. n_samples
+    while (eb < 32 && ((int64_t)1 << eb) <= B->n_samples) eb++;
+    B->passes = (eb + 7) / 8;
+    // The separable views' gather walks, per sample, the views that reach its
+    // light-field view: worth it while a view's pixels outnumber a light-field
+    // view's samples / 256 (a walked view costs a wave of 64 samples about 20
+    // cycles, a sorted record about 45 ps), and while the tables stay
+    // smaller than the records.
+    const int64_t tables = (int64_t)nv * (16 * ((int64_t)wo + ho) + 8 * ((int64_t)g.w + g.h + g.na + g.nb) +
+                                          4 * (int64_t)g.na * g.nb + 4);
+    B->use_axes = (int64_t)wo * ho * 256 >= (int64_t)g.w * g.h && tables <= 16 * B->n_recs + (1 << 20);
+    int64_t o = 0;
+    auto take = [&](int64_t bytes) {
+        const int64_t at = o;
+        o += al256(bytes);
+        return at;
+    };
+    B->o_kin = take(B->n_recs * 4);
+    B->o_kout = take(B->n_recs * 4);
+    B->o_vin = take(B->n_recs * 4);
+    B->o_vout = take(B->n_recs * 4);
+    B->o_hist = take(AD_SORT_WG * 256 * 4);
+    B->o_start = take(B->n_samples * 4);
+    B->o_max = take(256);  // largest shift, then the flag "some view does not separate"
+    B->o_parts = take(AD_MAX_PARTS * 4);
+    B->o_rayf = take(B->n_recs / 4 * 16);  // one float4 per ray
+    B->o_brec = take(h->L.n_rec * 16);     // one split shift per predictive block
+    const int64_t k = B->use_axes ? nv : 0;
+    B->o_sep = take(k * 4);
+    B->o_col = take(k * wo * 16);
+    B->o_row = take(k * ho * 16);
+    B->o_rx = take(k * g.w * 8);
+    B->o_ry = take(k * g.h * 8);
+    B->o_ra = take(k * g.na * 8);
+    B->o_rb = take(k * g.nb * 8);
+    B->o_count = take(k ? (int64_t)g.na * g.nb * 4 : 0);
+    B->o_list = take(k * g.na * g.nb * 4);
+    B->total = o;
     return LF_OK;
 }
 
@@ -328,86 +349,434 @@ extern "C" lf_status lf_backward_workspace(const lf_handle* h, int32_t n_views, 
     return LF_OK;
 }
 
-__global__ void k_ad_records(LfGeom g, const float* __restrict__ cams, int nv, int wo, int ho,
-                             uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, float4* __restrict__ rayf)
+// ---- rays whose axes separate ----
+//
+// With every third row (0, 0, 1) and no cross terms, a camera's (u, s) depend
+// on the pixel column alone and (v, t) on the row alone, each monotone along
+// its axis.  The rays reaching sample (b, a, y, x) are then the pixels of a
+// rectangle: columns whose x0 is x - 1 or x and whose a0 is a - 1 or a, rows
+// likewise, and their blend weights are products of a column and a row factor.
+// Such views need no records and no sort: per view, tables of the columns and
+// rows and of the intervals that reach each x, y, a and b.
+struct AdAxes {
+    int* sep;               // [nv] 1: the view's axes separate
+    int* general;           // [1] 1: some view's do not
+    float4 *col, *row;      // [nv][wo], [nv][ho]: (x0 | a0 << 16, fs, fu), (y0 | b0 << 16, ft, fv)
+    int2 *rx, *ry, *ra, *rb;  // [nv][w], [nv][h], [nv][na], [nv][nb]: first and past-the-last column or row
+    int *count, *list;      // [nb na], [nb na][nv]: separating views that reach light-field view (b, a), in order
+};
+
+__device__ __forceinline__ bool ad_separates(const float* __restrict__ cam)
 {
-    const int64_t npix = (int64_t)wo * ho;
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= npix * nv) return;
-    const int v = (int)(r / npix);
-    const int64_t px = r - (int64_t)v * npix;
-    const AdRay ry = ad_ray(g, cams + 18 * v, (int)(px % wo), (int)(px / wo));
-    rayf[r] = make_float4(ry.fu, ry.fv, ry.fs, ry.ft);  // the blend fractions, for the gather pass
+    bool ok = true;
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int b = (q & 2) ? ry.b1 : ry.b0, a = (q & 1) ? ry.a1 : ry.a0;
-        keys[r * 4 + q] = (uint32_t)((((int64_t)b * g.na + a) * g.h + ry.y0) * g.w + ry.x0);
-        vals[r * 4 + q] = (uint32_t)(r * 4 + q);
+    for (int h = 0; h < 18; h += 9) {
+        ok = ok && cam[h + 6] == 0.0f && cam[h + 7] == 0.0f && cam[h + 8] == 1.0f && cam[h + 1] == 0.0f && cam[h + 3] == 0.0f;
+        // finite: x - x is 0 only for finite x
+        ok = ok && cam[h] - cam[h] == 0.0f && cam[h + 2] - cam[h + 2] == 0.0f && cam[h + 4] - cam[h + 4] == 0.0f &&
+             cam[h + 5] - cam[h + 5] == 0.0f;
+    }
+    return ok;
+}
+
+// Lower neighbour and fraction along one axis of n samples: coordinate 0 (u)
+// or 1 (v) of homography h at pixel column (row) i.
+__device__ __forceinline__ int ad_axis_at(const float* __restrict__ h, int which, int i, int n, float* f)
+{
+    float x, y;
+    int k0, k1;
+    lf_ray_h(h, (float)i + 0.5f, (float)i + 0.5f, x, y);  // no cross terms: the other pixel coordinate does not enter
+    lf_axis(which ? y : x, n, k0, k1, *f);
+    return k0;
+}
+
+// Interval of i in [0, len) whose lower neighbour is k - 1 or k.
+__device__ __forceinline__ int2 ad_interval(const float* __restrict__ h, int which, int len, int n, int k)
+{
+    const bool up = h[which ? 4 : 0] >= 0.0f;  // the neighbour grows (or stays) with i, else it falls
+    int edge[2];
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        // first i whose neighbour is at least k - 1, then k + 1 (at most k, then k - 2)
+        const int want = up ? k - 1 + 2 * e : k - 2 * e;
+        int lo = 0, hi = len;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            float f;
+            const int at = ad_axis_at(h, which, mid, n, &f);
+            if (up ? at >= want : at <= want)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        edge[e] = lo;
+    }
+    return make_int2(edge[0], edge[1]);
+}
+
+// One thread per table entry of one view: columns, rows, then the intervals.
+// The interval search costs 2 log2(len) coordinate evaluations.
+__global__ void k_ad_axes(LfGeom g, const float* __restrict__ cams, int nv, int wo, int ho, AdAxes t)
+{
+    const int64_t per = (int64_t)wo + ho + g.w + g.h + g.na + g.nb;
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= per * nv) return;
+    const int64_t v = id / per;
+    int e = (int)(id - v * per);
+    const float* cam = cams + 18 * v;
+    const bool sep = ad_separates(cam);
+    if (e == 0) {
+        t.sep[v] = sep;
+        if (!sep) *t.general = 1;  // cleared by an earlier kernel; every writer stores 1
+    }
+    if (!sep) return;
+    float fc, fu;
+    if (e < wo) {
+        const int x0 = ad_axis_at(cam + 9, 0, e, g.w, &fc), a0 = ad_axis_at(cam, 0, e, g.na, &fu);
+        t.col[v * wo + e] = make_float4(__int_as_float(x0 | (a0 << 16)), fc, fu, 0.0f);
+        return;
+    }
+    e -= wo;
+    if (e < ho) {
+        const int y0 = ad_axis_at(cam + 9, 1, e, g.h, &fc), b0 = ad_axis_at(cam, 1, e, g.nb, &fu);
+        t.row[v * ho + e] = make_float4(__int_as_float(y0 | (b0 << 16)), fc, fu, 0.0f);
+        return;
+    }
+    e -= ho;
+    if (e < g.w) {
+        t.rx[v * g.w + e] = ad_interval(cam + 9, 0, wo, g.w, e);
+        return;
+    }
+    e -= g.w;
+    if (e < g.h) {
+        t.ry[v * g.h + e] = ad_interval(cam + 9, 1, ho, g.h, e);
+        return;
+    }
+    e -= g.h;
+    if (e < g.na)
+        t.ra[v * g.na + e] = ad_interval(cam, 0, wo, g.na, e);
+    else
+        t.rb[v * g.nb + e - g.na] = ad_interval(cam, 1, ho, g.nb, e - g.na);
+}
+
+// Separating views that reach each light-field view, in view order: one
+// wave64 per light-field view.
+__global__ void __launch_bounds__(256) k_ad_lists(LfGeom g, int nv, AdAxes t)
+{
+    const int k = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (k >= g.na * g.nb) return;  // uniform per wave
+    const int b = k / g.na, a = k - b * g.na;
+    int n = 0;
+    for (int v0 = 0; v0 < nv; v0 += 64) {
+        const int v = v0 + lane;
+        bool hit = false;
+        if (v < nv && t.sep[v]) {
+            const int2 ra = t.ra[(int64_t)v * g.na + a], rb = t.rb[(int64_t)v * g.nb + b];
+            hit = ra.x < ra.y && rb.x < rb.y;
+        }
+        const uint64_t m = __ballot(hit);
+        if (hit) t.list[(int64_t)k * nv + n + __popcll(m & ((1ull << lane) - 1ull))] = v;
+        n += __popcll(m);
+    }
+    if (lane == 0) t.count[k] = n;
+}
+
+// ---- the other rays: records sorted by the sample they reach ----
+//
+// A stable least-significant-digit radix sort of (key, record), 8 bits a
+// pass, AD_SORT_WG workgroups each owning one contiguous range of the
+// records: count the range's digits, then scatter in order.  Every kernel
+// returns at once when all views separate.
+struct AdSort {
+    uint32_t *kin, *kout, *vin, *vout;  // ping-pong; the sorted records end in kin, vin after an even number of passes
+    uint32_t* hist;                     // [AD_SORT_WG][256]
+    int64_t n;                          // records: 4 per ray
+    int64_t per;                        // records per workgroup (a multiple of 4)
+};
+
+__device__ __forceinline__ void ad_sort_count(uint32_t (&h)[256], const uint32_t* __restrict__ keys, int64_t begin, int64_t end,
+                                              int shift)
+{
+    for (int64_t i = begin + threadIdx.x; i < end; i += AD_SORT_T) atomicAdd(&h[(keys[i] >> shift) & 255u], 1u);
+}
+
+// Records and blend fractions of every ray (a view that separates gets the
+// key past every sample), the first digit's counts, and the empty key table.
+__global__ void __launch_bounds__(AD_SORT_T) k_ad_records(LfGeom g, const float* __restrict__ cams, int nv, int wo, int ho,
+                                                          AdAxes t, int all_general, AdSort s, float4* __restrict__ rayf,
+                                                          uint32_t* __restrict__ start, int64_t n_samples)
+{
+    if (!all_general && !*t.general) return;
+    __shared__ uint32_t h[256];
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t npix = (int64_t)wo * ho, rays = npix * nv;
+    const int64_t begin = (int64_t)blockIdx.x * s.per / 4, end = min(begin + s.per / 4, rays);
+    for (int64_t r = begin + threadIdx.x; r < end; r += AD_SORT_T) {
+        const int v = (int)(r / npix);
+        const int64_t px = r - (int64_t)v * npix;
+        const bool use = all_general || !t.sep[v];
+        const AdRay ry = ad_ray(g, cams + 18 * (int64_t)v, (int)(px % wo), (int)(px / wo));
+        rayf[r] = make_float4(ry.fu, ry.fv, ry.fs, ry.ft);  // the blend fractions, for the gather pass
+        uint32_t key[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int b = (q & 2) ? ry.b1 : ry.b0, a = (q & 1) ? ry.a1 : ry.a0;
+            key[q] = use ? (uint32_t)((((int64_t)b * g.na + a) * g.h + ry.y0) * g.w + ry.x0) : (uint32_t)n_samples;
+            atomicAdd(&h[key[q] & 255u], 1u);
+        }
+        reinterpret_cast<uint4*>(s.kin)[r] = make_uint4(key[0], key[1], key[2], key[3]);
+        const uint32_t r4 = (uint32_t)(r * 4);
+        reinterpret_cast<uint4*>(s.vin)[r] = make_uint4(r4, r4 + 1u, r4 + 2u, r4 + 3u);
+    }
+    for (int64_t i = (int64_t)blockIdx.x * AD_SORT_T + threadIdx.x; i < n_samples; i += (int64_t)gridDim.x * AD_SORT_T)
+        start[i] = 0xFFFFFFFFu;
+    __syncthreads();
+    if (threadIdx.x < 256) s.hist[blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+}
+
+__global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_count(const int* __restrict__ general, int all_general, AdSort s,
+                                                             const uint32_t* __restrict__ keys, int shift)
+{
+    if (!all_general && !*general) return;
+    __shared__ uint32_t h[256];
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t begin = (int64_t)blockIdx.x * s.per;
+    ad_sort_count(h, keys, begin, min(begin + s.per, s.n), shift);
+    __syncthreads();
+    if (threadIdx.x < 256) s.hist[blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+}
+
+__global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_scatter(const int* __restrict__ general, int all_general, AdSort s,
+                                                               const uint32_t* __restrict__ ki, const uint32_t* __restrict__ vi,
+                                                               uint32_t* __restrict__ ko, uint32_t* __restrict__ vo, int shift)
+{
+    if (!all_general && !*general) return;
+    constexpr int W = AD_SORT_T / 64;
+    __shared__ uint32_t base[256];          // next output place of each digit
+    __shared__ uint32_t cnt[W][256];        // this round's digit counts per wave
+    __shared__ uint32_t wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    // digit d: records of it in the workgroups before this one, and in all
+    {
+        const int d = tid & 255, part = tid >> 8;  // four threads per digit, a quarter of the workgroups each
+        uint32_t before = 0, all = 0;
+        for (int w = part * (AD_SORT_WG / 4); w < (part + 1) * (AD_SORT_WG / 4); w++) {
+            const uint32_t c = s.hist[w * 256 + d];
+            all += c;
+            before += w < (int)blockIdx.x ? c : 0u;
+        }
+        cnt[part][d] = before;
+        cnt[4 + part][d] = all;
+    }
+    __syncthreads();
+    uint32_t before = 0, all = 0, inc = 0;
+    if (tid < 256) {
+        for (int q = 0; q < 4; q++) {
+            before += cnt[q][tid];
+            all += cnt[4 + q][tid];
+        }
+        inc = all;  // inclusive scan over the 256 digits
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
+            if (lane >= o) inc += t;
+        }
+        if (lane == 63) wsum[wv] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        for (int q = 0; q < wv; q++) inc += wsum[q];
+        base[tid] = inc - all + before;
+    }
+    for (int i = tid; i < W * 256; i += AD_SORT_T) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+    const int64_t begin = (int64_t)blockIdx.x * s.per, end = min(begin + s.per, s.n);
+    for (int64_t i0 = begin; i0 < end; i0 += AD_SORT_T) {
+        const int64_t i = i0 + tid;
+        const bool in = i < end;
+        const uint32_t key = in ? ki[i] : 0u, val = in ? vi[i] : 0u;
+        const uint32_t d = (key >> shift) & 255u;
+        // lanes of the wave with the same digit
+        uint64_t same = __ballot(in);
+#pragma unroll
+        for (int bit = 0; bit < 8; bit++) {
+            const bool one = (d >> bit) & 1u;
+            const uint64_t m = __ballot(one);
+            same &= one ? m : ~m;
+        }
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
+        if (in && rank == 0) cnt[wv][d] = (uint32_t)__popcll(same);
+        __syncthreads();
+        if (in) {
+            uint32_t at = base[d] + (uint32_t)rank;
+            for (int q = 0; q < wv; q++) at += cnt[q][d];
+            ko[at] = key;
+            vo[at] = val;
+        }
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t sum = 0;
+            for (int q = 0; q < W; q++) {
+                sum += cnt[q][tid];
+                cnt[q][tid] = 0;
+            }
+            base[tid] += sum;
+        }
+        __syncthreads();
     }
 }
 
-__global__ void k_ad_nostart(uint32_t* __restrict__ start, int64_t n)
-{
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x)
-        start[t] = 0xFFFFFFFFu;
-}
-
 // first record of every key present
-__global__ void k_ad_heads(const uint32_t* __restrict__ keys, int64_t n, uint32_t* __restrict__ start)
+__global__ void k_ad_heads(const int* __restrict__ general, int all_general, const uint32_t* __restrict__ keys, int64_t n,
+                           int64_t n_samples, uint32_t* __restrict__ start)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t k = keys[i];
-    if (i == 0 || keys[i - 1] != k) start[k] = (uint32_t)i;
+    if (!all_general && !*general) return;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t k = keys[i];
+        if ((int64_t)k < n_samples && (i == 0 || keys[i - 1] != k)) start[k] = (uint32_t)i;
+    }
 }
 
-// One thread per light-field sample ((b * na + a) * h + y) * w + x, which is
-// also the offset of pixel (y, x) in the level-0 node planes of a channel, so
-// the YCoCg sample gradients go straight into the residual gradient (channel
-// stride cstride); samples no ray reaches get zero.  A record keyed at the
+struct AdGather {
+    AdAxes t;
+    int use_axes, all_general;
+    const float4* rayf;
+    const float* grad_out;
+    const uint32_t *keys, *vals, *start;
+    int64_t n_recs;
+    int nv, wo, ho;
+};
+
+// Gradient of the RGB sample (b, a, y, x): over the separating views that
+// reach view (b, a), the rectangle of their pixels that reach (y, x); then,
+// if some view does not separate, the sorted records keyed at the sample and
+// at its left, upper and upper-left neighbours.  A record keyed at the
 // footprint corner (y0, x0) reaches pixel corner (cy, cx) at (y0 + cy, x0 +
 // cx), except along an axis of length 1, where both corners are pixel 0.
-__global__ void k_ad_samples(const float4* __restrict__ rayf, int wo, int ho, const float* __restrict__ grad_out,
-                             const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals,
-                             const uint32_t* __restrict__ start, int64_t n_recs, int64_t n_samples, int w, int h,
-                             int64_t cstride, float* __restrict__ g0 /* level-0 planes of channel 0 */)
+__device__ __forceinline__ void ad_sample(const LfGeom& g, const AdGather& G, int b, int a, int y, int x, bool general,
+                                          float (&acc)[3])
 {
-    const int64_t S = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (S >= n_samples) return;
-    const int64_t npix = (int64_t)wo * ho;
-    const int x = (int)(S % w), y = (int)((S / w) % h);
-    float acc[3] = {0.0f, 0.0f, 0.0f};
+    const int64_t npix = (int64_t)G.wo * G.ho;
+    acc[0] = acc[1] = acc[2] = 0.0f;
+    if (G.use_axes) {
+        const int k = b * g.na + a, n = G.t.count[k];
+        for (int q = 0; q < n; q++) {
+            const int v = __builtin_amdgcn_readfirstlane(G.t.list[(int64_t)k * G.nv + q]);
+            const int2 ra = G.t.ra[(int64_t)v * g.na + a], rb = G.t.rb[(int64_t)v * g.nb + b];
+            const int2 rx = G.t.rx[(int64_t)v * g.w + x], ry = G.t.ry[(int64_t)v * g.h + y];
+            const int i0 = max(ra.x, rx.x), i1 = min(ra.y, rx.y), j0 = max(rb.x, ry.x), j1 = min(rb.y, ry.y);
+            const float4* col = G.t.col + (int64_t)v * G.wo;
+            const float4* row = G.t.row + (int64_t)v * G.ho;
+            const float* go = G.grad_out + (int64_t)v * 3 * npix;
+            for (int j = j0; j < j1; j++) {
+                const float4 r = row[j];
+                const int yb = __float_as_int(r.x);
+                const float wy = ((yb & 0xFFFF) == y ? 1.0f - r.y : r.y) * ((yb >> 16) == b ? 1.0f - r.z : r.z);
+                for (int i = i0; i < i1; i++) {
+                    const float4 c = col[i];
+                    const int xa = __float_as_int(c.x);
+                    const float wx = ((xa & 0xFFFF) == x ? 1.0f - c.y : c.y) * ((xa >> 16) == a ? 1.0f - c.z : c.z);
+                    const float wt = wy * wx * (1.0f / 255.0f);
+                    const int64_t px = (int64_t)j * G.wo + i;
+#pragma unroll
+                    for (int ch = 0; ch < 3; ch++) acc[ch] = fmaf(wt, go[ch * npix + px], acc[ch]);
+                }
+            }
+        }
+    }
+    if (!general) return;
+    const int64_t S = (((int64_t)b * g.na + a) * g.h + y) * g.w + x;
     for (int cy = 0; cy < 2; cy++) {
-        const int dy = h >= 2 ? cy : 0;
+        const int dy = g.h >= 2 ? cy : 0;
         if (y < dy) continue;
         for (int cx = 0; cx < 2; cx++) {
-            const int dx = w >= 2 ? cx : 0;
+            const int dx = g.w >= 2 ? cx : 0;
             if (x < dx) continue;
-            const uint32_t K = (uint32_t)(S - (int64_t)dy * w - dx);
-            uint32_t j = start[K];
+            const uint32_t K = (uint32_t)(S - (int64_t)dy * g.w - dx);
+            uint32_t j = G.start[K];
             if (j == 0xFFFFFFFFu) continue;
-            for (; (int64_t)j < n_recs && keys[j] == K; j++) {
-                const uint32_t val = vals[j];
+            for (; (int64_t)j < G.n_recs && G.keys[j] == K; j++) {
+                const uint32_t val = G.vals[j];
                 const int64_t ray = val >> 2;
                 const int q = (int)(val & 3u);
                 const int v = (int)(ray / npix);
                 const int64_t px = ray - (int64_t)v * npix;
-                const float4 f = rayf[ray];  // (fu, fv, fs, ft)
+                const float4 f = G.rayf[ray];  // (fu, fv, fs, ft)
                 const float wt = ((q & 2) ? f.y : 1.0f - f.y) * ((q & 1) ? f.x : 1.0f - f.x) *
                                  (cy ? f.w : 1.0f - f.w) * (cx ? f.z : 1.0f - f.z) * (1.0f / 255.0f);
 #pragma unroll
-                for (int c = 0; c < 3; c++) acc[c] = fmaf(wt, grad_out[((int64_t)v * 3 + c) * npix + px], acc[c]);
+                for (int c = 0; c < 3; c++) acc[c] = fmaf(wt, G.grad_out[((int64_t)v * 3 + c) * npix + px], acc[c]);
             }
         }
     }
-    // colour transpose of R = Y + Co/2 - Cg/2, G = Y + Cg/2, B = Y - Co/2 - Cg/2
-    g0[S] = acc[0] + acc[1] + acc[2];
-    g0[cstride + S] = 0.5f * (acc[0] - acc[2]);
-    g0[2 * cstride + S] = 0.5f * (acc[1] - acc[0] - acc[2]);
 }
 
-// node gradients of level l >= 1: the sum of its children's (level 0 holds
-// the sample gradients themselves)
+// Sample gradients and the node gradients above them.  One thread per pixel
+// and cluster of 2^D x 2^D light-field views: it gathers each view's sample
+// gradient, applies the colour transpose, writes the level-0 gradient (zero
+// where no ray reaches), and writes levels 1 .. D as the sums of the children
+// it has in registers, so that no level is read back.  Bound by writing
+// every gradient once: 1.2 GB in 0.43 ms for 17x17 views of 512x512, 16
+// views (records for every ray, a library radix sort, one thread per sample
+// and a pass per tree level: 2.05 ms).
+template <int D>
+__global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int pix_wgs, float* __restrict__ gres)
+{
+    const int cl = (int)blockIdx.x / pix_wgs;
+    const int px = ((int)blockIdx.x - cl * pix_wgs) * 256 + (int)threadIdx.x;
+    const int plane = g.w * g.h;
+    if (px >= plane) return;
+    const int y = px / g.w, x = px - y * g.w;
+    const bool general = G.all_general || *G.t.general;
+    const int nac = (g.na + (1 << D) - 1) >> D;
+    const int B = cl / nac, A = cl - B * nac;  // cluster
+    const int64_t cstride = (int64_t)g.n_nodes * plane;
+    auto put = [&](int l, int Bl, int Al, const float (&v)[3]) {
+        float* o = gres + (int64_t)(g.node_base[l] + Bl * g.na_l[l] + Al) * plane + px;
+        o[0] = v[0];
+        o[cstride] = v[1];
+        o[2 * cstride] = v[2];
+    };
+    auto leaf = [&](int b, int a, float (&o)[3]) {
+        float acc[3];
+        ad_sample(g, G, b, a, y, x, general, acc);
+        // colour transpose of R = Y + Co/2 - Cg/2, G = Y + Cg/2, B = Y - Co/2 - Cg/2
+        o[0] = acc[0] + acc[1] + acc[2];
+        o[1] = 0.5f * (acc[0] - acc[2]);
+        o[2] = 0.5f * (acc[1] - acc[0] - acc[2]);
+        put(0, b, a, o);
+    };
+    if (D == 0) {
+        float o[3];
+        leaf(B, A, o);
+        return;
+    }
+    float top[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int q2 = 0; q2 < (D == 2 ? 4 : 1); q2++) {
+        const int B1 = D == 2 ? 2 * B + (q2 >> 1) : B, A1 = D == 2 ? 2 * A + (q2 & 1) : A;
+        if (B1 >= g.nb_l[1] || A1 >= g.na_l[1]) continue;
+        float mid[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+        for (int q1 = 0; q1 < 4; q1++) {
+            const int b = 2 * B1 + (q1 >> 1), a = 2 * A1 + (q1 & 1);
+            if (b >= g.nb || a >= g.na) continue;
+            float o[3];
+            leaf(b, a, o);
+#pragma unroll
+            for (int c = 0; c < 3; c++) mid[c] += o[c];
+        }
+        put(1, B1, A1, mid);
+#pragma unroll
+        for (int c = 0; c < 3; c++) top[c] += mid[c];
+    }
+    if (D == 2) put(2, B, A, top);
+}
+
+// node gradients of a level the gather pass does not reach: the sum of its
+// children's
 __global__ void k_ad_tree(LfGeom g, int l, float* __restrict__ gres)
 {
     const int64_t plane = (int64_t)g.w * g.h;
@@ -457,7 +826,10 @@ __global__ void k_ad_maxparts(const float* __restrict__ parts, int n, float* __r
         if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = red[0];
+    if (threadIdx.x == 0) {
+        out[0] = red[0];
+        reinterpret_cast<int*>(out)[1] = 0;  // "some view does not separate", set by k_ad_axes
+    }
 }
 
 // pixel range [lo, hi] of [k0, k1] whose tap (x + fd + o), clamped to [0, n-1], equals X
@@ -943,30 +1315,61 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     if (((uintptr_t)d_workspace) & 255) return lf_fail(LF_EINVAL, "workspace must be 256-byte aligned");
     hipStream_t s = (hipStream_t)stream;
     uint8_t* W = (uint8_t*)d_workspace;
-    uint32_t *kin = (uint32_t*)(W + Bl.o_kin), *kout = (uint32_t*)(W + Bl.o_kout);
-    uint32_t *vin = (uint32_t*)(W + Bl.o_vin), *vout = (uint32_t*)(W + Bl.o_vout);
     float* mxs = (float*)(W + Bl.o_max);
-    float4* rayf = (float4*)(W + Bl.o_rayf);
-    const int64_t rays = (int64_t)n_views * width * height;
-    hipLaunchKernelGGL(k_ad_records, dim3((unsigned)((rays + 255) / 256)), dim3(256), 0, s, g, d_cams, n_views,
-                       width, height, kin, vin, rayf);
-    size_t sb = Bl.sort_bytes;
-    if (hipcub::DeviceRadixSort::SortPairs(W + Bl.o_sort, sb, kin, kout, vin, vout, (int)Bl.n_recs, 0, Bl.end_bit, s) !=
-        hipSuccess)
-        return lf_fail(LF_EDEVICE, "radix sort failed");
-    uint32_t* start = (uint32_t*)(W + Bl.o_start);
-    hipLaunchKernelGGL(k_ad_nostart, dim3(4096), dim3(256), 0, s, start, Bl.n_samples);
-    hipLaunchKernelGGL(k_ad_heads, dim3((unsigned)((Bl.n_recs + 255) / 256)), dim3(256), 0, s, kout, Bl.n_recs, start);
-    // level-0 node planes of each channel, every sample written
-    const int64_t plane = (int64_t)g.w * g.h, cstride = (int64_t)g.n_nodes * plane;
-    float* g0 = d_grad_residual + (int64_t)g.node_base[0] * plane;
-    hipLaunchKernelGGL(k_ad_samples, dim3((unsigned)((Bl.n_samples + 255) / 256)), dim3(256), 0, s, rayf, width, height,
-                       d_grad_out, kout, vout, start, Bl.n_recs, Bl.n_samples, g.w, g.h, cstride, g0);
-    for (int l = 1; l < g.H; l++)
-        hipLaunchKernelGGL(k_ad_tree, dim3(8192), dim3(256), 0, s, g, l, d_grad_residual);
     float* parts = (float*)(W + Bl.o_parts);
     hipLaunchKernelGGL(k_ad_maxshift, dim3(AD_MAX_PARTS), dim3(256), 0, s, (const float2*)d_shift, h->L.n_rec, parts);
     hipLaunchKernelGGL(k_ad_maxparts, dim3(1), dim3(256), 0, s, parts, AD_MAX_PARTS, mxs);
+    AdAxes t;
+    t.sep = (int*)(W + Bl.o_sep);
+    t.general = (int*)(W + Bl.o_max) + 1;
+    t.col = (float4*)(W + Bl.o_col);
+    t.row = (float4*)(W + Bl.o_row);
+    t.rx = (int2*)(W + Bl.o_rx);
+    t.ry = (int2*)(W + Bl.o_ry);
+    t.ra = (int2*)(W + Bl.o_ra);
+    t.rb = (int2*)(W + Bl.o_rb);
+    t.count = (int*)(W + Bl.o_count);
+    t.list = (int*)(W + Bl.o_list);
+    const int all_general = !Bl.use_axes;
+    if (Bl.use_axes) {
+        const int64_t items = n_views * ((int64_t)width + height + g.w + g.h + g.na + g.nb);
+        hipLaunchKernelGGL(k_ad_axes, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, g, d_cams, n_views, width,
+                           height, t);
+        hipLaunchKernelGGL(k_ad_lists, dim3((unsigned)((g.na * g.nb + 3) / 4)), dim3(256), 0, s, g, n_views, t);
+    }
+    AdSort srt;
+    srt.kin = (uint32_t*)(W + Bl.o_kin);
+    srt.kout = (uint32_t*)(W + Bl.o_kout);
+    srt.vin = (uint32_t*)(W + Bl.o_vin);
+    srt.vout = (uint32_t*)(W + Bl.o_vout);
+    srt.hist = (uint32_t*)(W + Bl.o_hist);
+    srt.n = Bl.n_recs;
+    srt.per = ((Bl.n_recs / 4 + AD_SORT_WG - 1) / AD_SORT_WG) * 4;
+    float4* rayf = (float4*)(W + Bl.o_rayf);
+    uint32_t* start = (uint32_t*)(W + Bl.o_start);
+    hipLaunchKernelGGL(k_ad_records, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, g, d_cams, n_views, width, height, t,
+                       all_general, srt, rayf, start, Bl.n_samples);
+    uint32_t *ki = srt.kin, *vi = srt.vin, *ko = srt.kout, *vo = srt.vout;
+    for (int ps = 0; ps < Bl.passes; ps++) {
+        if (ps > 0)
+            hipLaunchKernelGGL(k_ad_sort_count, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, t.general, all_general, srt, ki,
+                               8 * ps);
+        hipLaunchKernelGGL(k_ad_sort_scatter, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, t.general, all_general, srt, ki, vi,
+                           ko, vo, 8 * ps);
+        std::swap(ki, ko);
+        std::swap(vi, vo);
+    }
+    hipLaunchKernelGGL(k_ad_heads, dim3((unsigned)std::min<int64_t>((Bl.n_recs + 255) / 256, 8192)), dim3(256), 0, s,
+                       t.general, all_general, ki, Bl.n_recs, Bl.n_samples, start);
+    // level-0 gradients (every sample written) and up to two levels above
+    const int64_t plane = (int64_t)g.w * g.h;
+    AdGather ga{t, Bl.use_axes, all_general, rayf, d_grad_out, ki, vi, start, Bl.n_recs, n_views, width, height};
+    const int D = std::min(g.H - 1, 2), pix_wgs = (int)((plane + 255) / 256);
+    const int64_t clusters = (int64_t)((g.na + (1 << D) - 1) >> D) * ((g.nb + (1 << D) - 1) >> D);
+    hipLaunchKernelGGL(D == 0 ? k_ad_gather<0> : (D == 1 ? k_ad_gather<1> : k_ad_gather<2>),
+                       dim3((unsigned)(clusters * pix_wgs)), dim3(256), 0, s, g, ga, pix_wgs, d_grad_residual);
+    for (int l = D + 1; l < g.H; l++)
+        hipLaunchKernelGGL(k_ad_tree, dim3(8192), dim3(256), 0, s, g, l, d_grad_residual);
     // the shift pass reads the predictive nodes' gradients, which the
     // reference pass leaves untouched, and writes the block records it pulls from
     int4* brec = (int4*)(W + Bl.o_brec);

@@ -79,3 +79,45 @@ def test_gradient_buffer_alignment(torch):
     lf.check(lf.lib().lf_render_backward(field.handle, lf._ptr(res), lf._ptr(sh), lf._ptr(dc), 2, 30, 20, lf._ptr(dg),
                                          lf._ptr(g_res), lf._ptr(g_sh), lf._ptr(ws), need.value, lf._stream()))
     _compare(o, res, sh, cams, 30, 20, g, g_res, g_sh)
+
+
+def _cams(kind, views, na, nb, w, h, wo, ho):
+    """Separable cameras (diagonal homographies, some mirrored), projective
+    ones, or both in one batch."""
+    cams = lfscene.random_pinhole_cameras(views, na, nb, w, h, wo, ho, seed=wo)
+    for c in cams[::3]:  # mirrored: coordinates fall along the row
+        c[2], c[0] = c[2] + c[0] * wo, -c[0]
+        c[11], c[9] = c[11] + c[9] * wo, -c[9]
+    if kind != "separable":
+        warped = lfscene.projective_warp(cams, 3e-3, -2e-3)
+        cams = warped if kind == "projective" else np.where(np.arange(views)[:, None] % 2 == 0, cams, warped)
+    return np.ascontiguousarray(cams, dtype=np.float32)
+
+
+@pytest.mark.parametrize("kind", ["separable", "projective", "mixed"])
+@pytest.mark.parametrize("na,nb,levels,wo,ho,views", [(5, 3, 1, 33, 7, 3), (6, 7, 2, 64, 40, 4), (5, 5, 3, 9, 70, 3),
+                                                      (8, 8, 4, 40, 30, 2), (3, 4, 2, 2, 1, 5)])
+def test_gather_paths(torch, kind, na, nb, levels, wo, ho, views):
+    """Sample gradients from the axis tables, from sorted records and from
+    both, for every depth of the fused tree; frames of 2x1 pixels are too
+    small for the tables and always take the records."""
+    o, field = _field(na, nb, 48, 40, 8, levels)
+    rng, res, sh = _params(torch, field, levels, 0.25)
+    cams = _cams(kind, views, na, nb, 40, 48, wo, ho)
+    g = rng.normal(size=(views, 3, ho, wo)).astype(np.float32)
+    args = (res, sh, torch.from_numpy(cams).cuda(), wo, ho, torch.from_numpy(g).cuda())
+    got = field.render_backward(*args)
+    _compare(o, res, sh, cams, wo, ho, g, *got)
+    again = field.render_backward(*args)
+    assert all(torch.equal(x, y) for x, y in zip(got, again))
+
+
+def test_record_sort_large(torch):
+    """More records than one workgroup's round of the sort (projective views
+    of 256x256), magnified so that many records share a key."""
+    o, field = _field(4, 4, 32, 32, 8)
+    rng, res, sh = _params(torch, field, 5, 0.25)
+    cams = _cams("projective", 3, 4, 4, 32, 32, 256, 256)
+    g = rng.normal(size=(3, 3, 256, 256)).astype(np.float32)
+    got = field.render_backward(res, sh, torch.from_numpy(cams).cuda(), 256, 256, torch.from_numpy(g).cuda())
+    _compare(o, res, sh, cams, 256, 256, g, *got)
