@@ -42,9 +42,9 @@
 #define AD_TILE 16         // reference tile side of the pull kernel
 #define AD_FAR 48          // reach up to which positions outside the image are folded (three tiles)
 
-// n / d for 0 <= n <= 3072, 1 <= d <= 1024: the quotient of n + 1/2 is at
-// least 1 / (2 d) from an integer, the rounded reciprocal and product are off
-// by less than n 2^-22
+// n / d for 0 <= n < 2^20, d >= 1: (n + 1/2) / d is at least 1 / (2 d) from
+// an integer, and the rounded reciprocal and product are off by less than
+// (n / d) 2^-22
 __device__ __forceinline__ int lf_small_div(int n, int d)
 {
     return (int)(((float)n + 0.5f) * __builtin_amdgcn_rcpf((float)d));
@@ -55,6 +55,14 @@ __device__ __forceinline__ float ad_lerp(float p, float q, float f) { return fma
 // four (two) consecutive floats at any 4-byte aligned address, one load
 typedef float ad_f4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float ad_f2 __attribute__((ext_vector_type(2), aligned(4)));
+
+// element i of a uniform base, i * sizeof(T) below 2^32: one scalar base and
+// one 32-bit offset register per load
+template <class T, class E>
+__device__ __forceinline__ T ad_ld(const E* __restrict__ base, uint32_t i)
+{
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(E));
+}
 
 struct AdRay {
     int a0, a1, b0, b1, x0, x1, y0, y1;
@@ -73,22 +81,11 @@ __device__ __forceinline__ AdRay ad_ray(const LfGeom& g, const float* __restrict
     return r;
 }
 
-// record index of predictive node (B, A) of level l, channel c, block blk
-__device__ __forceinline__ int64_t ad_record(const LfGeom& g, int c, int l, int B, int A, int blk)
-{
-    return g.rec_base[c][l] + (int64_t)pred_ordinal(g.na_l[l], B, A) * g.nblk + blk;
-}
-
 // phase of record j of (channel c, level l): 2-bit codes, sixteen to a word
 __device__ __forceinline__ int ad_phase_at(const LfGeom& g, const LfPtrs& p, int c, int l, uint32_t j)
 {
     const uint32_t code = (p.mv[g.sig_word[c][l] + (j >> 4)] >> (2u * (j & 15u))) & 3u;
     return code == 0u ? 1 : (code == 1u ? -1 : 0);
-}
-
-__device__ __forceinline__ int ad_phase(const LfGeom& g, const LfPtrs& p, int c, int l, int B, int A, int blk)
-{
-    return ad_phase_at(g, p, c, l, (uint32_t)(pred_ordinal(g.na_l[l], B, A) * g.nblk + blk));
 }
 
 // ---------------------------------------------------------------------------
@@ -141,47 +138,46 @@ extern "C" lf_status lf_export_params(const lf_handle* h, float* d_residual, flo
 // relaxed forward
 // ---------------------------------------------------------------------------
 
-// bilinear sample of a real plane at (y + dy, x + dx), taps clamped
-__device__ __forceinline__ float ad_bilerp(const float* __restrict__ R, int w, int h, int y, int x, float2 d)
-{
-    const float fdx = floorf(d.x), fdy = floorf(d.y);
-    const float fx = d.x - fdx, fy = d.y - fdy;
-    const int x0 = x + (int)fdx, y0 = y + (int)fdy;
-    const int xa = lf_clampi(x0, 0, w - 1), xb = lf_clampi(x0 + 1, 0, w - 1);
-    const int ya = lf_clampi(y0, 0, h - 1), yb = lf_clampi(y0 + 1, 0, h - 1);
-    return ad_lerp(ad_lerp(R[ya * w + xa], R[ya * w + xb], fx), ad_lerp(R[yb * w + xa], R[yb * w + xb], fx), fy);
-}
-
 // Relaxed SRV values of node (B, A) of level l, channel c, at the pixels
 // (ys[k >> 1], xs[k & 1]): the residual plus the phase-signed bilinear
-// prediction; the block's phase and shift are read once per block.
-__device__ inline void ad_srv_quad(const LfGeom& g, const LfPtrs& p, const float* __restrict__ res,
-                                   const float2* __restrict__ shift, int c, int l, int B, int A, const int ys[2],
-                                   const int xs[2], float v[4])
+// prediction.  The four pixels' loads are issued together; the two taps of a
+// row come in one (columns q and q + 1, q at most w - 2; see ad_srv_nodes).
+__device__ __forceinline__ void ad_srv_quad(const LfGeom& g, const LfPtrs& p, const float* __restrict__ res,
+                                            const float2* __restrict__ shift, int c, int l, int B, int A, const int ys[2],
+                                            const int xs[2], float v[4])
 {
     const int64_t plane = (int64_t)g.w * g.h;
     const float* S = res + ((int64_t)c * g.n_nodes + g.node_base[l] + B * g.na_l[l] + A) * plane;
-    const bool pred = (A | B) & 1;
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = S[ys[k >> 1] * g.w + xs[k & 1]];
+    if (!((A | B) & 1)) return;
     const float* R = res + ((int64_t)c * g.n_nodes + g.node_base[l] + (B & ~1) * g.na_l[l] + (A & ~1)) * plane;
-    int blk0 = -1, sg = 0;
-    float2 d = make_float2(0.0f, 0.0f);
-#pragma unroll 1
+    const uint32_t j0 = (uint32_t)pred_ordinal(g.na_l[l], B, A) * (uint32_t)g.nblk;
+    const float2* sh = shift + g.rec_base[c][l] + j0;
+    int sg[4];
+    float2 d[4];
+    ad_f2 ta[4], tb[4];
+#pragma unroll
     for (int k = 0; k < 4; k++) {
-        const int y = ys[k >> 1], x = xs[k & 1];
-        float sv = S[y * g.w + x];
-        if (pred) {
-            const int blk = (y / g.bs) * g.nbx + x / g.bs;
-            if (blk != blk0) {
-                sg = ad_phase(g, p, c, l, B, A, blk);
-                if (sg) d = shift[ad_record(g, c, l, B, A, blk)];
-                blk0 = blk;
-            }
-            if (sg) {
-                const float q = ad_bilerp(R, g.w, g.h, y, x, d);
-                sv += sg > 0 ? q : -q;
-            }
-        }
-        v[k] = sv;
+        const int blk = (ys[k >> 1] >> g.bsl) * g.nbx + (xs[k & 1] >> g.bsl);
+        sg[k] = ad_phase_at(g, p, c, l, j0 + (uint32_t)blk);
+        d[k] = sh[blk];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const int x0 = xs[k & 1] + (int)floorf(d[k].x), y0 = ys[k >> 1] + (int)floorf(d[k].y);
+        const int q = max(min(lf_clampi(x0, 0, g.w - 1), g.w - 2), 0);
+        ta[k] = *reinterpret_cast<const ad_f2*>(R + lf_clampi(y0, 0, g.h - 1) * g.w + q);
+        tb[k] = *reinterpret_cast<const ad_f2*>(R + lf_clampi(y0 + 1, 0, g.h - 1) * g.w + q);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const float fdx = floorf(d[k].x), fx = d[k].x - fdx, fy = d[k].y - floorf(d[k].y);
+        const int x0 = xs[k & 1] + (int)fdx;
+        const int xa = lf_clampi(x0, 0, g.w - 1), xb = lf_clampi(x0 + 1, 0, g.w - 1), q = max(min(xa, g.w - 2), 0);
+        const float t = ad_lerp(ad_lerp(xa > q ? ta[k].y : ta[k].x, xb > q ? ta[k].y : ta[k].x, fx),
+                                ad_lerp(xa > q ? tb[k].y : tb[k].x, xb > q ? tb[k].y : tb[k].x, fx), fy);
+        if (sg[k]) v[k] += sg[k] > 0 ? t : -t;
     }
 }
 
@@ -220,39 +216,290 @@ __device__ __forceinline__ void ad_ray_channel(const LfGeom& g, const LfPtrs& p,
     }
 }
 
-__global__ void __launch_bounds__(256) k_render_relaxed(LfGeom g, LfPtrs p, const float* __restrict__ res,
-                                                        const float2* __restrict__ shift,
-                                                        const float* __restrict__ cams, int nv, int wo, int ho,
-                                                        float* __restrict__ out)
+// Relaxed SRVs of N nodes of level l at one pixel (block blk), all three
+// channels: the residual plus the phase-signed bilinear prediction.  Level
+// and nodes are uniform across the wave.  All residual, phase and shift loads
+// are issued first, then all taps, so that a level costs two round trips to
+// memory.  The two taps of a row come in one load: columns q and q + 1 with q
+// at most w - 2 (a plane one column wide reads one element of the next plane;
+// a reference with predictive siblings is never the buffer's last).
+template <int N>
+__device__ __forceinline__ void ad_srv_nodes(const LfGeom& g, const LfPtrs& p, const float* __restrict__ res,
+                                             const float2* __restrict__ shift, int l, const int (&B)[N], const int (&A)[N],
+                                             int y, int x, int blk, float (&o)[N][3])
 {
-    const int64_t npix = (int64_t)wo * ho;
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= npix * nv) return;
-    const int v = (int)(r / npix);
-    const int64_t px = r - (int64_t)v * npix;
-    const int j = (int)(px / wo), i = (int)(px % wo);
-    const AdRay ry = ad_ray(g, cams + 18 * v, i, j);
-    float Ys[16], Cos[16], Cgs[16];
-    ad_ray_channel(g, p, res, shift, ry, 0, Ys);
-    ad_ray_channel(g, p, res, shift, ry, 1, Cos);
-    ad_ray_channel(g, p, res, shift, ry, 2, Cgs);
-    float sm[16][3];
+    const int64_t plane = (int64_t)g.w * g.h;
+    const float* level = res + (int64_t)g.node_base[l] * plane;
+    uint32_t code[N][3];
+    float2 d[N][3];
+    ad_f2 ta[N][3], tb[N][3];
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const float Y = Ys[k], Co = Cos[k], Cg = Cgs[k];
-        sm[k][0] = Y + 0.5f * Co - 0.5f * Cg;
-        sm[k][1] = Y + 0.5f * Cg;
-        sm[k][2] = Y - 0.5f * Co - 0.5f * Cg;
+    for (int n = 0; n < N; n++) {
+        const bool pred = (A[n] | B[n]) & 1;
+        const uint32_t j0 = (uint32_t)pred_ordinal(g.na_l[l], B[n], A[n]) * (uint32_t)g.nblk;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            o[n][c] = ad_ld<float>(level + ((int64_t)c * g.n_nodes + B[n] * g.na_l[l] + A[n]) * plane, (uint32_t)(y * g.w + x));
+            if (pred) {
+                const uint32_t j = j0 + (uint32_t)blk;
+                code[n][c] = (ad_ld<uint32_t>(p.mv + g.sig_word[c][l], j >> 4) >> (2u * (j & 15u))) & 3u;
+                d[n][c] = ad_ld<float2>(shift + g.rec_base[c][l] + j0, (uint32_t)blk);
+            }
+        }
     }
 #pragma unroll
-    for (int c = 0; c < 3; c++) {
-        float vw[4];
+    for (int n = 0; n < N; n++)
+        if ((A[n] | B[n]) & 1)
 #pragma unroll
-        for (int q = 0; q < 4; q++)
-            vw[q] = ad_lerp(ad_lerp(sm[4 * q][c], sm[4 * q + 1][c], ry.fs), ad_lerp(sm[4 * q + 2][c], sm[4 * q + 3][c], ry.fs),
-                            ry.ft);
-        out[((int64_t)v * 3 + c) * npix + px] =
-            ad_lerp(ad_lerp(vw[0], vw[1], ry.fu), ad_lerp(vw[2], vw[3], ry.fu), ry.fv) * (1.0f / 255.0f);
+            for (int c = 0; c < 3; c++) {
+                const float* R = level + ((int64_t)c * g.n_nodes + (B[n] & ~1) * g.na_l[l] + (A[n] & ~1)) * plane;
+                const int x0 = x + (int)floorf(d[n][c].x), y0 = y + (int)floorf(d[n][c].y);
+                const int q = max(min(lf_clampi(x0, 0, g.w - 1), g.w - 2), 0);
+                ta[n][c] = ad_ld<ad_f2>(R, (uint32_t)(lf_clampi(y0, 0, g.h - 1) * g.w + q));
+                tb[n][c] = ad_ld<ad_f2>(R, (uint32_t)(lf_clampi(y0 + 1, 0, g.h - 1) * g.w + q));
+            }
+#pragma unroll
+    for (int n = 0; n < N; n++)
+        if ((A[n] | B[n]) & 1)
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                const float fdx = floorf(d[n][c].x), fx = d[n][c].x - fdx, fy = d[n][c].y - floorf(d[n][c].y);
+                const int x0 = x + (int)fdx;
+                const int xa = lf_clampi(x0, 0, g.w - 1), xb = lf_clampi(x0 + 1, 0, g.w - 1), q = max(min(xa, g.w - 2), 0);
+                const float v = ad_lerp(ad_lerp(xa > q ? ta[n][c].y : ta[n][c].x, xb > q ? ta[n][c].y : ta[n][c].x, fx),
+                                        ad_lerp(xa > q ? tb[n][c].y : tb[n][c].x, xb > q ? tb[n][c].y : tb[n][c].x, fx), fy);
+                if (code[n][c] < 2u) o[n][c] += code[n][c] == 0u ? v : -v;  // code 2, 3: no prediction
+            }
+}
+
+// Colour of one sample; the (s, t) blend of a view's four samples (row
+// major); the (u, v) blend of the four views, scaled and stored.
+__device__ __forceinline__ void ad_rgb(float Y, float Co, float Cg, float (&o)[3])
+{
+    o[0] = Y + 0.5f * Co - 0.5f * Cg;
+    o[1] = Y + 0.5f * Cg;
+    o[2] = Y - 0.5f * Co - 0.5f * Cg;
+}
+
+__device__ __forceinline__ void ad_blend_view(const float (&sm)[4][3], const AdRay& ry, float (&vw)[3])
+{
+#pragma unroll
+    for (int c = 0; c < 3; c++) vw[c] = ad_lerp(ad_lerp(sm[0][c], sm[1][c], ry.fs), ad_lerp(sm[2][c], sm[3][c], ry.fs), ry.ft);
+}
+
+__device__ __forceinline__ void ad_blend_store(const float (&vw)[4][3], const AdRay& ry, float* __restrict__ out, int64_t npix,
+                                               int64_t px)
+{
+#pragma unroll
+    for (int c = 0; c < 3; c++)
+        out[c * npix + px] =
+            ad_lerp(ad_lerp(vw[0][c], vw[1][c], ry.fu), ad_lerp(vw[2][c], vw[3][c], ry.fu), ry.fv) * (1.0f / 255.0f);
+}
+
+#define AD_RT 32             // screen tile of the relaxed render: AD_RT x 8 pixels, an 8x8 part per wave64
+#define AD_STAGE 10176       // floats of LDS per workgroup: 40 KB with the boxes, four workgroups per CU
+#define AD_MARK 0x7FC0DEADu  // NaN payload at a part's first pixel: left to the per-ray pass
+
+typedef unsigned short ad_u16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t ad_pk_min(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ad_u16x2, a), __builtin_bit_cast(ad_u16x2, b)));
+}
+__device__ __forceinline__ uint32_t ad_pk_max(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ad_u16x2, a), __builtin_bit_cast(ad_u16x2, b)));
+}
+
+// Relaxed render of 32x8 screen tiles: the samples that a tile's rays read
+// (every pixel of their bounding box, in every light-field view of theirs)
+// are reconstructed once into LDS, one plane per channel and light-field
+// view, and the rays blend from there.  Reconstructing them ray by ray
+// evaluates three times as many samples at unit magnification.  A wave takes
+// 64 box pixels at a time, in 2x2 light-field views, so that everything about
+// a tree node is scalar and views sharing a node share its value; the three
+// channels of up to four nodes are in flight together, because the chain of
+// dependent loads (shift, then taps, per level) is what bounds a tile.
+// A tile whose box exceeds the LDS (the rays' footprints spread over more than
+// about 1.6 light-field pixels per ray) is marked for k_relaxed_rest, where
+// each sample is read by about one ray.  The sums, and their order, are those
+// of the per-ray pass.  16 views of 512x512 over 17x17x512x512: 2.19 -> 0.74
+// ms, three views of 250x187 over 9x9x256x256: 0.146 -> 0.058 ms (all rays
+// one by one before).  30 KB of LDS, five workgroups per CU: 0.72 and 0.059
+// ms for this kernel, but tiles whose rays span 3x3 views then go to the
+// per-ray pass: 0.90 and 0.097 ms in all.
+__global__ void __launch_bounds__(256, 4) k_render_relaxed(LfGeom g, LfPtrs p, const float* __restrict__ res,
+                                                           const float2* __restrict__ shift,
+                                                           const float* __restrict__ cams, int wo, int ho, int tiles_x,
+                                                           int tiles_y, int64_t n_tiles, float* __restrict__ out)
+{
+    __shared__ float stage[AD_STAGE];
+    __shared__ uint32_t boxes[4][4];
+    const int64_t npix = (int64_t)wo * ho;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int per = tiles_x * tiles_y, H = g.H;
+    // XCD-aware order: each XCD takes a contiguous range of tiles (one tile a
+    // workgroup, except in launches of more than 2^20 tiles)
+    const int64_t per_xcd = (n_tiles + 7) / 8;
+    for (int64_t k8 = blockIdx.x >> 3; k8 < per_xcd; k8 += gridDim.x >> 3) {
+        const int64_t T = (int64_t)(blockIdx.x & 7) * per_xcd + k8;
+        if (T >= n_tiles) return;
+        const int v = (int)(T / per), tt = (int)(T - (int64_t)v * per);
+        const int tyi = tt / tiles_x, txi = tt - tyi * tiles_x;
+        const int i = txi * AD_RT + wv * 8 + (lane & 7), j = tyi * 8 + (lane >> 3);
+        const AdRay ry = ad_ray(g, cams + 18 * (int64_t)v, min(i, wo - 1), min(j, ho - 1));  // dead lanes repeat the last pixel
+        uint32_t m[4] = {(uint32_t)ry.a0 | ((uint32_t)ry.b0 << 16), (uint32_t)ry.a1 | ((uint32_t)ry.b1 << 16),
+                         (uint32_t)ry.x0 | ((uint32_t)ry.y0 << 16), (uint32_t)ry.x1 | ((uint32_t)ry.y1 << 16)};
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1)
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const uint32_t t = (uint32_t)__shfl_xor((int)m[k], s, 64);
+                m[k] = (k & 1) ? ad_pk_max(m[k], t) : ad_pk_min(m[k], t);
+            }
+        if (lane == 0)
+#pragma unroll
+            for (int k = 0; k < 4; k++) boxes[wv][k] = m[k];
+        __syncthreads();
+        uint32_t box[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            uint32_t t = boxes[0][k];
+            for (int w = 1; w < 4; w++) t = (k & 1) ? ad_pk_max(t, boxes[w][k]) : ad_pk_min(t, boxes[w][k]);
+            box[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+        }
+        const int amin = (int)(box[0] & 0xFFFFu), bmin = (int)(box[0] >> 16), amax = (int)(box[1] & 0xFFFFu),
+                  bmax = (int)(box[1] >> 16);
+        const int xmin = (int)(box[2] & 0xFFFFu), ymin = (int)(box[2] >> 16), nx = (int)(box[3] & 0xFFFFu) - xmin + 1,
+                  ny = (int)(box[3] >> 16) - ymin + 1;
+        const int nA = amax - amin + 1, nB = bmax - bmin + 1, nbox = nx * ny;
+        float* o = out + (int64_t)v * 3 * npix;
+        if (3 * (int64_t)nbox * nA * nB > AD_STAGE) {  // uniform
+            if (lane == 0 && i < wo) o[(int64_t)j * wo + i] = __uint_as_float(AD_MARK);
+            __syncthreads();  // the next tile rewrites the boxes
+            continue;
+        }
+        const int cs = nA * nB * nbox;  // channel stride in LDS
+        for (int e0 = wv * 64; e0 < nbox; e0 += 256) {
+            const int e = min(e0 + lane, nbox - 1);  // past the end: the last pixel again (same value)
+            const int yy = lf_small_div(e, nx);
+            const int y = ymin + yy, x = xmin + e - yy * nx;
+            const int blk = (y >> g.bsl) * g.nbx + (x >> g.bsl);
+            for (int b = bmin; b <= bmax; b += 2)
+                for (int a = amin; a <= amax; a += 2) {
+                    const int b1 = min(b + 1, bmax), a1 = min(a + 1, amax);
+                    float acc[4][3];
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        const int bb = (q & 2) ? b1 : b, aa = (q & 1) ? a1 : a;
+#pragma unroll
+                        for (int c = 0; c < 3; c++)
+                            acc[q][c] = (float)ad_ld<int16_t>(
+                                p.root + ((size_t)(c * g.root_nb + (bb >> H)) * g.root_na + (aa >> H)) * ((size_t)g.w * g.h),
+                                (uint32_t)(y * g.w + x));
+                    }
+                    for (int l = 0; l < H; l++) {
+                        const int B0 = b >> l, B1 = b1 >> l, A0 = a >> l, A1 = a1 >> l;
+                        if (B0 == B1 && A0 == A1) {  // uniform: views of the 2x2 that share the node share its value
+                            float s[1][3];
+                            ad_srv_nodes<1>(g, p, res, shift, l, {B0}, {A0}, y, x, blk, s);
+#pragma unroll
+                            for (int q = 0; q < 4; q++)
+#pragma unroll
+                                for (int c = 0; c < 3; c++) acc[q][c] += s[0][c];
+                        } else if (B0 == B1 || A0 == A1) {
+                            float s[2][3];
+                            ad_srv_nodes<2>(g, p, res, shift, l, {B0, B1}, {A0, A1}, y, x, blk, s);
+#pragma unroll
+                            for (int q = 0; q < 4; q++)
+#pragma unroll
+                                for (int c = 0; c < 3; c++) {
+                                    const bool second = B0 == B1 ? (q & 1) : (q & 2);
+                                    acc[q][c] += second ? s[1][c] : s[0][c];
+                                }
+                        } else {
+#pragma unroll
+                            for (int h = 0; h < 2; h++) {
+                                float s[2][3];
+                                ad_srv_nodes<2>(g, p, res, shift, l, {h ? B1 : B0, h ? B1 : B0}, {A0, A1}, y, x, blk, s);
+#pragma unroll
+                                for (int q = 0; q < 2; q++)
+#pragma unroll
+                                    for (int c = 0; c < 3; c++) acc[2 * h + q][c] += s[q][c];
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        const int bb = b + (q >> 1), aa = a + (q & 1);
+                        if (bb <= bmax && aa <= amax)
+#pragma unroll
+                            for (int c = 0; c < 3; c++) stage[c * cs + ((bb - bmin) * nA + aa - amin) * nbox + e] = acc[q][c];
+                    }
+                }
+        }
+        __syncthreads();
+        if (i < wo && j < ho) {
+            float vw[4][3];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const int b = (q & 2) ? ry.b1 : ry.b0, a = (q & 1) ? ry.a1 : ry.a0;
+                const float* view = stage + ((b - bmin) * nA + a - amin) * nbox;
+                float sm[4][3];
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const int y = (k & 2) ? ry.y1 : ry.y0, x = (k & 1) ? ry.x1 : ry.x0;
+                    const float* s = view + (y - ymin) * nx + x - xmin;
+                    ad_rgb(s[0], s[cs], s[2 * cs], sm[k]);
+                }
+                ad_blend_view(sm, ry, vw[q]);
+                __builtin_amdgcn_sched_barrier(0);  // one view's samples in registers at a time
+            }
+            ad_blend_store(vw, ry, o, npix, (int64_t)j * wo + i);
+        }
+        __syncthreads();  // the next tile rewrites the boxes and the stage
+    }
+}
+
+// Ray-by-ray render of the 8x8 parts that k_render_relaxed marked: a wave
+// looks at `each` parts and renders the marked ones.  60 views of 64x64 over
+// 17x17x512x512, every part marked: 0.22 ms (0.33 with the four pixels of a
+// node read one after the other).
+__global__ void __launch_bounds__(256) k_relaxed_rest(LfGeom g, LfPtrs p, const float* __restrict__ res,
+                                                      const float2* __restrict__ shift, const float* __restrict__ cams,
+                                                      int wo, int ho, int parts_x, int parts_y, int64_t n_parts, int each,
+                                                      float* __restrict__ out)
+{
+    const int64_t npix = (int64_t)wo * ho;
+    const int lane = threadIdx.x & 63;
+    const int per = parts_x * parts_y;
+    for (int64_t p0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * each; p0 < n_parts; p0 += (int64_t)gridDim.x * 4 * each) {
+        bool mine = false;
+        if (lane < each && p0 + lane < n_parts) {
+            const int v = (int)((p0 + lane) / per), t = (int)((p0 + lane) - (int64_t)v * per);
+            const int py = t / parts_x, px = t - py * parts_x;
+            mine = __float_as_uint(out[(int64_t)v * 3 * npix + (int64_t)(py * 8) * wo + px * 8]) == AD_MARK;
+        }
+        for (uint64_t m = __ballot(mine); m; m &= m - 1) {
+            const int64_t pt = p0 + __builtin_ctzll(m);
+            const int v = (int)(pt / per), t = (int)(pt - (int64_t)v * per);
+            const int py = t / parts_x, i = (t - py * parts_x) * 8 + (lane & 7), j = py * 8 + (lane >> 3);
+            if (i >= wo || j >= ho) continue;
+            const AdRay ry = ad_ray(g, cams + 18 * (int64_t)v, i, j);
+            float Ys[16], Cos[16], Cgs[16];
+            ad_ray_channel(g, p, res, shift, ry, 0, Ys);
+            ad_ray_channel(g, p, res, shift, ry, 1, Cos);
+            ad_ray_channel(g, p, res, shift, ry, 2, Cgs);
+            float vw[4][3];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                float sm[4][3];
+#pragma unroll
+                for (int k = 0; k < 4; k++) ad_rgb(Ys[4 * q + k], Cos[4 * q + k], Cgs[4 * q + k], sm[k]);
+                ad_blend_view(sm, ry, vw[q]);
+            }
+            ad_blend_store(vw, ry, out + (int64_t)v * 3 * npix, npix, (int64_t)j * wo + i);
+        }
     }
 }
 
@@ -266,8 +513,17 @@ extern "C" lf_status lf_render_relaxed(const lf_handle* h, const float* d_residu
     if (!d_cams || !d_out) return lf_fail(LF_EINVAL, "null buffer");
     const int64_t total = (int64_t)n_views * width * height;
     if ((total + 255) / 256 > 0x7FFFFFFF) return lf_fail(LF_EINVAL, "too many rays");
-    hipLaunchKernelGGL(k_render_relaxed, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
-                       h->L.g, h->p, d_residual, (const float2*)d_shift, d_cams, n_views, width, height, d_out);
+    const int tx = (width + AD_RT - 1) / AD_RT, ty = (height + 7) / 8, px = (width + 7) / 8;
+    const int64_t n_tiles = (int64_t)n_views * tx * ty, n_parts = (int64_t)n_views * px * ty;
+    hipStream_t s = (hipStream_t)stream;
+    hipLaunchKernelGGL(k_render_relaxed, dim3((unsigned)std::min<int64_t>((n_tiles + 7) / 8 * 8, 1 << 20)), dim3(256), 0, s, h->L.g, h->p,
+                       d_residual, (const float2*)d_shift, d_cams, width, height, tx, ty, n_tiles, d_out);
+    // marked parts: one per wave while that fills the chip, then up to eight
+    // (mostly unmarked) per wave
+    const int each = (int)std::min<int64_t>(std::max<int64_t>(n_parts / 8192, 1), 8);
+    const int64_t wgs = (n_parts + 4 * each - 1) / (4 * each);
+    hipLaunchKernelGGL(k_relaxed_rest, dim3((unsigned)std::min<int64_t>(wgs, 1 << 20)), dim3(256), 0, s, h->L.g, h->p,
+                       d_residual, (const float2*)d_shift, d_cams, width, height, px, ty, n_parts, each, d_out);
     return lf_check_launch("render_relaxed");
 }
 
@@ -414,13 +670,11 @@ __device__ __forceinline__ int2 ad_interval(const float* __restrict__ h, int whi
     return make_int2(edge[0], edge[1]);
 }
 
-// One thread per table entry of one view: columns, rows, then the intervals.
-// The interval search costs 2 log2(len) coordinate evaluations.
-__global__ void k_ad_axes(LfGeom g, const float* __restrict__ cams, int nv, int wo, int ho, AdAxes t)
+// Entry id of the tables (per entries a view): columns, rows, then the
+// intervals.  The interval search costs 2 log2(len) coordinate evaluations.
+__device__ __forceinline__ void ad_axes_entry(const LfGeom& g, const float* __restrict__ cams, int wo, int ho, const AdAxes& t,
+                                              int64_t per, int64_t id)
 {
-    const int64_t per = (int64_t)wo + ho + g.w + g.h + g.na + g.nb;
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= per * nv) return;
     const int64_t v = id / per;
     int e = (int)(id - v * per);
     const float* cam = cams + 18 * v;
@@ -457,6 +711,13 @@ __global__ void k_ad_axes(LfGeom g, const float* __restrict__ cams, int nv, int 
         t.ra[v * g.na + e] = ad_interval(cam, 0, wo, g.na, e);
     else
         t.rb[v * g.nb + e - g.na] = ad_interval(cam, 1, ho, g.nb, e - g.na);
+}
+
+__global__ void k_ad_axes(LfGeom g, const float* __restrict__ cams, int nv, int wo, int ho, AdAxes t)
+{
+    const int64_t per = (int64_t)wo + ho + g.w + g.h + g.na + g.nb;
+    for (int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; id < per * nv; id += (int64_t)gridDim.x * blockDim.x)
+        ad_axes_entry(g, cams, wo, ho, t, per, id);
 }
 
 // Separating views that reach each light-field view, in view order: one
@@ -722,16 +983,14 @@ __device__ __forceinline__ void ad_sample(const LfGeom& g, const AdGather& G, in
 // views (records for every ray, a library radix sort, one thread per sample
 // and a pass per tree level: 2.05 ms).
 template <int D>
-__global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int pix_wgs, float* __restrict__ gres)
+__global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int clusters, float* __restrict__ gres)
 {
-    const int cl = (int)blockIdx.x / pix_wgs;
-    const int px = ((int)blockIdx.x - cl * pix_wgs) * 256 + (int)threadIdx.x;
+    const int px = (int)(blockIdx.x * 256 + threadIdx.x);
     const int plane = g.w * g.h;
     if (px >= plane) return;
     const int y = px / g.w, x = px - y * g.w;
     const bool general = G.all_general || *G.t.general;
     const int nac = (g.na + (1 << D) - 1) >> D;
-    const int B = cl / nac, A = cl - B * nac;  // cluster
     const int64_t cstride = (int64_t)g.n_nodes * plane;
     auto put = [&](int l, int Bl, int Al, const float (&v)[3]) {
         float* o = gres + (int64_t)(g.node_base[l] + Bl * g.na_l[l] + Al) * plane + px;
@@ -748,31 +1007,34 @@ __global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int pix
         o[2] = 0.5f * (acc[1] - acc[0] - acc[2]);
         put(0, b, a, o);
     };
-    if (D == 0) {
-        float o[3];
-        leaf(B, A, o);
-        return;
-    }
-    float top[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-    for (int q2 = 0; q2 < (D == 2 ? 4 : 1); q2++) {
-        const int B1 = D == 2 ? 2 * B + (q2 >> 1) : B, A1 = D == 2 ? 2 * A + (q2 & 1) : A;
-        if (B1 >= g.nb_l[1] || A1 >= g.na_l[1]) continue;
-        float mid[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-        for (int q1 = 0; q1 < 4; q1++) {
-            const int b = 2 * B1 + (q1 >> 1), a = 2 * A1 + (q1 & 1);
-            if (b >= g.nb || a >= g.na) continue;
+    for (int cl = blockIdx.y; cl < clusters; cl += gridDim.y) {
+        const int B = cl / nac, A = cl - B * nac;
+        if (D == 0) {
             float o[3];
-            leaf(b, a, o);
-#pragma unroll
-            for (int c = 0; c < 3; c++) mid[c] += o[c];
+            leaf(B, A, o);
+            continue;
         }
-        put(1, B1, A1, mid);
+        float top[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+        for (int q2 = 0; q2 < (D == 2 ? 4 : 1); q2++) {
+            const int B1 = D == 2 ? 2 * B + (q2 >> 1) : B, A1 = D == 2 ? 2 * A + (q2 & 1) : A;
+            if (B1 >= g.nb_l[1] || A1 >= g.na_l[1]) continue;
+            float mid[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+            for (int q1 = 0; q1 < 4; q1++) {
+                const int b = 2 * B1 + (q1 >> 1), a = 2 * A1 + (q1 & 1);
+                if (b >= g.nb || a >= g.na) continue;
+                float o[3];
+                leaf(b, a, o);
 #pragma unroll
-        for (int c = 0; c < 3; c++) top[c] += mid[c];
+                for (int c = 0; c < 3; c++) mid[c] += o[c];
+            }
+            put(1, B1, A1, mid);
+#pragma unroll
+            for (int c = 0; c < 3; c++) top[c] += mid[c];
+        }
+        if (D == 2) put(2, B, A, top);
     }
-    if (D == 2) put(2, B, A, top);
 }
 
 // node gradients of a level the gather pass does not reach: the sum of its
@@ -1083,7 +1345,7 @@ __global__ void __launch_bounds__(256) k_ad_reference(LfGeom g, const int4* __re
                 // one candidate block per lane, (sibling, row, column) order
                 const int e = k0 + lane;
                 const int sib = e >= 2 * nk ? 3 : (e >= nk ? 2 : 1), es = e - (sib - 1) * nk;
-                const int ey = nk <= 1024 ? lf_small_div(es, nkx) : es / nkx;  // uniform choice
+                const int ey = nk < (1 << 18) ? lf_small_div(es, nkx) : es / nkx;  // uniform choice
                 const int kx = ckx0 + es - ey * nkx, ky = cky0 + ey;
                 int4 v = make_int4(0, 0, 0, 0);
                 if (e < 3 * nk && (sib == 1 ? h1 : (sib == 2 ? h2 : h3)))
@@ -1182,119 +1444,122 @@ struct AdPred {
 // load; 0.99 with five single loads per row of four).
 #define AD_SHIFT_U 4
 template <int LG, bool QUADS>
-__global__ void __launch_bounds__(256) k_ad_shift(LfGeom g, LfPtrs p, AdPred pn, int groups,
+__global__ void __launch_bounds__(256) k_ad_shift(LfGeom g, LfPtrs p, AdPred pn, int groups, int n_wg,
                                                   const float* __restrict__ res, const float2* __restrict__ shift,
                                                   const float* __restrict__ gres_pred, float2* __restrict__ gshift,
                                                   int4* __restrict__ brec)
 {
     constexpr int G = 1 << LG, U = LG == 6 ? AD_SHIFT_U : 1, PER = U * (256 / G);
-    // the node, scalar
-    const int cn = (int)blockIdx.x / groups;
-    const int c = cn / pn.total, np = cn - c * pn.total;
-    int l = g.H - 1;
-    while (l > 0 && np >= pn.first[l - 1]) l--;
-    const int pord = np - pn.first[l], na = g.na_l[l], pair = na + na / 2;
-    int B = 2 * (pord / pair), A;
-    const int rem = pord % pair;
-    if (rem < na / 2) {  // even rows hold the odd columns, odd rows every column
-        A = 2 * rem + 1;
-    } else {
-        B += 1;
-        A = rem - na / 2;
-    }
-    const int64_t plane = (int64_t)g.w * g.h;
-    const float* R = res + ((int64_t)c * g.n_nodes + g.node_base[l] + (B & ~1) * na + (A & ~1)) * plane;
-    const float* gp = gres_pred + ((int64_t)c * g.n_nodes + g.node_base[l] + B * na + A) * plane;
-    const int64_t rec0 = g.rec_base[c][l] + (int64_t)pord * g.nblk;
-    const uint32_t* code = p.mv + g.sig_word[c][l];
-    const uint32_t j0 = (uint32_t)pord * (uint32_t)g.nblk;
+    // one group of blocks a workgroup, except in launches of more than 2^22
+    for (int wg = (int)blockIdx.x; wg < n_wg; wg += (int)gridDim.x) {
+        // the node, scalar
+        const int cn = wg / groups;
+        const int c = cn / pn.total, np = cn - c * pn.total;
+        int l = g.H - 1;
+        while (l > 0 && np >= pn.first[l - 1]) l--;
+        const int pord = np - pn.first[l], na = g.na_l[l], pair = na + na / 2;
+        int B = 2 * (pord / pair), A;
+        const int rem = pord % pair;
+        if (rem < na / 2) {  // even rows hold the odd columns, odd rows every column
+            A = 2 * rem + 1;
+        } else {
+            B += 1;
+            A = rem - na / 2;
+        }
+        const int64_t plane = (int64_t)g.w * g.h;
+        const float* R = res + ((int64_t)c * g.n_nodes + g.node_base[l] + (B & ~1) * na + (A & ~1)) * plane;
+        const float* gp = gres_pred + ((int64_t)c * g.n_nodes + g.node_base[l] + B * na + A) * plane;
+        const int64_t rec0 = g.rec_base[c][l] + (int64_t)pord * g.nblk;
+        const uint32_t* code = p.mv + g.sig_word[c][l];
+        const uint32_t j0 = (uint32_t)pord * (uint32_t)g.nblk;
 
-    const int lane = threadIdx.x & (G - 1);
-    const int sub = LG == 6 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> LG);
-    const int blk0 = ((int)blockIdx.x - cn * groups) * PER + sub * U;
-    constexpr int N = QUADS ? 4 : 1;           // pixels per item
-    const int rowl = g.bsl - (QUADS ? 2 : 0);  // log2 items per block row
-    const int items = 1 << (g.bsl + rowl);
-    AdRec d[U];
-    float sx[U], sy[U];
-    bool some[U];
+        const int lane = threadIdx.x & (G - 1);
+        const int sub = LG == 6 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> LG);
+        const int blk0 = (wg - cn * groups) * PER + sub * U;
+        constexpr int N = QUADS ? 4 : 1;           // pixels per item
+        const int rowl = g.bsl - (QUADS ? 2 : 0);  // log2 items per block row
+        const int items = 1 << (g.bsl + rowl);
+        AdRec d[U];
+        float sx[U], sy[U];
+        bool some[U];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-        const int blk = min(blk0 + u, g.nblk - 1);  // past the end: the last block again, not stored
-        const uint32_t j = j0 + (uint32_t)blk, cw = (code[j >> 4] >> (2u * (j & 15u))) & 3u;
-        d[u] = ad_split(g, cw == 0u ? 1 : (cw == 1u ? -1 : 0), shift[rec0 + blk]);
-        sx[u] = sy[u] = 0.0f;
-        some[u] = false;
-    }
+        for (int u = 0; u < U; u++) {
+            const int blk = min(blk0 + u, g.nblk - 1);  // past the end: the last block again, not stored
+            const uint32_t j = j0 + (uint32_t)blk, cw = (code[j >> 4] >> (2u * (j & 15u))) & 3u;
+            d[u] = ad_split(g, cw == 0u ? 1 : (cw == 1u ? -1 : 0), shift[rec0 + blk]);
+            sx[u] = sy[u] = 0.0f;
+            some[u] = false;
+        }
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-        const int blk = min(blk0 + u, g.nblk - 1);
-        const int ky = blk / g.nbx;
-        const int by0 = ky << g.bsl, bx0 = (blk - ky * g.nbx) << g.bsl;
-        const float fx = d[u].fx, fy = d[u].fy, gx = 1.0f - fx, gy = 1.0f - fy, sg = (float)d[u].sg;
-        if (d[u].sg)
-            for (int q = lane; q < items; q += G) {
-                const int y = by0 + (q >> rowl), x = bx0 + (q & ((1 << rowl) - 1)) * N;
-                float gv[N];
-                if (QUADS) {
-                    const float4 t = *reinterpret_cast<const float4*>(gp + y * g.w + x);
-                    gv[0] = t.x;
-                    gv[N > 1 ? 1 : 0] = t.y;
-                    gv[N > 2 ? 2 : 0] = t.z;
-                    gv[N > 3 ? 3 : 0] = t.w;
-                } else {
-                    gv[0] = gp[y * g.w + x];
-                }
-                const int ra = lf_clampi(y + d[u].iy, 0, g.h - 1) * g.w, rb = lf_clampi(y + d[u].iy + 1, 0, g.h - 1) * g.w;
-                float ta[N + 1], tb[N + 1];
-                const int xt = x + d[u].ix;
-                if (QUADS && xt >= 0 && xt + 4 < g.w) {
-                    const ad_f4 a = *reinterpret_cast<const ad_f4*>(R + ra + xt), b = *reinterpret_cast<const ad_f4*>(R + rb + xt);
-                    ta[N] = R[ra + xt + N];
-                    tb[N] = R[rb + xt + N];
+        for (int u = 0; u < U; u++) {
+            const int blk = min(blk0 + u, g.nblk - 1);
+            const int ky = blk / g.nbx;
+            const int by0 = ky << g.bsl, bx0 = (blk - ky * g.nbx) << g.bsl;
+            const float fx = d[u].fx, fy = d[u].fy, gx = 1.0f - fx, gy = 1.0f - fy, sg = (float)d[u].sg;
+            if (d[u].sg)
+                for (int q = lane; q < items; q += G) {
+                    const int y = by0 + (q >> rowl), x = bx0 + (q & ((1 << rowl) - 1)) * N;
+                    float gv[N];
+                    if (QUADS) {
+                        const float4 t = *reinterpret_cast<const float4*>(gp + y * g.w + x);
+                        gv[0] = t.x;
+                        gv[N > 1 ? 1 : 0] = t.y;
+                        gv[N > 2 ? 2 : 0] = t.z;
+                        gv[N > 3 ? 3 : 0] = t.w;
+                    } else {
+                        gv[0] = gp[y * g.w + x];
+                    }
+                    const int ra = lf_clampi(y + d[u].iy, 0, g.h - 1) * g.w, rb = lf_clampi(y + d[u].iy + 1, 0, g.h - 1) * g.w;
+                    float ta[N + 1], tb[N + 1];
+                    const int xt = x + d[u].ix;
+                    if (QUADS && xt >= 0 && xt + 4 < g.w) {
+                        const ad_f4 a = *reinterpret_cast<const ad_f4*>(R + ra + xt), b = *reinterpret_cast<const ad_f4*>(R + rb + xt);
+                        ta[N] = R[ra + xt + N];
+                        tb[N] = R[rb + xt + N];
+#pragma unroll
+                        for (int t = 0; t < N; t++) {
+                            ta[t] = a[t];
+                            tb[t] = b[t];
+                        }
+                    } else {
+#pragma unroll
+                        for (int t = 0; t <= N; t++) {
+                            const int xc = lf_clampi(xt + t, 0, g.w - 1);
+                            ta[t] = R[ra + xc];
+                            tb[t] = R[rb + xc];
+                        }
+                    }
 #pragma unroll
                     for (int t = 0; t < N; t++) {
-                        ta[t] = a[t];
-                        tb[t] = b[t];
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t <= N; t++) {
-                        const int xc = lf_clampi(xt + t, 0, g.w - 1);
-                        ta[t] = R[ra + xc];
-                        tb[t] = R[rb + xc];
+                        some[u] |= gv[t] != 0.0f;
+                        const float v = sg * gv[t];
+                        sx[u] = fmaf(v, gy * (ta[t + 1] - ta[t]) + fy * (tb[t + 1] - tb[t]), sx[u]);
+                        sy[u] = fmaf(v, gx * (tb[t] - ta[t]) + fx * (tb[t + 1] - ta[t + 1]), sy[u]);
                     }
                 }
+        }
+        uint64_t any[U];
 #pragma unroll
-                for (int t = 0; t < N; t++) {
-                    some[u] |= gv[t] != 0.0f;
-                    const float v = sg * gv[t];
-                    sx[u] = fmaf(v, gy * (ta[t + 1] - ta[t]) + fy * (tb[t + 1] - tb[t]), sx[u]);
-                    sy[u] = fmaf(v, gx * (tb[t] - ta[t]) + fx * (tb[t + 1] - ta[t + 1]), sy[u]);
-                }
+        for (int u = 0; u < U; u++) {
+            any[u] = __ballot(some[u]);
+            if (LG < 6) any[u] = (any[u] >> (threadIdx.x & 63 & ~(G - 1))) & ((1ull << (G & 63)) - 1ull);
+#pragma unroll
+            for (int o = G / 2; o >= 1; o >>= 1) {
+                sx[u] += __shfl_xor(sx[u], o, 64);
+                sy[u] += __shfl_xor(sy[u], o, 64);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (lane == u && blk0 + u < g.nblk) {
+                gshift[rec0 + blk0 + u] = make_float2(sx[u], sy[u]);
+                // a block whose gradients are all zero adds zero to its reference
+                // through finite weights: its record is empty
+                AdRec e = d[u];
+                if (!any[u] && e.fx * 0.0f == 0.0f && e.fy * 0.0f == 0.0f) e.sg = 0;
+                brec[rec0 + blk0 + u] = ad_pack(e);
             }
     }
-    uint64_t any[U];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-        any[u] = __ballot(some[u]);
-        if (LG < 6) any[u] = (any[u] >> (threadIdx.x & 63 & ~(G - 1))) & ((1ull << (G & 63)) - 1ull);
-#pragma unroll
-        for (int o = G / 2; o >= 1; o >>= 1) {
-            sx[u] += __shfl_xor(sx[u], o, 64);
-            sy[u] += __shfl_xor(sy[u], o, 64);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < U; u++)
-        if (lane == u && blk0 + u < g.nblk) {
-            gshift[rec0 + blk0 + u] = make_float2(sx[u], sy[u]);
-            // a block whose gradients are all zero adds zero to its reference
-            // through finite weights: its record is empty
-            AdRec e = d[u];
-            if (!any[u] && e.fx * 0.0f == 0.0f && e.fy * 0.0f == 0.0f) e.sg = 0;
-            brec[rec0 + blk0 + u] = ad_pack(e);
-        }
 }
 
 extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_residual, const float* d_shift,
@@ -1333,7 +1598,7 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     const int all_general = !Bl.use_axes;
     if (Bl.use_axes) {
         const int64_t items = n_views * ((int64_t)width + height + g.w + g.h + g.na + g.nb);
-        hipLaunchKernelGGL(k_ad_axes, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, g, d_cams, n_views, width,
+        hipLaunchKernelGGL(k_ad_axes, dim3((unsigned)std::min<int64_t>((items + 255) / 256, 1 << 20)), dim3(256), 0, s, g, d_cams, n_views, width,
                            height, t);
         hipLaunchKernelGGL(k_ad_lists, dim3((unsigned)((g.na * g.nb + 3) / 4)), dim3(256), 0, s, g, n_views, t);
     }
@@ -1364,10 +1629,11 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     // level-0 gradients (every sample written) and up to two levels above
     const int64_t plane = (int64_t)g.w * g.h;
     AdGather ga{t, Bl.use_axes, all_general, rayf, d_grad_out, ki, vi, start, Bl.n_recs, n_views, width, height};
-    const int D = std::min(g.H - 1, 2), pix_wgs = (int)((plane + 255) / 256);
-    const int64_t clusters = (int64_t)((g.na + (1 << D) - 1) >> D) * ((g.nb + (1 << D) - 1) >> D);
+    const int D = std::min(g.H - 1, 2);
+    const int clusters = ((g.na + (1 << D) - 1) >> D) * ((g.nb + (1 << D) - 1) >> D);
     hipLaunchKernelGGL(D == 0 ? k_ad_gather<0> : (D == 1 ? k_ad_gather<1> : k_ad_gather<2>),
-                       dim3((unsigned)(clusters * pix_wgs)), dim3(256), 0, s, g, ga, pix_wgs, d_grad_residual);
+                       dim3((unsigned)((plane + 255) / 256), (unsigned)std::min(clusters, 65535)), dim3(256), 0, s, g, ga, clusters,
+                       d_grad_residual);
     for (int l = D + 1; l < g.H; l++)
         hipLaunchKernelGGL(k_ad_tree, dim3(8192), dim3(256), 0, s, g, l, d_grad_residual);
     // the shift pass reads the predictive nodes' gradients, which the
@@ -1388,7 +1654,8 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
                           : lg == 2 ? k_ad_shift<2, true>
                           : lg == 4 ? k_ad_shift<4, true>
                                     : k_ad_shift<6, true>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(3 * pn.total * groups)), dim3(256), 0, s, g, h->p, pn, groups,
+        const int n_wg = 3 * pn.total * groups;
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(n_wg, 1 << 22)), dim3(256), 0, s, g, h->p, pn, groups, n_wg,
                            d_residual, (const float2*)d_shift, d_grad_residual, (float2*)d_grad_shift, brec);
     }
     const int64_t n_tiles = 3 * (int64_t)g.n_refs * ((g.w + AD_TILE - 1) / AD_TILE) * ((g.h + AD_TILE - 1) / AD_TILE);

@@ -121,3 +121,18 @@ def test_record_sort_large(torch):
     g = rng.normal(size=(3, 3, 256, 256)).astype(np.float32)
     got = field.render_backward(res, sh, torch.from_numpy(cams).cuda(), 256, 256, torch.from_numpy(g).cuda())
     _compare(o, res, sh, cams, 256, 256, g, *got)
+
+
+@pytest.mark.parametrize("block,wo,ho,warp", [(8, 37, 19, 0.0), (8, 24, 24, 0.0), (8, 8, 6, 0.0), (2, 33, 9, 0.0),
+                                              (16, 40, 40, 4e-3), (8, 1, 1, 0.0)])
+def test_relaxed_forward_tiles(torch, block, wo, ho, warp):
+    """Tiles staged whole, in four parts and ray by ray (frames ever smaller
+    than the captured views), ragged sizes and projective cameras: within 1e-5
+    of the oracle, as every forward."""
+    o, field = _field(8, 8, 64, 64, block)
+    _, res, sh = _params(torch, field, wo, 2.0)
+    cams = lfscene.random_pinhole_cameras(3, 8, 8, 64, 64, wo, ho, seed=block, zoom_range=(0.9, 1.0))
+    if warp:
+        cams = lfscene.projective_warp(cams, warp, -warp)
+    got = field.render_relaxed(res, sh, torch.from_numpy(cams).cuda(), wo, ho).cpu().numpy().astype(np.float64)
+    assert np.abs(got - o.render_relaxed(res.cpu().numpy(), sh.cpu().numpy(), cams, wo, ho)).max() <= 1e-5
