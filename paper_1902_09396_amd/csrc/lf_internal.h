@@ -12,6 +12,9 @@ struct LfLayout {
     uint64_t root_off, root_bytes, table_off, table_bytes, payload_off, payload_bytes, mv_off, mv_bytes;
     int64_t n_rec;        // motion records over all channels and levels
     int64_t stream_bytes;
+    // per channel: sum over the levels of the largest SRV magnitude that the
+    // block table allows
+    int64_t srv_bound[3];
     // arena offsets
     int64_t a_root, a_table, a_payload, a_mv, a_refs, a_desc, a_status, arena;
     // sparse reference residency (LF_LOAD_SPARSE_REFS): a_refs holds n_tiles
