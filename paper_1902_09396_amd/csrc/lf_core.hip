@@ -736,6 +736,7 @@ extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbyte
         // when that does not settle the sample range are the samples decoded
         int64_t bound = 0;
         for (int c = 0; c < 3; c++) bound = std::max(bound, (int64_t)words[4 + c] + L.srv_bound[c]);
+        h->L.packed_levels = bound <= LF_SAMPLE_LIMIT;
         if (bound > LF_SAMPLE_LIMIT) {
             const int64_t ns = (int64_t)L.g.na * L.g.nb * L.g.w * L.g.h;
             const int64_t cblocks = std::min<int64_t>((ns + 255) / 256, 65536);

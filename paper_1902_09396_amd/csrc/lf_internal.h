@@ -15,6 +15,9 @@ struct LfLayout {
     // per channel: sum over the levels of the largest SRV magnitude that the
     // block table allows
     int64_t srv_bound[3];
+    // set by the load: that bound and the root keep every level's samples, not
+    // the leaf views' alone, inside the range of the packed 16-bit decode
+    int32_t packed_levels;
     // arena offsets
     int64_t a_root, a_table, a_payload, a_mv, a_refs, a_desc, a_status, arena;
     // sparse reference residency (LF_LOAD_SPARSE_REFS): a_refs holds n_tiles

@@ -24,6 +24,40 @@ __device__ __forceinline__ Ray lf_ray_setup(const LfGeom& g, const float* __rest
     return r;
 }
 
+// Level-of-detail rendering: rays address a grid of na x nb views, and view
+// (b, a)'s samples come from node (b >> lod, a >> lod) of the tree level that
+// the renderer's geometry has as its leaves.  LOD false: lod is 0 and the
+// grid is the geometry's own.
+struct LodGrid {
+    int na, nb, lod;
+};
+
+template <bool LOD>
+__device__ __forceinline__ void lf_view_axes(const LfGeom& g, const LodGrid& grid, float u, float v, int& a0, int& a1,
+                                             int& b0, int& b1, float& fu, float& fv)
+{
+    lf_axis(u, LOD ? grid.na : g.na, a0, a1, fu);
+    lf_axis(v, LOD ? grid.nb : g.nb, b0, b1, fv);
+    if (LOD) {
+        a0 >>= grid.lod;
+        a1 >>= grid.lod;
+        b0 >>= grid.lod;
+        b1 >>= grid.lod;
+    }
+}
+
+template <bool LOD>
+__device__ __forceinline__ Ray lf_ray_setup(const LfGeom& g, const LodGrid& grid, const float* __restrict__ cam, int i, int j)
+{
+    Ray r;
+    float u, v, s, t;
+    lf_ray(cam, i, j, u, v, s, t);
+    lf_view_axes<LOD>(g, grid, u, v, r.a0, r.a1, r.b0, r.b1, r.fu, r.fv);
+    lf_axis(s, g.w, r.x0, r.x1, r.fs);
+    lf_axis(t, g.h, r.y0, r.y1, r.ft);
+    return r;
+}
+
 // Quadrilinear blend of 16 samples given as unscaled 8-bit values (sample
 // 4 q + k: view q = (v-bit << 1 | u-bit), pixel k = (t-bit << 1 | s-bit)):
 // per view the st-bilinear sum with weights (1-fs)(1-ft), fs(1-ft), (1-fs)ft,
@@ -580,11 +614,14 @@ struct TileLds {
 // leaf samples are reconstructed one by one (luma walk, up-sampled chroma
 // walks) into the same LDS sample cache, without descriptors or staged
 // ancestors; the plan, the cache across groups and the blend are shared.
-template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false>
+// LOD: the samples of a coarser tree level (grid); g (and gc) are then the
+// geometry cut off below that level, whose nodes take the leaf views' place.
+template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false, bool LOD = false>
 __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc, const LfPtrs& pc,
                               const float* __restrict__ cams, int v0, int nf, int gmax, int wo, int ho, int txi,
-                              int tyi, float* __restrict__ out, const TileLds& S)
+                              int tyi, float* __restrict__ out, const TileLds& S, const LodGrid& grid = LodGrid{})
 {
+    static_assert(!(INLINE_FALLBACK && LOD), "the per-ray path takes the whole geometry and a level");
     // budgets of this instance (the dynamic LDS the launch reserved)
     constexpr int BD = SMALL_BLOCKS ? B_DESC_SB : B_DESC;
     constexpr int BR = SMALL_BLOCKS ? B_RGBA_SB : B_RGBA;
@@ -629,8 +666,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
         float u, v, s, t;
         lf_ray(cam, ci, cj, u, v, s, t);
         Ray r;
-        lf_axis(u, g.na, r.a0, r.a1, r.fu);
-        lf_axis(v, g.nb, r.b0, r.b1, r.fv);
+        lf_view_axes<LOD>(g, grid, u, v, r.a0, r.a1, r.b0, r.b1, r.fu, r.fv);
         lf_axis(s, g.w, r.x0, r.x1, r.fs);
         lf_axis(t, g.h, r.y0, r.y1, r.ft);
         const bool exact = cam[6] == 0.0f && cam[7] == 0.0f && cam[8] == 1.0f && cam[15] == 0.0f &&
@@ -665,7 +701,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
     __syncthreads();
     for (int f = 0; f < nf; f++) {
         if (fbox[f][0] != 0xFFFFFFFFu) continue;  // uniform
-        const Ray r = lf_ray_setup(g, cams + 18 * (v0 + f), ii, jj);
+        const Ray r = lf_ray_setup<LOD>(g, grid, cams + 18 * (v0 + f), ii, jj);
         const uint32_t m0 = wave_pk_min((uint32_t)r.a0 | ((uint32_t)r.b0 << 16));
         const uint32_t m1 = wave_pk_max((uint32_t)r.a1 | ((uint32_t)r.b1 << 16));
         const uint32_t m2 = wave_pk_min((uint32_t)r.x0 | ((uint32_t)r.y0 << 16));
@@ -1194,9 +1230,11 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                     lf_ray_h(cams + 18 * (v0 + q), (float)ii + 0.5f, (float)jj + 0.5f, u, v);
                     int a0, a1, b0, b1;
                     float fu, fv;
-                    lf_axis(u, g.na, a0, a1, fu);
-                    lf_axis(v, g.nb, b0, b1, fv);
-                    const uint32_t key = ((uint32_t)b0 << 16) | (uint32_t)a0;
+                    lf_view_axes<LOD>(g, grid, u, v, a0, a1, b0, b1, fu, fv);
+                    // the 2x2 block: its first view, and above the leaf level
+                    // whether the second row and column are other nodes
+                    uint32_t key = ((uint32_t)b0 << 16) | (uint32_t)a0;
+                    if (LOD) key |= (b1 != b0 ? 0x80000000u : 0u) | (a1 != a0 ? 0x8000u : 0u);
                     if (__ballot(key != ckey) != 0ull) {  // uniform
 #pragma unroll
                         for (int k = 0; k < 4; k++) {
@@ -1241,8 +1279,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                     if (st_shared) {
                         float u, v;
                         lf_ray_h(cams + 18 * (v0 + qq), (float)ii + 0.5f, (float)jj + 0.5f, u, v);
-                        lf_axis(u, g.na, r[h].a0, r[h].a1, r[h].fu);
-                        lf_axis(v, g.nb, r[h].b0, r[h].b1, r[h].fv);
+                        lf_view_axes<LOD>(g, grid, u, v, r[h].a0, r[h].a1, r[h].b0, r[h].b1, r[h].fu, r[h].fv);
                         r[h].x0 = rst.x0;
                         r[h].x1 = rst.x1;
                         r[h].y0 = rst.y0;
@@ -1250,7 +1287,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                         r[h].fs = rst.fs;
                         r[h].ft = rst.ft;
                     } else {
-                        r[h] = lf_ray_setup(g, cams + 18 * (v0 + qq), ii, jj);
+                        r[h] = lf_ray_setup<LOD>(g, grid, cams + 18 * (v0 + qq), ii, jj);
                     }
                     // x1 = x0 + 1 and y1 = y0 + 1: the captured views are at least one
                     // 4-pixel block wide and high on this path
