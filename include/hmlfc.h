@@ -91,8 +91,8 @@ typedef struct {
  * as int16 tiles, plus a tile index per block) instead of dense planes — the
  * reduced-memory reference storage of the Decompression Analysis.  Every
  * result is unchanged.  A sparse handle serves lf_decode_pixels(_lod),
- * lf_render_views(_per_ray, _lod) (one thread per ray) and the relaxed
- * render and adjoint; the serving loop rejects it. */
+ * lf_render_views(_per_ray, _lod) and the relaxed render and adjoint; the
+ * serving loop rejects it. */
 #define LF_LOAD_SPARSE_REFS 1
 
 /* Load flag: keep the reference SRVs as a per-pixel sparse matrix in
@@ -187,9 +187,10 @@ lf_status lf_decode_pixels_lod(const lf_handle* h, int32_t level, const int32_t*
 /* d_cams: device float [n_views][18].  d_out: device float
  * [n_views][3][height][width] (planar RGB).  width, height >= 1.  Runs the
  * staged tile kernel (on a 4:2:0 handle each leaf sample from the luma and
- * the up-sampled chroma decodes); fields with blocks smaller than 4x4 and
- * handles loaded with LF_LOAD_SPARSE_REFS or LF_LOAD_CSR_REFS run the
- * one-thread-per-ray kernel (same results). */
+ * the up-sampled chroma decodes); fields with blocks smaller than 4x4,
+ * handles loaded with LF_LOAD_CSR_REFS, and LF_LOAD_SPARSE_REFS handles whose
+ * decoded values or motion vectors are not bounded by the tile kernel's 16-bit
+ * lanes run the one-thread-per-ray kernel (same results). */
 lf_status lf_render_views(const lf_handle* h, const float* d_cams, int32_t n_views, int32_t width,
                           int32_t height, float* d_out, void* stream);
 

@@ -203,6 +203,7 @@ lf_status lf_parse(const uint8_t* s, size_t n, LfLayout* L)
             L->srv_bound[c] += top[0] + top[1];
         }
     int64_t rec = 0;
+    L->packed_vectors = 1;
     for (int c = 0; c < 3; c++)
         for (int l = g.H - 1; l >= 0; l--) {
             LfGeom& gg = geo(c);
@@ -221,6 +222,8 @@ lf_status lf_parse(const uint8_t* s, size_t n, LfLayout* L)
                 if ((int64_t)gg.mv_word[lc][l] + (bise_bits_host(m, 2 * expect) + 31) / 32 + 1 > mwords ||
                     (int64_t)gg.sig_word[lc][l] + (2 * expect + 31) / 32 + 1 > mwords)
                     return lf_fail(LF_EFORMAT, "motion-vector section out of range");
+                const int64_t most = ((int64_t)(2 * (m >> 5) + 1) << (m & 31)) - 1 - g.bias[l];
+                if (most > 2047 || g.bias[l] > 2047) L->packed_vectors = 0;
             }
             gg.rec_base[lc][l] = rec;
             rec += expect;
@@ -713,10 +716,17 @@ extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbyte
         const int64_t dblocks = std::min<int64_t>((nd + 255) / 256, 65536);
         hipLaunchKernelGGL(k_load_desc, dim3((unsigned)dblocks), dim3(256), 0, s, L.g, h->p, (uint4*)(A + L.a_desc),
                            status);
+        st = lf_check_launch("load_desc");
+        if (st != LF_OK) {
+            delete h;
+            return st;
+        }
+    }
+    if (!L.chroma420) {
         const int64_t per_channel = (int64_t)L.g.root_na * L.g.root_nb * L.g.w * L.g.h;
         hipLaunchKernelGGL(k_load_root_max, dim3((unsigned)std::min<int64_t>((per_channel + 1023) / 1024, 128), 3), dim3(256),
                            0, s, h->p.root, per_channel, status);
-        st = lf_check_launch("load_desc");
+        st = lf_check_launch("load_root_max");
         if (st != LF_OK) {
             delete h;
             return st;
@@ -730,14 +740,14 @@ extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbyte
         return lf_fail(LF_EDEVICE, "stream synchronise failed");
     }
     int flag = words[0];
-    if (!flag && !L.sparse && !L.chroma420) {
+    if (!flag && !L.chroma420) {
         // every decoded channel, and every partial sum from the root down, is
         // within the root's largest magnitude plus the levels' bounds; only
         // when that does not settle the sample range are the samples decoded
         int64_t bound = 0;
         for (int c = 0; c < 3; c++) bound = std::max(bound, (int64_t)words[4 + c] + L.srv_bound[c]);
-        h->L.packed_levels = bound <= LF_SAMPLE_LIMIT;
-        if (bound > LF_SAMPLE_LIMIT) {
+        h->L.packed_levels = bound <= LF_SAMPLE_LIMIT && L.packed_vectors;
+        if (bound > LF_SAMPLE_LIMIT && !L.sparse) {
             const int64_t ns = (int64_t)L.g.na * L.g.nb * L.g.w * L.g.h;
             const int64_t cblocks = std::min<int64_t>((ns + 255) / 256, 65536);
             hipLaunchKernelGGL(k_load_check, dim3((unsigned)cblocks), dim3(256), 0, s, L.g, h->p, status);

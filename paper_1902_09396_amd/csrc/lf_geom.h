@@ -237,10 +237,12 @@ __device__ __forceinline__ void lf_ycocg_to_rgb(int Y, int Co, int Cg, int& r, i
 
 // Block descriptor: x = payload word, y = min (16) | step (13) << 16 | phase code << 29,
 // z = mx (12, signed) | my (12, signed) << 12 | mode << 24, w = plane offset (elements)
-// of the reference plane (predictive node) or of the node's own plane (reference node).
+// of the reference plane (predictive node) or of the node's own plane (reference node);
+// block-sparse residency: the plane's index instead of its offset.
+template <int RES = LF_RES_DENSE>
 __device__ __forceinline__ uint4 lf_make_desc(const LfGeom& g, const LfPtrs& p, int c, int l, int B, int A, int blk)
 {
-    const uint32_t plane = (uint32_t)(g.w * g.h);
+    const uint32_t plane = RES == LF_RES_DENSE ? (uint32_t)(g.w * g.h) : 1u;
     const uint32_t ref = (uint32_t)(c * g.n_refs + g.ref_base[l] + (B >> 1) * g.na_l[l + 1] + (A >> 1)) * plane;
     if (!((A | B) & 1)) return make_uint4(0u, 0u, (uint32_t)MODE_PLANE << 24, ref);
     const int node = g.node_base[l] + B * g.na_l[l] + A;

@@ -15,8 +15,10 @@ struct LfLayout {
     // per channel: sum over the levels of the largest SRV magnitude that the
     // block table allows
     int64_t srv_bound[3];
-    // set by the load: that bound and the root keep every level's samples, not
-    // the leaf views' alone, inside the range of the packed 16-bit decode
+    // every motion vector fits the descriptors' 12 signed bits, by the sequences' widths
+    int32_t packed_vectors;
+    // set by the load: those bounds and the root keep every level's samples,
+    // not the leaf views' alone, inside the range of the packed 16-bit decode
     int32_t packed_levels;
     // arena offsets
     int64_t a_root, a_table, a_payload, a_mv, a_refs, a_desc, a_status, arena;

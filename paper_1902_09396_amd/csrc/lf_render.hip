@@ -72,7 +72,7 @@ lf_status lf_launch_render_rays(const lf_handle* h, const float* d_cams, int nv,
 // C420: a 4:2:0 stream, chroma geometry gc, pc (unused otherwise).  LOD: the
 // samples of a coarser tree level, g and gc cut off below it (grid unused
 // otherwise).
-template <bool SMALL_BLOCKS, bool C420, bool LOD>
+template <bool SMALL_BLOCKS, bool C420, bool LOD, int RES>
 __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGeom gc, LfPtrs pc,
                                                      const float* __restrict__ cams, int nv, int wo, int ho,
                                                      int tiles_x, int tiles_y, int chunk, int fpg, int64_t n_full,
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGe
         nf = min(per, c1 - v0);
         if (nf <= 0) return;
     }
-    lf_tile_views<false, SMALL_BLOCKS, C420, LOD>(g, p, gc, pc, cams, v0, nf, fpg, wo, ho, txi, tyi, out, S, grid);
+    lf_tile_views<false, SMALL_BLOCKS, C420, LOD, RES>(g, p, gc, pc, cams, v0, nf, fpg, wo, ho, txi, tyi, out, S, grid);
 }
 
 // Per-ray rendering of the (view, tile) pairs the batched kernel marked.
@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGe
 // of them at once (one per thread), compacts the marked ones, and renders
 // them one tile at a time, so a launch whose views are mostly marked (tiles
 // far minified) still spreads them over the whole grid.
-template <bool C420>
+template <bool C420, int RES>
 __global__ void __launch_bounds__(NT) k_render_fallback(LfGeom g, LfPtrs p, LfGeom gc, LfPtrs pc,
                                                         const float* __restrict__ cams, int nv, int wo, int ho,
                                                         int tiles_x, int tiles_y, int per_wg, float* __restrict__ out,
@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(NT) k_render_fallback(LfGeom g, LfPtrs p, LfGe
                 if (C420)
                     lf_render_one420(g, p, gc, pc, cams + 18 * v, i, j, o, lod);
                 else
-                    lf_render_one(g, p, cams + 18 * v, i, j, o, lod);
+                    lf_render_one<RES>(g, p, cams + 18 * v, i, j, o, lod);
 #pragma unroll
                 for (int c = 0; c < 3; c++) out[((int64_t)v * 3 + c) * npix + (int64_t)j * wo + i] = o[c];
             }
@@ -281,18 +281,21 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
     const size_t lds = small ? LDS_DYN_BYTES_SB : LDS_DYN_BYTES;
     using BatchKernel = void (*)(LfGeom, LfPtrs, LfGeom, LfPtrs, const float*, int, int, int, int, int, int, int,
                                  int64_t, int, float*, LodGrid);
-    static const BatchKernel kernels[2][2][2] = {
-        {{k_render_batch<false, false, false>, k_render_batch<false, false, true>},
-         {k_render_batch<false, true, false>, k_render_batch<false, true, true>}},
-        {{k_render_batch<true, false, false>, k_render_batch<true, false, true>},
-         {k_render_batch<true, true, false>, k_render_batch<true, true, true>}}};
-    const bool cut = lod > 0;
-    const BatchKernel kern = kernels[small][c420][cut];
-    static bool attr_set[2][2][2] = {};
-    if (lds > 65536 && !attr_set[small][c420][cut]) {
+    const bool cut = lod > 0, tiles = h->L.sparse == LF_RES_TILES;
+    // [small blocks][dense, coarser level, 4:2:0, 4:2:0 coarser level, block-sparse of any level]
+    constexpr int D = LF_RES_DENSE, T = LF_RES_TILES;
+    static const BatchKernel kernels[2][5] = {
+        {k_render_batch<false, false, false, D>, k_render_batch<false, false, true, D>, k_render_batch<false, true, false, D>,
+         k_render_batch<false, true, true, D>, k_render_batch<false, false, true, T>},
+        {k_render_batch<true, false, false, D>, k_render_batch<true, false, true, D>, k_render_batch<true, true, false, D>,
+         k_render_batch<true, true, true, D>, k_render_batch<true, false, true, T>}};
+    const int kind = tiles ? 4 : 2 * c420 + cut;
+    const BatchKernel kern = kernels[small][kind];
+    static bool attr_set[2][5] = {};
+    if (lds > 65536 && !attr_set[small][kind]) {
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return lf_fail(LF_EDEVICE, "cannot reserve %zu bytes of LDS", lds);
-        attr_set[small][c420][cut] = true;
+        attr_set[small][kind] = true;
     }
     // a 4:4:4 stream passes its own geometry as the (unused) chroma geometry
     const LfGeom& gc = c420 ? h->L.gc : h->L.g;
@@ -307,9 +310,25 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
     const int64_t fb_grid = std::min<int64_t>(pairs, h->L.g.bs >= 16 ? 1024 : 8192);
     const int64_t per_wg = (pairs + fb_grid - 1) / fb_grid;
     if (per_wg > 0x7FFFFFFF) return lf_fail(LF_EINVAL, "too many tiles");
-    hipLaunchKernelGGL(c420 ? k_render_fallback<true> : k_render_fallback<false>, dim3((unsigned)fb_grid), dim3(NT), 0,
-                       s, h->L.g, h->p, gc, pc, d_cams, nv, wo, ho, tx, ty, (int)per_wg, d_out, lod);
+    const auto rest = c420 ? k_render_fallback<true, D> : (tiles ? k_render_fallback<false, T> : k_render_fallback<false, D>);
+    hipLaunchKernelGGL(rest, dim3((unsigned)fb_grid), dim3(NT), 0, s, h->L.g, h->p, gc, pc, d_cams, nv, wo, ho, tx, ty, (int)per_wg, d_out, lod);
     return lf_check_launch("render_batch");
+}
+
+// Whether the tile renderer takes a render from tree level `level`: it
+// decodes quads of 4 pixels inside one block, on packed 16-bit lanes.  Dense
+// handles: the load refuses leaf samples beyond the lanes' range, and settles
+// the coarser levels' at once or not at all; 4:2:0 samples are decoded with 32
+// bits.  Block-sparse handles: taken when the load has settled the range of
+// every level and of the motion vectors (nothing is refused there).  The root
+// level is sixteen plain reads per ray: no tiles.  CSR handles search a row
+// per tap: no tiles.
+static bool lf_tiles_apply(const lf_handle* h, int level)
+{
+    const LfLayout& L = h->L;
+    if (L.g.bs < 4 || level >= L.g.H || L.sparse == LF_RES_CSR) return false;
+    if (L.sparse) return L.packed_levels != 0;
+    return level == 0 || L.chroma420 || L.packed_levels;
 }
 
 extern "C" lf_status lf_render_views(const lf_handle* h, const float* d_cams, int32_t n_views, int32_t width,
@@ -318,11 +337,8 @@ extern "C" lf_status lf_render_views(const lf_handle* h, const float* d_cams, in
     if (!h || n_views < 0 || width < 1 || height < 1) return lf_fail(LF_EINVAL, "bad argument");
     if (n_views == 0) return LF_OK;
     if (!d_cams || !d_out) return lf_fail(LF_EINVAL, "null buffer");
-    // the tile kernel decodes quads of 4 pixels inside one block and reads
-    // dense reference planes
-    if (h->L.g.bs < 4 || h->L.sparse)
-        return lf_launch_render_rays(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream);
-    return lf_launch_render_batch(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream);
+    if (lf_tiles_apply(h, 0)) return lf_launch_render_batch(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream);
+    return lf_launch_render_rays(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream);
 }
 
 extern "C" lf_status lf_render_views_per_ray(const lf_handle* h, const float* d_cams, int32_t n_views, int32_t width,
@@ -341,14 +357,9 @@ extern "C" lf_status lf_render_views_lod(const lf_handle* h, int32_t level, cons
         return lf_fail(LF_EINVAL, "bad argument");
     if (n_views == 0) return LF_OK;
     if (!d_cams || !d_out) return lf_fail(LF_EINVAL, "null buffer");
-    // The tile renderer with the tree cut off below the level: its packed
-    // 16-bit lanes need the level's partial sums in range, which the load
-    // settles for every level at once or not at all; 4:2:0 samples are decoded
-    // with 32 bits.  16 views of 512x512 at level 2 of 17x17x512x512: 0.098 ms
-    // against 1.10 ms one thread per ray.  The root level is sixteen plain
-    // reads per ray: no tiles.
-    const LfLayout& L = h->L;
-    if (L.g.bs >= 4 && !L.sparse && level < L.g.H && (level == 0 || L.chroma420 || L.packed_levels))
+    // 16 views of 512x512 at level 2 of 17x17x512x512: 0.098 ms through the
+    // tiles, 1.09 ms one thread per ray
+    if (lf_tiles_apply(h, level))
         return lf_launch_render_batch(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream, level);
     return lf_launch_render_rays(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream, level);
 }

@@ -439,8 +439,23 @@ struct QuadIn {
     uint32_t a0, a1, a2, b0, b1, b2;  // aligned words of tap rows y0, y0 + 1
 };
 
-__device__ __forceinline__ QuadIn lf_quad_fetch(const LfGeom& g, const LfPtrs& p, const int16_t* __restrict__ base,
-                                                const uint4& d, int y, int x0)
+//
+// Block-sparse references (RES tiles): the taps' aligned groups of four
+// columns each lie in one block, so a row is two groups, each the block's
+// tile (or zeros) read as 8 bytes; the window words are cut from them and the
+// rest is shared.  Root planes (root) are dense in every residency.
+template <int RES>
+__device__ __forceinline__ uint2 lf_tile_group(const LfGeom& g, const LfPtrs& p, uint32_t rp, int y, int x)
+{
+    const int t = p.slots[(size_t)rp * g.nblk + (y >> g.bsl) * g.nbx + (x >> g.bsl)];
+    // no tile: the section's first 8 bytes (there with no tile at all, too: the slots follow)
+    const size_t at = t < 0 ? 0 : ((size_t)t << (2 * g.bsl)) + (((y & (g.bs - 1)) << g.bsl) | (x & (g.bs - 1)));
+    const uint2 v = *reinterpret_cast<const uint2*>(p.refs + at);
+    return t < 0 ? make_uint2(0u, 0u) : v;
+}
+
+template <int RES>
+__device__ __forceinline__ QuadIn lf_quad_fetch(const LfGeom& g, const LfPtrs& p, bool root, const uint4& d, int y, int x0)
 {
     QuadIn in;
     const uint32_t mode = d.z >> 24;
@@ -455,8 +470,23 @@ __device__ __forceinline__ QuadIn lf_quad_fetch(const LfGeom& g, const LfPtrs& p
     // five taps from xb: the aligned words holding columns xs .. xs + 4, xs =
     // xb clamped into the row (a reference node: its own quad at x0)
     const int xs = plane ? x0 : max(min(xb, g.w - 5), 0);
-    const uint32_t ea = d.w + (uint32_t)__mul24(lf_clampi(y0, 0, g.h - 1), g.w) + (uint32_t)xs;
-    const uint32_t eb = d.w + (uint32_t)__mul24(lf_clampi(y0 + 1, 0, g.h - 1), g.w) + (uint32_t)xs;
+    const int ya = lf_clampi(y0, 0, g.h - 1), yb = lf_clampi(y0 + 1, 0, g.h - 1);
+    if (RES == LF_RES_TILES && !root) {
+        const int c0 = xs & ~3, c1 = min(c0 + 4, g.w - 4);
+        const uint2 a0 = lf_tile_group<RES>(g, p, d.w, ya, c0), a1 = lf_tile_group<RES>(g, p, d.w, ya, c1);
+        const uint2 b0 = lf_tile_group<RES>(g, p, d.w, yb, c0), b1 = lf_tile_group<RES>(g, p, d.w, yb, c1);
+        const bool odd = xs & 2;  // the window starts at the group's second word
+        in.a0 = odd ? a0.y : a0.x;
+        in.a1 = odd ? a1.x : a0.y;
+        in.a2 = odd ? a1.y : a1.x;
+        in.b0 = odd ? b0.y : b0.x;
+        in.b1 = odd ? b1.x : b0.y;
+        in.b2 = odd ? b1.y : b1.x;
+        return in;
+    }
+    const int16_t* base = root ? p.root : p.refs;
+    const uint32_t ea = d.w + (uint32_t)__mul24(ya, g.w) + (uint32_t)xs;
+    const uint32_t eb = d.w + (uint32_t)__mul24(yb, g.w) + (uint32_t)xs;
     const uint32_t* ra = reinterpret_cast<const uint32_t*>(base) + (ea >> 1);
     const uint32_t* rb = reinterpret_cast<const uint32_t*>(base) + (eb >> 1);
     in.a0 = ra[0];
@@ -616,7 +646,8 @@ struct TileLds {
 // ancestors; the plan, the cache across groups and the blend are shared.
 // LOD: the samples of a coarser tree level (grid); g (and gc) are then the
 // geometry cut off below that level, whose nodes take the leaf views' place.
-template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false, bool LOD = false>
+// RES: dense or block-sparse reference residency.
+template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false, bool LOD = false, int RES = LF_RES_DENSE>
 __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc, const LfPtrs& pc,
                               const float* __restrict__ cams, int v0, int nf, int gmax, int wo, int ho, int txi,
                               int tyi, float* __restrict__ out, const TileLds& S, const LodGrid& grid = LodGrid{})
@@ -1032,7 +1063,12 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
             const int qb = lf_div_small(e, gp.nA[l]), B = gp.B0[l] + qb, A = gp.A0[l] + e - qb * gp.nA[l];
             const int qk = lf_div_small(kb, nbkx), blk = (bky0 + qk) * g.nbx + bkx0 + kb - qk * nbkx;
             const int node = g.node_base[l] + B * g.na_l[l] + A;
-            desc[d] = p.desc[((size_t)c * g.n_nodes + node) * g.nblk + blk];
+            // block-sparse handles keep no descriptors: expanded here, once per
+            // tile, node and block
+            if (RES == LF_RES_DENSE)
+                desc[d] = p.desc[((size_t)c * g.n_nodes + node) * g.nblk + blk];
+            else
+                desc[d] = lf_make_desc<RES>(g, p, c, l, B, A, blk);
         }
         for (int sl = threadIdx.x; sl < nslots; sl += NT) {
             int l = 1;
@@ -1080,7 +1116,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                     const int kb = __mul24((y >> g.bsl) - bky0, nbkx) + (x0 >> g.bsl) - bkx0;
                     const uint4 d = root ? make_uint4(0u, 0u, (uint32_t)MODE_PLANE << 24, (info & 0x7FFFFFFFu) * plane)
                                          : desc[info + kb];
-                    in[u] = lf_quad_fetch(g, p, root ? p.root : p.refs, d, y, x0);
+                    in[u] = lf_quad_fetch<RES>(g, p, root, d, y, x0);
                     yy[u] = y;
                     xx[u] = x0;
                     sl4[u] = sl;
@@ -1137,7 +1173,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                 const int kb = __mul24((y >> g.bsl) - bky0, nbkx) + (x0 >> g.bsl) - bkx0;
                 const uint4* dq = desc + __mul24(3 * k, nbk) + kb;
 #pragma unroll
-                for (int c = 0; c < 3; c++) in[u][c] = lf_quad_fetch(g, p, p.refs, dq[c * nbk], y, x0);
+                for (int c = 0; c < 3; c++) in[u][c] = lf_quad_fetch<RES>(g, p, false, dq[c * nbk], y, x0);
                 kk2[u] = k;
                 rq2[u] = rq;
                 yy[u] = y;
