@@ -526,8 +526,9 @@ __device__ __forceinline__ uint2 lf_quad_finish(const LfGeom& g, const LfPtrs& p
     B[2] = __builtin_amdgcn_alignbit(in.b2, in.b1, sh);
     B[1] = __builtin_amdgcn_alignbit(B[2], B[0], 16);
     B[3] = __builtin_amdgcn_alignbit(in.b2 >> sh, B[2], 16);
-    if (xs != xb) {
-        // image border: tap c is column clamp(xb + c) = xs + k of the window
+    if (xs != xb || g.w < 5) {
+        // image border (always in a plane four columns wide, where the fifth
+        // tap has no column): tap c is column clamp(xb + c) = xs + k of the window
         uint32_t ta[5], tb[5];
 #pragma unroll
         for (int c = 0; c < 5; c++) {

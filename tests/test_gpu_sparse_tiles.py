@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("block,h,w,over", [
+    (4, 4, 4, {}),                                  # planes of one block: the fifth tap has no column
+    (4, 16, 4, dict(t_ref=100)),
     (4, 8, 8, {}),                                  # planes two blocks wide: most taps clamped
     (4, 24, 20, dict(t_ref=120, t_pred=120, subpel=False)),
     (4, 24, 20, dict(t_ref=1 << 20)),               # no reference block kept: no tiles at all
