@@ -186,11 +186,10 @@ lf_status lf_decode_pixels_lod(const lf_handle* h, int32_t level, const int32_t*
 
 /* d_cams: device float [n_views][18].  d_out: device float
  * [n_views][3][height][width] (planar RGB).  width, height >= 1.  Runs the
- * staged tile kernel (on a 4:2:0 handle each leaf sample from the luma and
- * the up-sampled chroma decodes); fields with blocks smaller than 4x4,
- * handles loaded with LF_LOAD_CSR_REFS, and LF_LOAD_SPARSE_REFS handles whose
- * decoded values or motion vectors are not bounded by the tile kernel's 16-bit
- * lanes run the one-thread-per-ray kernel (same results). */
+ * staged tile kernel; fields with blocks smaller than 4x4, handles loaded with
+ * LF_LOAD_CSR_REFS, and 4:2:0 or LF_LOAD_SPARSE_REFS handles whose decoded
+ * values or motion vectors are not bounded by the tile kernel's 16-bit lanes
+ * run the one-thread-per-ray kernel (same results). */
 lf_status lf_render_views(const lf_handle* h, const float* d_cams, int32_t n_views, int32_t width,
                           int32_t height, float* d_out, void* stream);
 

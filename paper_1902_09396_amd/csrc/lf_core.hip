@@ -407,13 +407,13 @@ __global__ void __launch_bounds__(256) k_load_ref_quads(LfGeom g, LfPtrs p, int1
     if (bad) atomicOr(status, LF_ST_REF);
 }
 
-// Largest root magnitude of each channel, into status words 4 .. 6 (zero
-// before; an integer maximum is the same in any order).
+// Largest root magnitude of channels c0 + blockIdx.y (c0 the first of the
+// planes given), into status words 4 .. 6 (zero before; an integer maximum is
+// the same in any order).
 __global__ void __launch_bounds__(256) k_load_root_max(const int16_t* __restrict__ root, int64_t per_channel,
-                                                       int* __restrict__ status)
+                                                       int c0, int* __restrict__ status)
 {
-    const int c = blockIdx.y;
-    const int16_t* r = root + c * per_channel;
+    const int16_t* r = root + blockIdx.y * per_channel;
     int m = 0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < per_channel; i += (int64_t)gridDim.x * 256)
         m = max(m, abs((int)r[i]));
@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(256) k_load_root_max(const int16_t* __restrict
     __shared__ int top[4];
     if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) atomicMax(status + 4 + c, max(max(top[0], top[1]), max(top[2], top[3])));
+    if (threadIdx.x == 0) atomicMax(status + 4 + c0 + blockIdx.y, max(max(top[0], top[1]), max(top[2], top[3])));
 }
 
 __global__ void k_load_refs(LfGeom g, LfPtrs p, int16_t* __restrict__ refs, int* __restrict__ status)
@@ -722,10 +722,11 @@ extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbyte
             return st;
         }
     }
-    if (!L.chroma420) {
-        const int64_t per_channel = (int64_t)L.g.root_na * L.g.root_nb * L.g.w * L.g.h;
-        hipLaunchKernelGGL(k_load_root_max, dim3((unsigned)std::min<int64_t>((per_channel + 1023) / 1024, 128), 3), dim3(256),
-                           0, s, h->p.root, per_channel, status);
+    for (int gi = 0; gi < (L.chroma420 ? 2 : 1); gi++) {
+        const LfGeom& g = gi ? L.gc : L.g;
+        const int64_t per_channel = (int64_t)g.root_na * g.root_nb * g.w * g.h;
+        hipLaunchKernelGGL(k_load_root_max, dim3((unsigned)std::min<int64_t>((per_channel + 1023) / 1024, 128), g.nch),
+                           dim3(256), 0, s, (gi ? h->pc : h->p).root, per_channel, gi, status);
         st = lf_check_launch("load_root_max");
         if (st != LF_OK) {
             delete h;
@@ -740,14 +741,14 @@ extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbyte
         return lf_fail(LF_EDEVICE, "stream synchronise failed");
     }
     int flag = words[0];
-    if (!flag && !L.chroma420) {
+    if (!flag) {
         // every decoded channel, and every partial sum from the root down, is
         // within the root's largest magnitude plus the levels' bounds; only
         // when that does not settle the sample range are the samples decoded
         int64_t bound = 0;
         for (int c = 0; c < 3; c++) bound = std::max(bound, (int64_t)words[4 + c] + L.srv_bound[c]);
         h->L.packed_levels = bound <= LF_SAMPLE_LIMIT && L.packed_vectors;
-        if (bound > LF_SAMPLE_LIMIT && !L.sparse) {
+        if (bound > LF_SAMPLE_LIMIT && !L.sparse && !L.chroma420) {
             const int64_t ns = (int64_t)L.g.na * L.g.nb * L.g.w * L.g.h;
             const int64_t cblocks = std::min<int64_t>((ns + 255) / 256, 65536);
             hipLaunchKernelGGL(k_load_check, dim3((unsigned)cblocks), dim3(256), 0, s, L.g, h->p, status);

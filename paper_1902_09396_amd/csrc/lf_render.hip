@@ -318,17 +318,17 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
 // Whether the tile renderer takes a render from tree level `level`: it
 // decodes quads of 4 pixels inside one block, on packed 16-bit lanes.  Dense
 // handles: the load refuses leaf samples beyond the lanes' range, and settles
-// the coarser levels' at once or not at all; 4:2:0 samples are decoded with 32
-// bits.  Block-sparse handles: taken when the load has settled the range of
-// every level and of the motion vectors (nothing is refused there).  The root
+// the coarser levels' at once or not at all.  4:2:0 and block-sparse handles:
+// taken when the load has settled the range of every level and of the motion
+// vectors (nothing is refused there).  The root
 // level is sixteen plain reads per ray: no tiles.  CSR handles search a row
 // per tap: no tiles.
 static bool lf_tiles_apply(const lf_handle* h, int level)
 {
     const LfLayout& L = h->L;
     if (L.g.bs < 4 || level >= L.g.H || L.sparse == LF_RES_CSR) return false;
-    if (L.sparse) return L.packed_levels != 0;
-    return level == 0 || L.chroma420 || L.packed_levels;
+    if (L.sparse || L.chroma420) return L.packed_levels != 0;
+    return level == 0 || L.packed_levels;
 }
 
 extern "C" lf_status lf_render_views(const lf_handle* h, const float* d_cams, int32_t n_views, int32_t width,

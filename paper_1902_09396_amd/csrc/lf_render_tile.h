@@ -634,6 +634,94 @@ struct TileLds {
     lf_fill_tab(digits_s);                                                                       \
     __syncthreads();
 
+// The half-size box that up-sampling a 4:2:0 footprint box reads: one chroma
+// row and column more on every side (clamped to the chroma plane), columns in
+// whole quads.
+struct ChromaBox {
+    int xq0, y0, sy, nq;
+};
+
+__device__ __forceinline__ ChromaBox lf_chroma_box(const LfGeom& gc, int xq0, int nq, int ymin, int sy)
+{
+    ChromaBox b;
+    b.y0 = max((ymin >> 1) - 1, 0);
+    b.sy = min(((ymin + sy - 1) >> 1) + 1, gc.h - 1) - b.y0 + 1;
+    b.xq0 = max((xq0 >> 1) - 1, 0) & ~3;
+    b.nq = (min((xq0 >> 1) + 2 * nq, gc.w - 1) >> 2) - (b.xq0 >> 2) + 1;
+    return b;
+}
+
+// Inverse YCoCg-R on pixel pairs (ch[channel][pair]), clamped to [0, 255],
+// packed as four RGBA8 pixels.
+__device__ __forceinline__ uint4 lf_rgba_quad(const lf_i16x2 (&ch)[3][2])
+{
+    uint4 px4;
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const lf_i16x2 Yv = ch[0][h], Co = ch[1][h], Cg = ch[2][h];
+        const lf_i16x2 t = Yv - (Cg >> lf_splat(1));
+        const lf_i16x2 G = Cg + t;
+        const lf_i16x2 Bv = t - (Co >> lf_splat(1));
+        const lf_i16x2 R = Bv + Co;
+        const lf_i16x2 z = lf_splat(0), m = lf_splat(255);
+        const uint32_t r2 = lf_as_u32(__builtin_elementwise_min(__builtin_elementwise_max(R, z), m));
+        const uint32_t g2 = lf_as_u32(__builtin_elementwise_min(__builtin_elementwise_max(G, z), m));
+        const uint32_t b2 = lf_as_u32(__builtin_elementwise_min(__builtin_elementwise_max(Bv, z), m));
+        const uint32_t rg = r2 | (g2 << 8);  // bytes R0 G0 R1 G1
+        // pixel 2h: R0 G0 B0 0; pixel 2h+1: R1 G1 B1 0
+        const uint32_t p0 = __builtin_amdgcn_perm(b2, rg, 0x0C040100u);
+        const uint32_t p1 = __builtin_amdgcn_perm(b2, rg, 0x0C060302u);
+        if (h == 0) {
+            px4.x = p0;
+            px4.y = p1;
+        } else {
+            px4.z = p0;
+            px4.w = p1;
+        }
+    }
+    return px4;
+}
+
+// Staged quads of 4:2:0 planes of one geometry: item it is quad rq of plane
+// it / rowq; plane_of maps a plane to (root?, first descriptor or root plane)
+// and `put` stores the quad's value.  Four quads per thread at a time, all
+// their loads issued before any is used.
+template <class PlaneOf, class Put>
+__device__ __forceinline__ void lf_stage_quads(const LfGeom& g, const LfPtrs& p, const uint4* desc, const uint32_t* digits,
+                                               int n_planes, int xq0, int y0, int sy, int nq, int bkx0, int bky0, int nbkx,
+                                               PlaneOf plane_of, Put put)
+{
+    const int rowq = sy * nq, n = n_planes * rowq;
+    const uint32_t m_rowq = lf_magic((uint32_t)rowq), m_nq = lf_magic((uint32_t)nq);
+    const uint32_t plane = (uint32_t)(g.w * g.h);
+    for (int it0 = threadIdx.x; it0 < n; it0 += 4 * NT) {
+        QuadIn in[4];
+        uint4 d[4];
+        int yy[4], xx[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int it = min(it0 + u * NT, n - 1);  // past the end: repeat the last quad, not stored
+            const int pl = lf_qdiv(it, m_rowq), rq = it - pl * rowq;
+            const int yl = lf_qdiv(rq, m_nq), qi = rq - yl * nq;
+            yy[u] = y0 + yl;
+            xx[u] = xq0 + 4 * qi;
+            const uint32_t info = plane_of(pl);
+            const bool root = info & 0x80000000u;
+            const int kb = __mul24((yy[u] >> g.bsl) - bky0, nbkx) + (xx[u] >> g.bsl) - bkx0;
+            d[u] = root ? make_uint4(0u, 0u, (uint32_t)MODE_PLANE << 24, (info & 0x7FFFFFFFu) * plane) : desc[info + kb];
+            in[u] = lf_quad_fetch<LF_RES_DENSE>(g, p, root, d[u], yy[u], xx[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int it = it0 + u * NT;
+            if (it < n) {
+                const int pl = lf_qdiv(it, m_rowq);
+                put(pl, it - pl * rowq, lf_quad_finish(g, p, in[u], d[u], yy[u], xx[u], digits));
+            }
+        }
+    }
+}
+
 // Render screen tile (txi, tyi) of views v0 .. v0 + nf - 1 (cameras cams[v],
 // output out[v][3][ho][wo]; nf <= FMAX), in groups of at most gmax
 // consecutive views.  A single view whose tile footprint exceeds the LDS
@@ -641,10 +729,11 @@ struct TileLds {
 // FALLBACK_MARK at the tile origin for a per-ray pass; the return value says
 // whether any view was left so (the same in every thread).  Every thread of
 // the workgroup calls it; LDS contents do not carry over between calls.
-// C420: a 4:2:0 stream (luma geometry g, p; chroma geometry gc, pc): the
-// leaf samples are reconstructed one by one (luma walk, up-sampled chroma
-// walks) into the same LDS sample cache, without descriptors or staged
-// ancestors; the plan, the cache across groups and the blend are shared.
+// C420: a 4:2:0 stream (luma geometry g, p; chroma geometry gc, pc): every
+// node is staged as one luma plane over the footprint box and two chroma
+// planes over the half-size box that its up-sampling reads; new leaf views'
+// chroma goes through a scratch third of the staged values.  The plan, the
+// cache across groups and the blend are shared.
 // LOD: the samples of a coarser tree level (grid); g (and gc) are then the
 // geometry cut off below that level, whose nodes take the leaf views' place.
 // RES: dense or block-sparse reference residency.
@@ -792,7 +881,14 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
             const uint32_t bx0 = (uint32_t)xq0 | ((uint32_t)ymin << 16), bx1 = (uint32_t)nq | ((uint32_t)sy << 16);
             const bool same = (uint32_t)__builtin_amdgcn_readfirstlane((int)gp.cbox0) == bx0 &&
                               (uint32_t)__builtin_amdgcn_readfirstlane((int)gp.cbox1) == bx1;  // cached entries hold this box
-            const int cap0 = min(CMAX, BR / npix), cap1 = min(CMAX, BSV / (3 * npix));
+            // 4:2:0: chroma box, its pixels and blocks; values and descriptors per node
+            const ChromaBox cb = C420 ? lf_chroma_box(gc, xq0, nq, ymin, sy) : ChromaBox{};
+            const int cnpix = C420 ? 4 * cb.nq * cb.sy : 0;
+            const int nbkc = C420 ? (((cb.xq0 + 4 * cb.nq - 1) >> gc.bsl) - (cb.xq0 >> gc.bsl) + 1) *
+                                        (((cb.y0 + cb.sy - 1) >> gc.bsl) - (cb.y0 >> gc.bsl) + 1)
+                                  : 0;
+            const int per_node = C420 ? npix + 2 * cnpix : 3 * npix, per_desc = C420 ? nbk + 2 * nbkc : 3 * nbk;
+            const int cap0 = min(CMAX, BR / npix), cap1 = min(CMAX, (C420 ? BSV - BSV / 3 : BSV) / per_node);
             const int nA0 = amax - amin + 1, nB0 = bmax - bmin + 1;
             ok = nA0 * nB0 <= LMAX && npix <= BR;
             if (!ok) break;
@@ -827,7 +923,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
             const bool new0 = use0 && ent0 < 0;
             const uint64_t newm0 = __ballot(new0);
             const int nnew0 = __popcll(newm0);
-            ok = ok && nnew0 <= __popcll(free0);
+            ok = ok && nnew0 <= __popcll(free0) && (!C420 || nnew0 * 2 * cnpix <= BSV / 3);
             if (!ok) break;
             // the k-th new leaf view takes the k-th free entry
             if ((free0 >> lane) & 1ull) inv[0][__popcll(free0 & ((1ull << lane) - 1ull))] = (uint8_t)lane;
@@ -854,7 +950,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
             }
             const uint64_t keep1 = __ballot(kneed);
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            int nd = C420 ? 0 : 3 * nbk * nnew0;
+            int nd = per_desc * nnew0;
             int cnt[LF_MAX_LEVELS + 1];
             cnt[0] = nnew0;
             const uint64_t free1 = ~keep1 & (cap1 >= 64 ? ~0ull : ((1ull << cap1) - 1ull));
@@ -869,7 +965,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
 #pragma unroll
             for (int l = 1; l <= LF_MAX_LEVELS + 1; l++) {
                 off[l] = total;
-                if (!C420 && l <= g.H) {  // a 4:2:0 group stages no ancestors
+                if (l <= g.H) {
                     const int nBl = (bmax >> l) - (bmin >> l) + 1, nAl = (amax >> l) - (amin >> l) + 1;
                     if (nBl * nAl > LMAX) ok = 0;
                     total += nBl * nAl;
@@ -925,7 +1021,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                     cnt[l] += __popcll(nmp[pp] & m);
                 }
                 nnew1 += cnt[l];
-                if (l < g.H) nd += 3 * nbk * cnt[l];
+                if (l < g.H) nd += per_desc * cnt[l];
             }
             const int ns = 3 * nnew1;
             ok = ok && nnew1 <= __popcll(free1) && nd <= BD && ns <= SLOT_MAX;
@@ -975,7 +1071,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                 for (int k = 0; k <= LF_MAX_LEVELS; k++) {
                     if (k == l) cl = cnt[k];
                     if (k >= 1 && k < l) s3 += 3 * cnt[k];
-                    if (k < l) d3 += 3 * nbk * cnt[k];
+                    if (k < l) d3 += per_desc * cnt[k];
                 }
                 gp.B0[l] = bmin >> l;
                 gp.A0[l] = amin >> l;
@@ -1051,6 +1147,113 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
         const int ndesc = LF_UNI(gp.ndesc), nslots = LF_UNI(gp.nslots), nnew0 = LF_UNI(gp.nnew[0]);
         const int B00 = LF_UNI(gp.B0[0]), A00 = LF_UNI(gp.A0[0]), nA0 = LF_UNI(gp.nA[0]);
 #undef LF_UNI
+        if constexpr (C420) {
+            const ChromaBox cb = lf_chroma_box(gc, xq0, nq, ymin, rowq / nq);
+            const int crowq = cb.sy * cb.nq, cbkx0 = cb.xq0 >> gc.bsl, cbky0 = cb.y0 >> gc.bsl;
+            const int cnbkx = ((cb.xq0 + 4 * cb.nq - 1) >> gc.bsl) - cbkx0 + 1;
+            const int nbkc = cnbkx * (((cb.y0 + cb.sy - 1) >> gc.bsl) - cbky0 + 1);
+            const int per = nbk + 2 * nbkc, planes = rowq + 2 * crowq;  // descriptors, staged quads per node
+            // 1a: descriptors (luma, then Co and Cg), expanded here: 4:2:0
+            // handles keep none; slot table; ancestor entries of the new leaves
+            for (int d = threadIdx.x; d < ndesc; d += NT) {
+                int l = 0;
+                while (l + 1 < g.H && d >= gp.dbase[l + 1]) l++;
+                const int k = lf_div_small(d - gp.dbase[l], per);
+                int j = d - gp.dbase[l] - k * per;
+                const int e = nodelist[l][k] & 0xFF;
+                const int qb = lf_div_small(e, gp.nA[l]), B = gp.B0[l] + qb, A = gp.A0[l] + e - qb * gp.nA[l];
+                if (j < nbk) {
+                    const int qk = lf_div_small(j, nbkx);
+                    desc[d] = lf_make_desc(g, p, 0, l, B, A, (bky0 + qk) * g.nbx + bkx0 + j - qk * nbkx);
+                } else {
+                    const int cc = j >= nbk + nbkc;
+                    j -= nbk + cc * nbkc;
+                    const int qk = lf_div_small(j, cnbkx);
+                    desc[d] = lf_make_desc(gc, pc, cc, l, B, A, (cbky0 + qk) * gc.nbx + cbkx0 + j - qk * cnbkx);
+                }
+            }
+            for (int sl = threadIdx.x; sl < nslots; sl += NT) {
+                int l = 1;
+                while (l < g.H && sl >= gp.sbase[l + 1]) l++;
+                const int row = sl - gp.sbase[l], k = row / 3, c = row - 3 * k;
+                const uint32_t nl = nodelist[l][k];
+                if (l == g.H) {
+                    const int e = nl & 0xFF;
+                    const int qb = lf_div_small(e, gp.nA[l]), B = gp.B0[l] + qb, A = gp.A0[l] + e - qb * gp.nA[l];
+                    slotinfo[sl] = 0x80000000u | (uint32_t)(((c == 2 ? 1 : 0) * g.root_nb + B) * g.root_na + A);
+                } else {
+                    slotinfo[sl] = (uint32_t)(gp.dbase[l] + k * per + (c == 0 ? 0 : nbk + (c - 1) * nbkc));
+                }
+                slotdst[sl] = (uint8_t)(nl >> 8);
+            }
+            for (int k = threadIdx.x; k < nnew0; k += NT) {
+                const int e = nodelist[0][k] & 0xFF;
+                const int qb = lf_div_small(e, nA0), b = B00 + qb, a = A00 + e - qb * nA0;
+                for (int l = 1; l <= g.H; l++)
+                    ancs[k][l - 1] = (uint8_t)nodemap[l][__mul24((b >> l) - gp.B0[l], gp.nA[l]) + ((a >> l) - gp.A0[l])];
+            }
+            __syncthreads();
+            // 1b: ancestors and roots, luma then chroma planes
+            uint2* const staged = reinterpret_cast<uint2*>(sval);
+            lf_stage_quads(
+                g, p, desc, digits, nslots / 3, xq0, ymin, rowq / nq, nq, bkx0, bky0, nbkx, [&](int pl) { return slotinfo[3 * pl]; },
+                [&](int pl, int rq, uint2 v) { staged[__mul24((int)slotdst[3 * pl], planes) + rq] = v; });
+            lf_stage_quads(
+                gc, pc, desc, digits, nslots / 3 * 2, cb.xq0, cb.y0, cb.sy, cb.nq, cbkx0, cbky0, cnbkx,
+                [&](int pl) { return slotinfo[3 * (pl >> 1) + 1 + (pl & 1)]; },
+                [&](int pl, int rq, uint2 v) {
+                    staged[__mul24((int)slotdst[3 * (pl >> 1)], planes) + rowq + (pl & 1) * crowq + rq] = v;
+                });
+            __syncthreads();
+            // 1c: the new leaf views' chroma: their SRVs plus the ancestors'
+            uint2* const leafc = reinterpret_cast<uint2*>(sval + (BSV - BSV / 3) / 4 * 4);
+            lf_stage_quads(
+                gc, pc, desc, digits, 2 * nnew0, cb.xq0, cb.y0, cb.sy, cb.nq, cbkx0, cbky0, cnbkx,
+                [&](int pl) { return (uint32_t)((pl >> 1) * per + nbk + (pl & 1) * nbkc); },
+                [&](int pl, int rq, uint2 v) {
+                    lf_i16x2 v0 = lf_as_i16x2(v.x), v1 = lf_as_i16x2(v.y);
+                    for (int l = 1; l <= g.H; l++) {
+                        const uint2 a = staged[__mul24((int)ancs[pl >> 1][l - 1], planes) + rowq + (pl & 1) * crowq + rq];
+                        v0 += lf_as_i16x2(a.x);
+                        v1 += lf_as_i16x2(a.y);
+                    }
+                    leafc[pl * crowq + rq] = make_uint2(lf_as_u32(v0), lf_as_u32(v1));
+                });
+            __syncthreads();
+            // 2: leaf samples: luma SRV plus ancestors; Co and Cg of the quad
+            // blended from four half-size columns of two half-size rows
+            // (centred bilinear, in 32 bits)
+            const int16_t* const lc = reinterpret_cast<const int16_t*>(leafc);
+            lf_stage_quads(
+                g, p, desc, digits, nnew0, xq0, ymin, rowq / nq, nq, bkx0, bky0, nbkx, [&](int pl) { return (uint32_t)(pl * per); },
+                [&](int k, int rq, uint2 v) {
+                    lf_i16x2 ch[3][2] = {{lf_as_i16x2(v.x), lf_as_i16x2(v.y)}, {}, {}};
+                    for (int l = 1; l <= g.H; l++) {
+                        const uint2 a = staged[__mul24((int)ancs[k][l - 1], planes) + rq];
+                        ch[0][0] += lf_as_i16x2(a.x);
+                        ch[0][1] += lf_as_i16x2(a.y);
+                    }
+                    const int yl = lf_qdiv(rq, m_nq), y = ymin + yl, hx = (xq0 + 4 * (rq - yl * nq)) >> 1;
+                    const int h0 = (y >> 1) - ((y & 1) ? 0 : 1), wy0 = (y & 1) ? 3 : 1, wy1 = 4 - wy0;
+                    const int r0 = max(h0, 0) - cb.y0, r1 = min(h0 + 1, gc.h - 1) - cb.y0;
+                    const int x[4] = {max(hx - 1, 0) - cb.xq0, hx - cb.xq0, min(hx + 1, gc.w - 1) - cb.xq0,
+                                      min(hx + 2, gc.w - 1) - cb.xq0};
+#pragma unroll
+                    for (int cc = 0; cc < 2; cc++) {
+                        const int16_t* a = lc + 4 * ((2 * k + cc) * crowq + r0 * cb.nq);
+                        const int16_t* b = lc + 4 * ((2 * k + cc) * crowq + r1 * cb.nq);
+                        int q[4];
+#pragma unroll
+                        for (int i4 = 0; i4 < 4; i4++) q[i4] = wy0 * a[x[i4]] + wy1 * b[x[i4]];
+                        const int o0 = (q[0] + 3 * q[1] + 8) >> 4, o1 = (3 * q[1] + q[2] + 8) >> 4;
+                        const int o2 = (q[1] + 3 * q[2] + 8) >> 4, o3 = (3 * q[2] + q[3] + 8) >> 4;
+                        ch[1 + cc][0] = lf_as_i16x2(lf_pack_lo((uint32_t)o0, (uint32_t)o1));
+                        ch[1 + cc][1] = lf_as_i16x2(lf_pack_lo((uint32_t)o2, (uint32_t)o3));
+                    }
+                    reinterpret_cast<uint4*>(rgba)[__mul24((int)(nodelist[0][k] >> 8), rowq) + rq] = lf_rgba_quad(ch);
+                });
+            __syncthreads();
+        } else {
         // phase 1a: block descriptors of the new nodes of levels 0..H-1, the
         // slot table of the new staged values (levels 1..H), and the
         // ancestor slots of the new leaf views
@@ -1088,7 +1291,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
             slotinfo[sl] = info;
             slotdst[sl] = (uint8_t)(3 * (nl >> 8) + c);
         }
-        for (int k = threadIdx.x; k < (C420 ? 0 : nnew0); k += NT) {
+        for (int k = threadIdx.x; k < nnew0; k += NT) {
             const int e = nodelist[0][k] & 0xFF;
             const int qb = lf_div_small(e, nA0), b = B00 + qb, a = A00 + e - qb * nA0;
             for (int l = 1; l <= g.H; l++) {
@@ -1141,28 +1344,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
         // phase 2: every new (view, pixel quad) sample: level-0 SRV + staged
         // ancestors and root; two quads (six channel decodes) per thread at a time
         const int n2 = nnew0 * rowq;
-        if (C420) {
-            // 4:2:0: each sample of the quad from the luma walk and the
-            // up-sampled chroma walks, inverse YCoCg-R, RGBA8
-            for (int it = threadIdx.x; it < n2; it += NT) {
-                const int k = lf_qdiv(it, m_rowq), rq = it - k * rowq;
-                const int yl = lf_qdiv(rq, m_nq), qi = rq - yl * nq;
-                const int y = ymin + yl, x0 = xq0 + 4 * qi;
-                const uint32_t nl = nodelist[0][k];
-                const int e = nl & 0xFF;
-                const int qb = lf_div_small(e, nA0), b = B00 + qb, a = A00 + e - qb * nA0;
-                uint32_t px[4];
-#pragma unroll 1
-                for (int t = 0; t < 4; t++) {
-                    int R, G, B;
-                    lf_ycocg_to_rgb(lf_decode_channel(g, p, 0, b, a, y, x0 + t), lf_chroma_up(gc, pc, 0, b, a, y, x0 + t),
-                                    lf_chroma_up(gc, pc, 1, b, a, y, x0 + t), R, G, B);
-                    px[t] = (uint32_t)R | ((uint32_t)G << 8) | ((uint32_t)B << 16);
-                }
-                reinterpret_cast<uint4*>(rgba)[__mul24((int)(nl >> 8), rowq) + rq] = make_uint4(px[0], px[1], px[2], px[3]);
-            }
-        }
-        for (int it0 = threadIdx.x; it0 < (C420 ? 0 : n2); it0 += 2 * NT) {
+        for (int it0 = threadIdx.x; it0 < n2; it0 += 2 * NT) {
             QuadIn in[2][3];
             int kk2[2], rq2[2], yy[2], xx[2];
 #pragma unroll
@@ -1204,35 +1386,11 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
                     ch[c][1] += lf_as_i16x2(s4.y);
                 }
             }
-            // inverse YCoCg-R on pixel pairs, clamped to [0, 255], packed as RGBA8
-            uint4 px4;
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const lf_i16x2 Yv = ch[0][h], Co = ch[1][h], Cg = ch[2][h];
-                const lf_i16x2 t = Yv - (Cg >> lf_splat(1));
-                const lf_i16x2 G = Cg + t;
-                const lf_i16x2 Bv = t - (Co >> lf_splat(1));
-                const lf_i16x2 R = Bv + Co;
-                const lf_i16x2 z = lf_splat(0), m = lf_splat(255);
-                const uint32_t r2 = lf_as_u32(__builtin_elementwise_min(__builtin_elementwise_max(R, z), m));
-                const uint32_t g2 = lf_as_u32(__builtin_elementwise_min(__builtin_elementwise_max(G, z), m));
-                const uint32_t b2 = lf_as_u32(__builtin_elementwise_min(__builtin_elementwise_max(Bv, z), m));
-                const uint32_t rg = r2 | (g2 << 8);  // bytes R0 G0 R1 G1
-                // pixel 2h: R0 G0 B0 0; pixel 2h+1: R1 G1 B1 0
-                const uint32_t p0 = __builtin_amdgcn_perm(b2, rg, 0x0C040100u);
-                const uint32_t p1 = __builtin_amdgcn_perm(b2, rg, 0x0C060302u);
-                if (h == 0) {
-                    px4.x = p0;
-                    px4.y = p1;
-                } else {
-                    px4.z = p0;
-                    px4.w = p1;
-                }
-            }
-            reinterpret_cast<uint4*>(rgba)[__mul24((int)(nodelist[0][k] >> 8), rowq) + rq] = px4;
+            reinterpret_cast<uint4*>(rgba)[__mul24((int)(nodelist[0][k] >> 8), rowq) + rq] = lf_rgba_quad(ch);
             }
         }
         __syncthreads();
+        }
         // phase 3: blend every ray of the group's views: with one shared (s, t)
         // axis view by view, reusing per-view (s, t) sums; otherwise two views
         // at a time (the second view's sample reads in flight during the
