@@ -7,6 +7,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/hmlfc.h"
@@ -46,6 +47,21 @@ lf_status lf_check_launch(const char* what)
 
 static uint32_t rd32(const uint8_t* p) { uint32_t v; memcpy(&v, p, 4); return v; }
 static uint64_t rd64(const uint8_t* p) { uint64_t v; memcpy(&v, p, 8); return v; }
+
+void lf_parallel(int parts, const std::function<void(int)>& work)
+{
+    std::vector<std::thread> threads;
+    int started = 1;
+    try {
+        threads.reserve((size_t)parts);
+        for (; started < parts; started++) threads.emplace_back(work, started);
+    } catch (const std::exception&) {
+        // no more threads to be had: the caller does the rest itself
+    }
+    work(0);
+    for (int k = started; k < parts; k++) work(k);
+    for (auto& t : threads) t.join();
+}
 
 static int64_t bise_bits_host(int mode, int64_t n)
 {
@@ -167,41 +183,78 @@ lf_status lf_parse(const uint8_t* s, size_t n, LfLayout* L)
     // section, and every value the mode can hold, (min + v) * step, must
     // stay within LF_RES_LIMIT so that the decoders' int32 sums cannot wrap
     const uint8_t* tab = s + L->table_off;
-    for (int c = 0; c < 3; c++)
-        for (int l = g.H - 1; l >= 0; l--) {
-            const int nblk = geo(c).nblk, step = g.step[l];
-            const uint8_t* t = tab + 8 * (tfirst[c] + (int64_t)g.node_base[l] * nblk);
-            // per mode: payload words + 1, values it can hold
-            int64_t words1[256], cap[256];
-            for (int m = 0; m < 256; m++) {
-                const bool ok = (m >> 5) <= 2 && (m & 31) <= 20;
-                words1[m] = ok ? (bise_bits_host(m, (int64_t)g.bs * g.bs) + 31) / 32 + 1 : -1;
-                cap[m] = ok ? (int64_t)(2 * (m >> 5) + 1) << (m & 31) : 0;  // values 0 .. cap - 1
-            }
-            int64_t top[2] = {0, 0};  // largest residual magnitude of reference and of predictive blocks
-            for (int B = 0; B < g.nb_l[l]; B++)
-                for (int A = 0; A < g.na_l[l]; A++) {
-                    int64_t most = 0;
-                    for (int k = 0; k < nblk; k++, t += 8) {
-                        const int mode = t[6];
-                        if (mode == LF_MODE_ZERO) continue;
-                        const long long e = (long long)((t - tab) / 8);
-                        if (words1[mode] < 0) return lf_fail(LF_EFORMAT, "bad block mode at entry %lld", e);
-                        if ((int64_t)rd32(t) + words1[mode] > pwords)
-                            return lf_fail(LF_EFORMAT, "block payload out of range");
-                        int16_t mn;
-                        memcpy(&mn, t + 4, 2);
-                        const int64_t lo = (int64_t)mn * step, hi = ((int64_t)mn + cap[mode] - 1) * step;
-                        most = std::max(most, std::max(std::abs(lo), std::abs(hi)));
-                        if (most > LF_RES_LIMIT)
-                            return lf_fail(LF_EFORMAT, "block residual range beyond %d at entry %lld", LF_RES_LIMIT, e);
-                    }
-                    top[(A | B) & 1] = std::max(top[(A | B) & 1], most);
+    // per mode: payload words + 1 (the window may read one word on), and values it can hold
+    int64_t words1[256], cap[256];
+    for (int m = 0; m < 256; m++) {
+        const bool ok = (m >> 5) <= 2 && (m & 31) <= 20;
+        words1[m] = ok ? (bise_bits_host(m, (int64_t)g.bs * g.bs) + 31) / 32 + 1 : -1;
+        cap[m] = ok ? (int64_t)(2 * (m >> 5) + 1) << (m & 31) : 0;  // values 0 .. cap - 1
+    }
+    // nodes m0 .. m1 - 1 of the table's order (channel, then node): the first
+    // bad entry, and the largest residual magnitude of each channel and
+    // level's reference and predictive blocks
+    struct Scan {
+        int64_t bad = -1;
+        int what = 0;  // 1 mode, 2 payload, 3 range
+        int64_t top[3][LF_MAX_LEVELS][2] = {};
+    };
+    auto scan = [&](int64_t m0, int64_t m1, Scan* r) {
+        for (int64_t m = m0; m < m1; m++) {
+            const int c = (int)(m / nodes), node = (int)(m - c * nodes), nblk = geo(c).nblk;
+            int l = 0;
+            while (node < g.node_base[l]) l++;
+            const int local = node - g.node_base[l], B = local / g.na_l[l], A = local - B * g.na_l[l];
+            const int step = g.step[l];
+            const int64_t first = tfirst[c] + (int64_t)node * nblk;
+            const uint8_t* t = tab + 8 * first;
+            int64_t most = 0;
+            for (int k = 0; k < nblk; k++, t += 8) {
+                const int mode = t[6];
+                if (mode == LF_MODE_ZERO) continue;
+                int what = 0;
+                if (words1[mode] < 0) {
+                    what = 1;
+                } else if ((int64_t)rd32(t) + words1[mode] > pwords) {
+                    what = 2;
+                } else {
+                    int16_t mn;
+                    memcpy(&mn, t + 4, 2);
+                    const int64_t lo = (int64_t)mn * step, hi = ((int64_t)mn + cap[mode] - 1) * step;
+                    most = std::max(most, std::max(std::abs(lo), std::abs(hi)));
+                    if (most > LF_RES_LIMIT) what = 3;
                 }
-            // a node's SRV is a reference's residual, or a residual plus a
-            // weighted mean of reference values, rounded (no further from zero)
-            L->srv_bound[c] += top[0] + top[1];
+                if (what) {
+                    r->bad = first + k;
+                    r->what = what;
+                    return;
+                }
+            }
+            int64_t& top = r->top[c][l][(A | B) & 1];
+            top = std::max(top, most);
         }
+    };
+    // a large table is scanned by up to eight threads (1.2 M entries: 1.6 ms by one)
+    const int64_t all_nodes = 3 * nodes;
+    const int parts = (int)std::min<int64_t>(tb >> 16 ? 8 : 1, all_nodes);
+    Scan res[8];
+    lf_parallel(parts, [&](int k) { scan(all_nodes * k / parts, all_nodes * (k + 1) / parts, &res[k]); });
+    for (int k = 0; k < parts; k++)
+        switch (res[k].what) {
+            case 1: return lf_fail(LF_EFORMAT, "bad block mode at entry %lld", (long long)res[k].bad);
+            case 2: return lf_fail(LF_EFORMAT, "block payload out of range");
+            case 3:
+                return lf_fail(LF_EFORMAT, "block residual range beyond %d at entry %lld", LF_RES_LIMIT,
+                               (long long)res[k].bad);
+        }
+    // a node's SRV is a reference's residual, or a residual plus a weighted
+    // mean of reference values, rounded (no further from zero)
+    for (int c = 0; c < 3; c++)
+        for (int l = 0; l < g.H; l++)
+            for (int kind = 0; kind < 2; kind++) {
+                int64_t top = 0;
+                for (int k = 0; k < parts; k++) top = std::max(top, res[k].top[c][l][kind]);
+                L->srv_bound[c] += top;
+            }
     int64_t rec = 0;
     L->packed_vectors = 1;
     for (int c = 0; c < 3; c++)

@@ -3,6 +3,7 @@
 
 #include <cstdarg>
 #include <cstdint>
+#include <functional>
 
 #include "../../include/hmlfc.h"
 #include "lf_geom.h"
@@ -54,6 +55,11 @@ lf_status lf_require_full_chroma(const lf_handle* h, const char* what);
 lf_status lf_fail(lf_status s, const char* fmt, ...);
 lf_status lf_check_launch(const char* what);
 lf_status lf_parse(const uint8_t* s, size_t n, LfLayout* L);
+
+// work(0) .. work(parts - 1), each on a thread of its own while threads can be
+// started (work(0) and the rest on the caller's); returns when all are done.
+// work must not throw.
+void lf_parallel(int parts, const std::function<void(int)>& work);
 
 // Phase-shifted motion search (lf_search.hip) on device planes, for the
 // device encoder: checks the sizes, enqueues k_mc_search on `stream`.

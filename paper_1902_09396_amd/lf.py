@@ -270,6 +270,17 @@ class EncodeParams(C.Structure):
                 ("no_mc", C.c_int32), ("chroma420", C.c_int32)]
 
 
+class _EncodedStream:
+    """Owner of a stream the library allocated: arrays made from it keep it alive."""
+
+    def __init__(self, address: int, size: int):
+        self._address, self._free = address, lib().lf_encode_free
+        self.__array_interface__ = {"data": (address, False), "shape": (size,), "typestr": "|u1", "version": 3}
+
+    def __del__(self):
+        self._free(self._address)
+
+
 def encode(light_field: np.ndarray, enc: dict) -> np.ndarray:
     """Encode a uint8 [nb][na][h][w][3] light field on the current GPU; returns the stream bytes."""
     lf = np.ascontiguousarray(light_field, dtype=np.uint8)
@@ -283,9 +294,7 @@ def encode(light_field: np.ndarray, enc: dict) -> np.ndarray:
     check(lib().lf_encode_device(lf.ctypes.data_as(C.c_void_p), nb, na, h, w, C.byref(p), _ptr(work), work.numel(),
                                  _stream(), C.byref(out), C.byref(n)))
     del work
-    buf = np.ctypeslib.as_array(C.cast(out, C.POINTER(C.c_uint8)), shape=(n.value,)).copy()
-    lib().lf_encode_free(out)
-    return buf
+    return np.asarray(_EncodedStream(out.value, n.value))
 
 
 def mc_search(pred: torch.Tensor, ref: torch.Tensor, items: torch.Tensor, block: int, win: int,
