@@ -736,8 +736,11 @@ __device__ __forceinline__ void lf_stage_quads(const LfGeom& g, const LfPtrs& p,
 // cache across groups and the blend are shared.
 // LOD: the samples of a coarser tree level (grid); g (and gc) are then the
 // geometry cut off below that level, whose nodes take the leaf views' place.
-// RES: dense or block-sparse reference residency.
-template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false, bool LOD = false, int RES = LF_RES_DENSE>
+// RES: dense or block-sparse reference residency.  LONE: groups of one view
+// on a new box take the plan without lookups (left out, the general plan
+// serves them too).
+template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false, bool LOD = false, int RES = LF_RES_DENSE,
+          bool LONE = true>
 __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc, const LfPtrs& pc,
                               const float* __restrict__ cams, int v0, int nf, int gmax, int wo, int ho, int txi,
                               int tyi, float* __restrict__ out, const TileLds& S, const LodGrid& grid = LodGrid{})
@@ -892,193 +895,246 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
             const int nA0 = amax - amin + 1, nB0 = bmax - bmin + 1;
             ok = nA0 * nB0 <= LMAX && npix <= BR;
             if (!ok) break;
-            // node maps start empty; cache entries that a node of this group
-            // keeps write their index into the node's map (entry side), and
-            // each node then reads its map (node side; same wave, LDS in order)
-#pragma unroll
-            for (int l = 0; l <= LF_MAX_LEVELS; l++)
-                if (l <= g.H) nodemap[l][lane] = -1;
-            // level 0: leaf views some ray of the group reaches
-            bool use0 = false;
-            if (ok && lane < nA0 * nB0) {
-                const int qb = lf_div_small(lane, nA0), b = bmin + qb, a = amin + lane - qb * nA0;
-                for (int q = f; q < f + n && !use0; q++) {
-                    const uint32_t q0 = fbox[q][0], q1 = fbox[q][1];
-                    use0 = (int)(q0 >> 16) <= b && (int)(q1 >> 16) >= b && (int)(q0 & 0xFFFFu) <= a &&
-                           (int)(q1 & 0xFFFFu) >= a;
+            int nd, ns;  // descriptors and staged slots of the new nodes
+            if (LONE && n == 1 && !same) {
+                // One view on a box that no cache entry holds: its rectangle
+                // of leaf views is used whole, every node above it is needed
+                // and all are new, so entries and lists are the nodes in
+                // order and nothing is looked up.  (A single view of a call,
+                // and every group of unrelated cameras: the general plan took
+                // 40% of such a workgroup's time.)  Level l's nodes are
+                // entries base .. of the ancestors; lane t finds node t, and
+                // lane l keeps level l's fields.
+                const int leaves = nA0 * nB0;
+                int total = 0, above = 0, my_l = 1, my_base = 0, l_base = 0, l_count = leaves;
+#pragma unroll 1
+                for (int l = 1; l <= g.H; l++) {
+                    const int here = ((bmax >> l) - (bmin >> l) + 1) * ((amax >> l) - (amin >> l) + 1);
+                    if (lane >= total) {
+                        my_l = l;
+                        my_base = total;
+                    }
+                    if (lane == l) {
+                        l_base = total;
+                        l_count = here;
+                    }
+                    if (l == g.H) above = total;  // nodes of levels 1 .. H - 1
+                    total += here;
                 }
-            }
-            const uint64_t used0 = __ballot(use0);
-            const uint32_t key0 = same && lane < cap0 ? ckey[0][lane] : CKEY_EMPTY;
-            const uint32_t key1 = same && lane < cap1 ? ckey[1][lane] : CKEY_EMPTY;
-            bool keep = false;
-            if (key0 != CKEY_EMPTY) {
-                const int b = (int)((key0 >> 14) & 0x3FFFu) - bmin, a = (int)(key0 & 0x3FFFu) - amin;
-                keep = ok && b >= 0 && b < nB0 && a >= 0 && a < nA0 && ((used0 >> (b * nA0 + a)) & 1ull);
-                if (keep) nodemap[0][b * nA0 + a] = (int8_t)lane;
-            }
-            const uint64_t free0 = ~__ballot(keep) & (cap0 >= 64 ? ~0ull : ((1ull << cap0) - 1ull));
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            int ent0 = nodemap[0][lane];
-            const bool new0 = use0 && ent0 < 0;
-            const uint64_t newm0 = __ballot(new0);
-            const int nnew0 = __popcll(newm0);
-            ok = ok && nnew0 <= __popcll(free0) && (!C420 || nnew0 * 2 * cnpix <= BSV / 3);
-            if (!ok) break;
-            // the k-th new leaf view takes the k-th free entry
-            if ((free0 >> lane) & 1ull) inv[0][__popcll(free0 & ((1ull << lane) - 1ull))] = (uint8_t)lane;
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            if (new0) ent0 = inv[0][__popcll(newm0 & ((1ull << lane) - 1ull))];
-            // levels 1..H: ancestors of the new leaf views.  A node (B, A) of
-            // level l covers leaf rows [B << l, (B + 1) << l) and columns
-            // [A << l, (A + 1) << l); it is needed when one of the new leaf
-            // views lies there.
-            const int kl = key1 != CKEY_EMPTY ? (int)(key1 >> 28) : 0;
-            bool kneed = false;
-            if (kl >= 1 && kl <= g.H) {
-                const int B = (int)((key1 >> 14) & 0x3FFFu), A = (int)(key1 & 0x3FFFu);
-                if (B >= (bmin >> kl) && B <= (bmax >> kl) && A >= (amin >> kl) && A <= (amax >> kl)) {
-                    const int rb0 = max(B << kl, bmin) - bmin, rb1 = min(((B + 1) << kl) - 1, bmax) - bmin;
-                    const int ra0 = max(A << kl, amin) - amin, ra1 = min(((A + 1) << kl) - 1, amax) - amin;
-                    for (int r = rb0; r <= rb1 && !kneed; r++)
-                        kneed = ((newm0 >> (r * nA0 + ra0)) & ((2ull << (ra1 - ra0)) - 1ull)) != 0ull;
-                    const int nA = (amax >> kl) - (amin >> kl) + 1;
-                    const int el = (B - (bmin >> kl)) * nA + (A - (amin >> kl));
-                    kneed = kneed && el < LMAX;
-                    if (kneed) nodemap[kl][el] = (int8_t)lane;
+                nd = per_desc * (leaves + above);
+                ns = 3 * total;
+                ok = leaves <= cap0 && total <= cap1 && nd <= BD && ns <= SLOT_MAX && (!C420 || leaves * 2 * cnpix <= BSV / 3);
+                if (!ok) break;
+                const int lv = min(lane, leaves - 1), q0 = lf_div_small(lv, nA0);
+                nodemap[0][lv] = (int8_t)lv;
+                nodelist[0][lv] = (uint16_t)(lv | (lv << 8));
+                ckey[0][lane] = lane < leaves ? lf_node_key(0, bmin + q0, amin + lane - q0 * nA0) : CKEY_EMPTY;
+                uint32_t key = CKEY_EMPTY;
+                if (lane < total) {  // total <= cap1 <= 64
+                    const int A0 = amin >> my_l, nA = (amax >> my_l) - A0 + 1, e = lane - my_base;
+                    const int qb = lf_div_small(e, nA);
+                    nodemap[my_l][e] = (int8_t)lane;
+                    nodelist[my_l][e] = (uint16_t)(e | (lane << 8));
+                    key = lf_node_key(my_l, (bmin >> my_l) + qb, A0 + e - qb * nA);
                 }
-            }
-            const uint64_t keep1 = __ballot(kneed);
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            int nd = per_desc * nnew0;
-            int cnt[LF_MAX_LEVELS + 1];
-            cnt[0] = nnew0;
-            const uint64_t free1 = ~keep1 & (cap1 >= 64 ? ~0ull : ((1ull << cap1) - 1ull));
-            ok = ok && nd <= BD;
-            if (!ok) break;
-            // Levels 1..H at once: the level rectangles laid end to end (level
-            // 1 first), node t of the concatenation in lane t % 64 of pass t / 64.
-            // Their total stays below 128: level l holds at most
-            // (nB0 / 2^l + 1)(nA0 / 2^l + 1) nodes and nA0 nB0 <= 64.
-            int off[LF_MAX_LEVELS + 2];
-            int total = 0;
-#pragma unroll
-            for (int l = 1; l <= LF_MAX_LEVELS + 1; l++) {
-                off[l] = total;
-                if (l <= g.H) {
-                    const int nBl = (bmax >> l) - (bmin >> l) + 1, nAl = (amax >> l) - (amin >> l) + 1;
-                    if (nBl * nAl > LMAX) ok = 0;
-                    total += nBl * nAl;
+                ckey[1][lane] = key;
+                if (lane <= g.H) {
+                    gp.B0[lane] = bmin >> lane;
+                    gp.A0[lane] = amin >> lane;
+                    gp.nA[lane] = (amax >> lane) - (amin >> lane) + 1;
+                    gp.nnew[lane] = l_count;
+                    if (lane >= 1) gp.sbase[lane] = 3 * l_base;
+                    if (lane < g.H) gp.dbase[lane] = lane == 0 ? 0 : per_desc * (leaves + l_base);
                 }
-            }
-            ok = ok && total <= 128;
-            if (!ok) break;
-            bool newp[2];
-            int lvp[2], idxp[2];
-            uint64_t nmp[2];
+            } else {
+                // node maps start empty; cache entries that a node of this group
+                // keeps write their index into the node's map (entry side), and
+                // each node then reads its map (node side; same wave, LDS in order)
 #pragma unroll
-            for (int pp = 0; pp < 2; pp++) {
-                const int t = 64 * pp + lane;
-                newp[pp] = false;
-                lvp[pp] = 1;
-                idxp[pp] = 0;
-                if (t < total) {
-                    // level of node t and its place in that level's rectangle
-                    int l = 1, base = 0;
-#pragma unroll
-                    for (int k = 2; k <= LF_MAX_LEVELS; k++)
-                        if (k <= g.H && t >= off[k]) {
-                            l = k;
-                            base = off[k];
-                        }
-                    const int B0 = bmin >> l, A0 = amin >> l, nA = (amax >> l) - A0 + 1;
-                    const int e = t - base;
-                    const int qb = lf_div_small(e, nA), B = B0 + qb, A = A0 + e - qb * nA;
-                    // A node (B, A) of level l covers leaf rows [B << l, (B + 1) << l)
-                    // and columns [A << l, (A + 1) << l); it is needed when one of the
-                    // new leaf views lies there.
-                    const int rb0 = max(B << l, bmin) - bmin, rb1 = min(((B + 1) << l) - 1, bmax) - bmin;
-                    const int ra0 = max(A << l, amin) - amin, ra1 = min(((A + 1) << l) - 1, amax) - amin;
-                    bool need = false;
-                    for (int r = rb0; r <= rb1 && !need; r++)
-                        need = ((newm0 >> (r * nA0 + ra0)) & ((2ull << (ra1 - ra0)) - 1ull)) != 0ull;
-                    newp[pp] = need && nodemap[l][e] < 0;
-                    lvp[pp] = l;
-                    idxp[pp] = e;
-                }
-                nmp[pp] = __ballot(newp[pp]);
-            }
-            // new nodes per level: the set bits of each level's segment
-            int nnew1 = 0;
-#pragma unroll
-            for (int l = 1; l <= LF_MAX_LEVELS; l++) {
-                cnt[l] = 0;
-                if (l > g.H) continue;
-#pragma unroll
-                for (int pp = 0; pp < 2; pp++) {
-                    const int lo = min(max(off[l] - 64 * pp, 0), 64), hi = min(max(off[l + 1] - 64 * pp, 0), 64);
-                    const uint64_t m = (hi >= 64 ? ~0ull : ((1ull << hi) - 1ull)) & ~(lo >= 64 ? ~0ull : ((1ull << lo) - 1ull));
-                    cnt[l] += __popcll(nmp[pp] & m);
-                }
-                nnew1 += cnt[l];
-                if (l < g.H) nd += per_desc * cnt[l];
-            }
-            const int ns = 3 * nnew1;
-            ok = ok && nnew1 <= __popcll(free1) && nd <= BD && ns <= SLOT_MAX;
-            if (!ok) break;
-            if ((free1 >> lane) & 1ull) inv[1][__popcll(free1 & ((1ull << lane) - 1ull))] = (uint8_t)lane;
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            {
-                // commit: entries of the new nodes, node maps, new-node lists, keys
-                if (!same && lane < CMAX) {
-                    ckey[0][lane] = CKEY_EMPTY;
-                    ckey[1][lane] = CKEY_EMPTY;
-                }
-                if (new0) {
-                    nodemap[0][lane] = (int8_t)ent0;
-                    const int k = __popcll(newm0 & ((1ull << lane) - 1ull));
-                    nodelist[0][k] = (uint16_t)(lane | (ent0 << 8));
-                    const int qb = lf_div_small(lane, nA0);
-                    ckey[0][ent0] = lf_node_key(0, bmin + qb, amin + lane - qb * nA0);
-                }
-                // a new node's entry is the r-th free one, r its rank among the
-                // new nodes of all levels (level order); its list index is r less
-                // the new nodes of the levels before
-#pragma unroll
-                for (int pp = 0; pp < 2; pp++) {
-                    if (newp[pp]) {
-                        const int r = (pp ? __popcll(nmp[0]) : 0) + __popcll(nmp[pp] & ((1ull << lane) - 1ull));
-                        const int e = inv[1][r];
-                        int before = 0;
-#pragma unroll
-                        for (int k = 1; k < LF_MAX_LEVELS; k++)
-                            if (k < lvp[pp]) before += cnt[k];
-                        const int l = lvp[pp], nA = (amax >> l) - (amin >> l) + 1;
-                        const int qb = lf_div_small(idxp[pp], nA);
-                        nodelist[l][r - before] = (uint16_t)(idxp[pp] | (e << 8));
-                        ckey[1][e] = lf_node_key(l, (bmin >> l) + qb, (amin >> l) + idxp[pp] - qb * nA);
-                        nodemap[lvp[pp]][idxp[pp]] = (int8_t)e;
+                for (int l = 0; l <= LF_MAX_LEVELS; l++)
+                    if (l <= g.H) nodemap[l][lane] = -1;
+                // level 0: leaf views some ray of the group reaches
+                bool use0 = false;
+                if (ok && lane < nA0 * nB0) {
+                    const int qb = lf_div_small(lane, nA0), b = bmin + qb, a = amin + lane - qb * nA0;
+                    for (int q = f; q < f + n && !use0; q++) {
+                        const uint32_t q0 = fbox[q][0], q1 = fbox[q][1];
+                        use0 = (int)(q0 >> 16) <= b && (int)(q1 >> 16) >= b && (int)(q0 & 0xFFFFu) <= a &&
+                               (int)(q1 & 0xFFFFu) >= a;
                     }
                 }
-            }
-            if (lane <= g.H) {
-                // per-level fields, lane l for level l: the level's rectangle,
-                // its new nodes, and the first staged slot (levels 1..H) and
-                // descriptor (levels 0..H-1) of its new nodes
-                const int l = lane;
-                int cl = 0, s3 = 0, d3 = 0;
-#pragma unroll
-                for (int k = 0; k <= LF_MAX_LEVELS; k++) {
-                    if (k == l) cl = cnt[k];
-                    if (k >= 1 && k < l) s3 += 3 * cnt[k];
-                    if (k < l) d3 += per_desc * cnt[k];
+                const uint64_t used0 = __ballot(use0);
+                const uint32_t key0 = same && lane < cap0 ? ckey[0][lane] : CKEY_EMPTY;
+                const uint32_t key1 = same && lane < cap1 ? ckey[1][lane] : CKEY_EMPTY;
+                bool keep = false;
+                if (key0 != CKEY_EMPTY) {
+                    const int b = (int)((key0 >> 14) & 0x3FFFu) - bmin, a = (int)(key0 & 0x3FFFu) - amin;
+                    keep = ok && b >= 0 && b < nB0 && a >= 0 && a < nA0 && ((used0 >> (b * nA0 + a)) & 1ull);
+                    if (keep) nodemap[0][b * nA0 + a] = (int8_t)lane;
                 }
-                gp.B0[l] = bmin >> l;
-                gp.A0[l] = amin >> l;
-                gp.nA[l] = (amax >> l) - (amin >> l) + 1;
-                gp.nnew[l] = cl;
-                if (l >= 1) gp.sbase[l] = s3;
-                if (l < g.H) gp.dbase[l] = d3;
+                const uint64_t free0 = ~__ballot(keep) & (cap0 >= 64 ? ~0ull : ((1ull << cap0) - 1ull));
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                int ent0 = nodemap[0][lane];
+                const bool new0 = use0 && ent0 < 0;
+                const uint64_t newm0 = __ballot(new0);
+                const int nnew0 = __popcll(newm0);
+                ok = ok && nnew0 <= __popcll(free0) && (!C420 || nnew0 * 2 * cnpix <= BSV / 3);
+                if (!ok) break;
+                // the k-th new leaf view takes the k-th free entry
+                if ((free0 >> lane) & 1ull) inv[0][__popcll(free0 & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if (new0) ent0 = inv[0][__popcll(newm0 & ((1ull << lane) - 1ull))];
+                // levels 1..H: ancestors of the new leaf views.  A node (B, A) of
+                // level l covers leaf rows [B << l, (B + 1) << l) and columns
+                // [A << l, (A + 1) << l); it is needed when one of the new leaf
+                // views lies there.
+                const int kl = key1 != CKEY_EMPTY ? (int)(key1 >> 28) : 0;
+                bool kneed = false;
+                if (kl >= 1 && kl <= g.H) {
+                    const int B = (int)((key1 >> 14) & 0x3FFFu), A = (int)(key1 & 0x3FFFu);
+                    if (B >= (bmin >> kl) && B <= (bmax >> kl) && A >= (amin >> kl) && A <= (amax >> kl)) {
+                        const int rb0 = max(B << kl, bmin) - bmin, rb1 = min(((B + 1) << kl) - 1, bmax) - bmin;
+                        const int ra0 = max(A << kl, amin) - amin, ra1 = min(((A + 1) << kl) - 1, amax) - amin;
+                        for (int r = rb0; r <= rb1 && !kneed; r++)
+                            kneed = ((newm0 >> (r * nA0 + ra0)) & ((2ull << (ra1 - ra0)) - 1ull)) != 0ull;
+                        const int nA = (amax >> kl) - (amin >> kl) + 1;
+                        const int el = (B - (bmin >> kl)) * nA + (A - (amin >> kl));
+                        kneed = kneed && el < LMAX;
+                        if (kneed) nodemap[kl][el] = (int8_t)lane;
+                    }
+                }
+                const uint64_t keep1 = __ballot(kneed);
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                nd = per_desc * nnew0;
+                int cnt[LF_MAX_LEVELS + 1];
+                cnt[0] = nnew0;
+                const uint64_t free1 = ~keep1 & (cap1 >= 64 ? ~0ull : ((1ull << cap1) - 1ull));
+                ok = ok && nd <= BD;
+                if (!ok) break;
+                // Levels 1..H at once: the level rectangles laid end to end (level
+                // 1 first), node t of the concatenation in lane t % 64 of pass t / 64.
+                // Their total stays below 128: level l holds at most
+                // (nB0 / 2^l + 1)(nA0 / 2^l + 1) nodes and nA0 nB0 <= 64.
+                int off[LF_MAX_LEVELS + 2];
+                int total = 0;
+#pragma unroll
+                for (int l = 1; l <= LF_MAX_LEVELS + 1; l++) {
+                    off[l] = total;
+                    if (l <= g.H) {
+                        const int nBl = (bmax >> l) - (bmin >> l) + 1, nAl = (amax >> l) - (amin >> l) + 1;
+                        if (nBl * nAl > LMAX) ok = 0;
+                        total += nBl * nAl;
+                    }
+                }
+                ok = ok && total <= 128;
+                if (!ok) break;
+                bool newp[2];
+                int lvp[2], idxp[2];
+                uint64_t nmp[2];
+#pragma unroll
+                for (int pp = 0; pp < 2; pp++) {
+                    const int t = 64 * pp + lane;
+                    newp[pp] = false;
+                    lvp[pp] = 1;
+                    idxp[pp] = 0;
+                    if (t < total) {
+                        // level of node t and its place in that level's rectangle
+                        int l = 1, base = 0;
+#pragma unroll
+                        for (int k = 2; k <= LF_MAX_LEVELS; k++)
+                            if (k <= g.H && t >= off[k]) {
+                                l = k;
+                                base = off[k];
+                            }
+                        const int B0 = bmin >> l, A0 = amin >> l, nA = (amax >> l) - A0 + 1;
+                        const int e = t - base;
+                        const int qb = lf_div_small(e, nA), B = B0 + qb, A = A0 + e - qb * nA;
+                        // A node (B, A) of level l covers leaf rows [B << l, (B + 1) << l)
+                        // and columns [A << l, (A + 1) << l); it is needed when one of the
+                        // new leaf views lies there.
+                        const int rb0 = max(B << l, bmin) - bmin, rb1 = min(((B + 1) << l) - 1, bmax) - bmin;
+                        const int ra0 = max(A << l, amin) - amin, ra1 = min(((A + 1) << l) - 1, amax) - amin;
+                        bool need = false;
+                        for (int r = rb0; r <= rb1 && !need; r++)
+                            need = ((newm0 >> (r * nA0 + ra0)) & ((2ull << (ra1 - ra0)) - 1ull)) != 0ull;
+                        newp[pp] = need && nodemap[l][e] < 0;
+                        lvp[pp] = l;
+                        idxp[pp] = e;
+                    }
+                    nmp[pp] = __ballot(newp[pp]);
+                }
+                // new nodes per level: the set bits of each level's segment
+                int nnew1 = 0;
+#pragma unroll
+                for (int l = 1; l <= LF_MAX_LEVELS; l++) {
+                    cnt[l] = 0;
+                    if (l > g.H) continue;
+#pragma unroll
+                    for (int pp = 0; pp < 2; pp++) {
+                        const int lo = min(max(off[l] - 64 * pp, 0), 64), hi = min(max(off[l + 1] - 64 * pp, 0), 64);
+                        const uint64_t m = (hi >= 64 ? ~0ull : ((1ull << hi) - 1ull)) & ~(lo >= 64 ? ~0ull : ((1ull << lo) - 1ull));
+                        cnt[l] += __popcll(nmp[pp] & m);
+                    }
+                    nnew1 += cnt[l];
+                    if (l < g.H) nd += per_desc * cnt[l];
+                }
+                ns = 3 * nnew1;
+                ok = ok && nnew1 <= __popcll(free1) && nd <= BD && ns <= SLOT_MAX;
+                if (!ok) break;
+                if ((free1 >> lane) & 1ull) inv[1][__popcll(free1 & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                {
+                    // commit: entries of the new nodes, node maps, new-node lists, keys
+                    if (!same && lane < CMAX) {
+                        ckey[0][lane] = CKEY_EMPTY;
+                        ckey[1][lane] = CKEY_EMPTY;
+                    }
+                    if (new0) {
+                        nodemap[0][lane] = (int8_t)ent0;
+                        const int k = __popcll(newm0 & ((1ull << lane) - 1ull));
+                        nodelist[0][k] = (uint16_t)(lane | (ent0 << 8));
+                        const int qb = lf_div_small(lane, nA0);
+                        ckey[0][ent0] = lf_node_key(0, bmin + qb, amin + lane - qb * nA0);
+                    }
+                    // a new node's entry is the r-th free one, r its rank among the
+                    // new nodes of all levels (level order); its list index is r less
+                    // the new nodes of the levels before
+#pragma unroll
+                    for (int pp = 0; pp < 2; pp++) {
+                        if (newp[pp]) {
+                            const int r = (pp ? __popcll(nmp[0]) : 0) + __popcll(nmp[pp] & ((1ull << lane) - 1ull));
+                            const int e = inv[1][r];
+                            int before = 0;
+#pragma unroll
+                            for (int k = 1; k < LF_MAX_LEVELS; k++)
+                                if (k < lvp[pp]) before += cnt[k];
+                            const int l = lvp[pp], nA = (amax >> l) - (amin >> l) + 1;
+                            const int qb = lf_div_small(idxp[pp], nA);
+                            nodelist[l][r - before] = (uint16_t)(idxp[pp] | (e << 8));
+                            ckey[1][e] = lf_node_key(l, (bmin >> l) + qb, (amin >> l) + idxp[pp] - qb * nA);
+                            nodemap[lvp[pp]][idxp[pp]] = (int8_t)e;
+                        }
+                    }
+                }
+                if (lane <= g.H) {
+                    // per-level fields, lane l for level l: the level's rectangle,
+                    // its new nodes, and the first staged slot (levels 1..H) and
+                    // descriptor (levels 0..H-1) of its new nodes
+                    const int l = lane;
+                    int cl = 0, s3 = 0, d3 = 0;
+#pragma unroll
+                    for (int k = 0; k <= LF_MAX_LEVELS; k++) {
+                        if (k == l) cl = cnt[k];
+                        if (k >= 1 && k < l) s3 += 3 * cnt[k];
+                        if (k < l) d3 += per_desc * cnt[k];
+                    }
+                    gp.B0[l] = bmin >> l;
+                    gp.A0[l] = amin >> l;
+                    gp.nA[l] = (amax >> l) - (amin >> l) + 1;
+                    gp.nnew[l] = cl;
+                    if (l >= 1) gp.sbase[l] = s3;
+                    if (l < g.H) gp.dbase[l] = d3;
+                }
             }
             if (lane == 0) {
                 gp.ok = ok;
