@@ -175,6 +175,20 @@ lf_status lf_decode_pixels(const lf_handle* h, const int32_t* d_coords, int64_t 
 lf_status lf_decode_pixels_lod(const lf_handle* h, int32_t level, const int32_t* d_coords, int64_t n,
                                uint8_t* d_rgb, void* stream);
 
+/* Device scratch lf_decode_pixels_ordered takes for n requests (16 bytes a
+ * request and small tables), or 0 where ordering does not pay: few requests,
+ * small fields, and handles other than dense 4:4:4 ones.  Host-only. */
+lf_status lf_decode_workspace(const lf_handle* h, int64_t n, int64_t* bytes);
+
+/* lf_decode_pixels_lod with scratch in which many scattered requests are
+ * first ordered by the pixels they fall on, so that requests sharing cache
+ * lines run together; requests found in order already are left so.  Same
+ * results.  d_workspace: caller-owned, 256-byte aligned, at least
+ * lf_decode_workspace bytes (ignored when that is 0); calls that overlap need
+ * one each.  Errors: as lf_decode_pixels_lod, LF_ENOMEM (workspace too small). */
+lf_status lf_decode_pixels_ordered(const lf_handle* h, int32_t level, const int32_t* d_coords, int64_t n,
+                                   uint8_t* d_rgb, void* d_workspace, int64_t workspace_bytes, void* stream);
+
 /* ---------------------------------------------------------------------- */
 /* Novel-view rendering fused with decoding (Random Access for             */
 /* Interactive Rendering; two-plane interpolation of Light Field           */

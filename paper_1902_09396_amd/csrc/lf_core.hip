@@ -886,26 +886,6 @@ __device__ __forceinline__ void lf_count_clamps(unsigned long long* counter, boo
     if (m && __lane_id() == (unsigned)(__ffsll((long long)m) - 1)) atomicAdd(counter, (unsigned long long)__popcll(m));
 }
 
-template <int RES>
-__global__ void k_decode_pixels(LfGeom g, LfPtrs p, const int32_t* __restrict__ coords, int64_t n,
-                                uint8_t* __restrict__ rgb, unsigned long long* __restrict__ clamps)
-{
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    int4 q = reinterpret_cast<const int4*>(coords)[k];
-    int b = lf_clampi(q.x, 0, g.nb - 1), a = lf_clampi(q.y, 0, g.na - 1);
-    int y = lf_clampi(q.z, 0, g.h - 1), x = lf_clampi(q.w, 0, g.w - 1);
-    lf_count_clamps(clamps, b != q.x || a != q.y || y != q.z || x != q.w);
-    int Y = lf_decode_channel<RES>(g, p, 0, b, a, y, x);
-    int Co = lf_decode_channel<RES>(g, p, 1, b, a, y, x);
-    int Cg = lf_decode_channel<RES>(g, p, 2, b, a, y, x);
-    int r, gg, bl;
-    lf_ycocg_to_rgb(Y, Co, Cg, r, gg, bl);
-    rgb[3 * k] = (uint8_t)r;
-    rgb[3 * k + 1] = (uint8_t)gg;
-    rgb[3 * k + 2] = (uint8_t)bl;
-}
-
 // 4:2:0 streams: luma from the luma geometry, Co and Cg up-sampled from the
 // half-size chroma geometry; lod > 0 reads level-lod node images (B, A).
 __global__ void k_decode_pixels420(LfGeom g, LfPtrs p, LfGeom gc, LfPtrs pc, int lod,
@@ -939,25 +919,8 @@ static lf_status lf_launch_decode420(const lf_handle* h, int lod, const int32_t*
     return lf_check_launch("decode_pixels");
 }
 
-extern "C" lf_status lf_decode_pixels(const lf_handle* h, const int32_t* d_coords, int64_t n, uint8_t* d_rgb,
-                                      void* stream)
-{
-    if (!h || n < 0) return lf_fail(LF_EINVAL, "bad argument");
-    if (n == 0) return LF_OK;
-    if (!d_coords || !d_rgb) return lf_fail(LF_EINVAL, "null buffer");
-    if (((uintptr_t)d_coords) & 15) return lf_fail(LF_EINVAL, "coords must be 16-byte aligned");
-    if (h->L.chroma420) return lf_launch_decode420(h, 0, d_coords, n, d_rgb, stream);
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 0x7FFFFFFF) return lf_fail(LF_EINVAL, "too many samples");
-    hipLaunchKernelGGL(h->L.sparse == LF_RES_CSR     ? k_decode_pixels<LF_RES_CSR>
-                       : h->L.sparse == LF_RES_TILES ? k_decode_pixels<LF_RES_TILES>
-                                                     : k_decode_pixels<LF_RES_DENSE>,
-                       dim3((unsigned)blocks), dim3(256),
-                       0, (hipStream_t)stream, h->L.g, h->p, d_coords, n, d_rgb, lf_clamp_counter(h));
-    return lf_check_launch("decode_pixels");
-}
-
-// Progressive decode: samples of the level-`lod` node images.
+// Samples of the level-`lod` node images (lod = 0: the leaf views): one thread
+// per sample.
 template <int RES>
 __global__ void k_decode_nodes(LfGeom g, LfPtrs p, int lod, const int32_t* __restrict__ coords, int64_t n,
                                uint8_t* __restrict__ rgb, unsigned long long* __restrict__ clamps)
@@ -978,22 +941,60 @@ __global__ void k_decode_nodes(LfGeom g, LfPtrs p, int lod, const int32_t* __res
     rgb[3 * k + 2] = (uint8_t)bl;
 }
 
-extern "C" lf_status lf_decode_pixels_lod(const lf_handle* h, int32_t level, const int32_t* d_coords, int64_t n,
-                                          uint8_t* d_rgb, void* stream)
+static lf_status lf_decode(const lf_handle* h, int32_t level, const int32_t* d_coords, int64_t n, uint8_t* d_rgb,
+                           void* d_scratch, void* stream)
 {
     if (!h || n < 0 || level < 0 || level > h->L.g.H) return lf_fail(LF_EINVAL, "bad argument");
     if (n == 0) return LF_OK;
     if (!d_coords || !d_rgb) return lf_fail(LF_EINVAL, "null buffer");
     if (((uintptr_t)d_coords) & 15) return lf_fail(LF_EINVAL, "coords must be 16-byte aligned");
     if (h->L.chroma420) return lf_launch_decode420(h, level, d_coords, n, d_rgb, stream);
+    // Without scratch, many requests keep the one-thread walk: scattered, they
+    // are bound by cache lines, and its table and vectors are half the bytes
+    // of the descriptors (2^18 scattered requests 125 us against 172, 98,304 75
+    // against 61).
+    if (!h->L.sparse && (d_scratch || n < 114688))
+        return lf_launch_decode_dense(h, level, d_coords, n, d_rgb, lf_clamp_counter(h), d_scratch, (hipStream_t)stream);
     const int64_t blocks = (n + 255) / 256;
     if (blocks > 0x7FFFFFFF) return lf_fail(LF_EINVAL, "too many samples");
     hipLaunchKernelGGL(h->L.sparse == LF_RES_CSR     ? k_decode_nodes<LF_RES_CSR>
                        : h->L.sparse == LF_RES_TILES ? k_decode_nodes<LF_RES_TILES>
                                                      : k_decode_nodes<LF_RES_DENSE>,
-                       dim3((unsigned)blocks), dim3(256), 0,
-                       (hipStream_t)stream, h->L.g, h->p, (int)level, d_coords, n, d_rgb, lf_clamp_counter(h));
-    return lf_check_launch("decode_pixels_lod");
+                       dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, h->L.g, h->p, (int)level, d_coords, n,
+                       d_rgb, lf_clamp_counter(h));
+    return lf_check_launch("decode_pixels");
+}
+
+extern "C" lf_status lf_decode_pixels(const lf_handle* h, const int32_t* d_coords, int64_t n, uint8_t* d_rgb,
+                                      void* stream)
+{
+    return lf_decode(h, 0, d_coords, n, d_rgb, nullptr, stream);
+}
+
+extern "C" lf_status lf_decode_pixels_lod(const lf_handle* h, int32_t level, const int32_t* d_coords, int64_t n,
+                                          uint8_t* d_rgb, void* stream)
+{
+    return lf_decode(h, level, d_coords, n, d_rgb, nullptr, stream);
+}
+
+extern "C" lf_status lf_decode_workspace(const lf_handle* h, int64_t n, int64_t* bytes)
+{
+    if (!h || n < 0 || !bytes) return lf_fail(LF_EINVAL, "bad argument");
+    *bytes = lf_decode_scratch(h, n);
+    return LF_OK;
+}
+
+extern "C" lf_status lf_decode_pixels_ordered(const lf_handle* h, int32_t level, const int32_t* d_coords, int64_t n,
+                                              uint8_t* d_rgb, void* d_workspace, int64_t workspace_bytes, void* stream)
+{
+    if (!h || n < 0) return lf_fail(LF_EINVAL, "bad argument");
+    const int64_t need = lf_decode_scratch(h, n);
+    if (need > 0) {
+        if (!d_workspace || (((uintptr_t)d_workspace) & 255)) return lf_fail(LF_EINVAL, "workspace must be 256-byte aligned");
+        if (workspace_bytes < need)
+            return lf_fail(LF_ENOMEM, "workspace of %lld bytes, %lld needed", (long long)workspace_bytes, (long long)need);
+    }
+    return lf_decode(h, level, d_coords, n, d_rgb, need > 0 ? d_workspace : nullptr, stream);
 }
 
 // ---------------------------------------------------------------------------

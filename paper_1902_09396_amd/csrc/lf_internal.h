@@ -61,6 +61,12 @@ lf_status lf_parse(const uint8_t* s, size_t n, LfLayout* L);
 // work must not throw.
 void lf_parallel(int parts, const std::function<void(int)>& work);
 
+// Samples of level `lod` from a dense handle (lf_decode.hip); d_scratch: null,
+// or lf_decode_scratch(h, n) > 0 bytes in which the requests are ordered first.
+int64_t lf_decode_scratch(const lf_handle* h, int64_t n);
+lf_status lf_launch_decode_dense(const lf_handle* h, int lod, const int32_t* d_coords, int64_t n, uint8_t* d_rgb,
+                                 unsigned long long* clamps, void* d_scratch, hipStream_t s);
+
 // Phase-shifted motion search (lf_search.hip) on device planes, for the
 // device encoder: checks the sizes, enqueues k_mc_search on `stream`.
 lf_status lf_search_launch(const int16_t* pred, const int16_t* ref, int64_t n_pred, int64_t n_ref, int w, int h,

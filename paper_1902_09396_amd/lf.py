@@ -53,6 +53,8 @@ SIGNATURES = {
     "lf_render_views_per_ray": (C.c_int, [_P, _P, _I32, _I32, _I32, _P, _P]),
     "lf_decode_pixels_lod": (C.c_int, [_P, _I32, _P, _I64, _P, _P]),
     "lf_render_views_lod": (C.c_int, [_P, _I32, _P, _I32, _I32, _I32, _P, _P]),
+    "lf_decode_workspace": (C.c_int, [_P, _I64, _P]),
+    "lf_decode_pixels_ordered": (C.c_int, [_P, _I32, _P, _I64, _P, _P, _I64, _P]),
     "lf_get_render_config": (C.c_int, [_I32, _I32, _I32, _P, _P]),
     "lf_ray_coords": (C.c_int, [_P, _I32, _I32, _I32, _P, _P]),
     "lf_footprint_bytes": (C.c_int, [_P, _P, _I32, _I32, _I32, _P, _P]),
@@ -164,17 +166,18 @@ class LightField:
 
     def decode_pixels(self, coords: torch.Tensor) -> torch.Tensor:
         """coords: int32 [n, 4] (b, a, y, x) on the device -> uint8 [n, 3] RGB."""
-        coords = _dev(coords, torch.int32, "coords").reshape(-1, 4)
-        out = torch.empty((coords.shape[0], 3), dtype=torch.uint8, device=coords.device)
-        check(lib().lf_decode_pixels(self._h, _ptr(coords), coords.shape[0], _ptr(out), _stream()))
-        return out
+        return self.decode_nodes(0, coords)
 
     def decode_nodes(self, level: int, coords: torch.Tensor) -> torch.Tensor:
         """Progressive decode: coords int32 [n, 4] (B, A, y, x) of level-`level`
         nodes on the device -> uint8 [n, 3] RGB of their reconstructed images."""
         coords = _dev(coords, torch.int32, "coords").reshape(-1, 4)
-        out = torch.empty((coords.shape[0], 3), dtype=torch.uint8, device=coords.device)
-        check(lib().lf_decode_pixels_lod(self._h, level, _ptr(coords), coords.shape[0], _ptr(out), _stream()))
+        n = coords.shape[0]
+        out = torch.empty((n, 3), dtype=torch.uint8, device=coords.device)
+        need = C.c_int64()
+        check(lib().lf_decode_workspace(self._h, n, C.byref(need)))
+        ws = torch.empty(need.value, dtype=torch.uint8, device=coords.device)
+        check(lib().lf_decode_pixels_ordered(self._h, level, _ptr(coords), n, _ptr(out), _ptr(ws), ws.numel(), _stream()))
         return out
 
     def render_views_lod(self, level: int, cams: torch.Tensor, width: int, height: int) -> torch.Tensor:
