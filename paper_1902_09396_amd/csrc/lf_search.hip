@@ -18,7 +18,9 @@
 //    instruction; the -1 phase compares the packed negation of the biased
 //    block, 32768 - p = -(p + 32768) mod 2^16, with the same reference pair,
 //    since |p + r| = |(32768 - p) - (r + 32768)|;
-//  - quarter-pel candidates: v_dot2_u32_u16 applies two bilinear weights per
+//  - quarter-pel candidates, values of 12 bits (every block of 8-bit content
+//    unless the coding errors of several levels add up): refine_narrow below;
+//  - quarter-pel candidates of wider values: v_dot2_u32_u16 applies two bilinear weights per
 //    instruction to biased taps; the weights sum to 16, so the bias passes
 //    through the rounding shift exactly.  Two lanes share a candidate (eight
 //    rows each), and each lane carries the lower tap row to the next row.
@@ -90,6 +92,94 @@ __host__ __device__ inline int search_lds_dwords(int bs, int win)
     return 2 * D * window_dwords(D) + bs * bs;
 }
 
+// Quarter-pel refinement where the window and the block lie in [-2048, 2047]:
+// 16 v + 8 fits 16 bits, so two pixels are interpolated per packed 16-bit
+// instruction, and the bias of the staged values drops out mod 2^16 (4 * 32768
+// = 0).  The integer best is a whole pixel, so a phase's 7x7 neighbourhood has
+// seven columns qx of which each interpolates a window row once, and the seven
+// rows qy lie between window rows y - 1, y (three quarters) and y, y + 1: one
+// row pair's three inner quarters serve block row y at +1..3 quarters and
+// block row y + 1 at -3..-1.  Lane: (row part, phase, qx); the rows' sums meet
+// in two exchanges.  Bound by instruction issue: about 9 packed and 7 SAD
+// instructions per dword of a row pair for seven candidates, where the dot
+// products of the general refinement take 8 a candidate: the searches of
+// 17x17x512x512 (16x16 blocks, W = 8, 875,000 of them) took 7.07 ms with those
+// and take 5.59.
+template <int BS>
+__device__ __forceinline__ void refine_narrow(const uint32_t* E, const uint32_t* O, const uint32_t* Pb, const uint32_t* Pn, int Dj,
+                                              int win, int lane, uint64_t& bestp, uint64_t& bestm)
+{
+    constexpr int HB = BS / 2, PARTS = BS >= 4 ? 4 : 2, HR = BS / PARTS;
+    const int lim = 4 * win, part = lane >> 4, s = (lane >> 3) & 1, j = lane & 7;
+    const int cx = key_mx(s ? bestm : bestp), cy = key_my(s ? bestm : bestp), qx = cx + j - 3;
+    const bool in = j < 7 && qx >= -lim && qx <= lim;
+    uint32_t acc[7] = {0, 0, 0, 0, 0, 0, 0};
+    if (in && part < PARTS) {
+        const int fx = qx & 3, ox = win + (qx >> 2), oy = win + (cy >> 2) + part * HR;
+        // columns ox + 2i, ox + 2i + 1 and one further, from the copies of their parity
+        const uint32_t* A = ((ox & 1) ? O : E) + (ox >> 1);
+        const uint32_t* B = ((ox & 1) ? E : O) + ((ox + 1) >> 1);
+        const uint32_t* P = (s ? Pn : Pb) + part * HR * HB;
+        const u16x2 wl = (u16x2)((unsigned short)(4 - fx)), wr = (u16x2)((unsigned short)fx);
+        const int above = max(oy - 1, 0) * Dj;  // row -1 of the window: of candidates beyond +-4W only, not ranked
+        auto pk = [](uint32_t v) { return __builtin_bit_cast(u16x2, v); };
+        auto u32 = [](u16x2 v) { return __builtin_bit_cast(uint32_t, v); };
+#pragma unroll 2
+        for (int i = 0; i < HB; i++) {
+            u16x2 h0 = pk(A[above + i]) * wl + pk(B[above + i]) * wr;
+            uint32_t p0 = 0;
+#pragma unroll
+            for (int r = 0; r <= HR; r++) {  // window rows r - 1 and r of this part
+                const int at = (oy + r) * Dj + i;
+                const u16x2 h1 = pk(A[at]) * wl + pk(B[at]) * wr, d = h1 - h0;
+                const u16x2 v0 = h0 * (unsigned short)4 + (unsigned short)0x8008;  // 16 v + 8, biased
+                const u16x2 v1 = v0 + d, v2 = v1 + d, v3 = v2 + d;
+                const uint32_t b1 = u32(v1 >> (unsigned short)4), b2 = u32(v2 >> (unsigned short)4),
+                               b3 = u32(v3 >> (unsigned short)4);
+                if (r > 0) {
+                    acc[3] = sad2(p0, u32(v0 >> (unsigned short)4), acc[3]);
+                    acc[4] = sad2(p0, b1, acc[4]);
+                    acc[5] = sad2(p0, b2, acc[5]);
+                    acc[6] = sad2(p0, b3, acc[6]);
+                }
+                if (r < HR) {
+                    p0 = u32(pk(P[r * HB + i]) - (unsigned short)30720);  // bias 32768 -> 2048
+                    acc[0] = sad2(p0, b1, acc[0]);
+                    acc[1] = sad2(p0, b2, acc[1]);
+                    acc[2] = sad2(p0, b3, acc[2]);
+                }
+                h0 = h1;
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 7; t++) {
+        acc[t] += __shfl_xor(acc[t], 16, 64);
+        acc[t] += __shfl_xor(acc[t], 32, 64);
+    }
+    // each of the four lanes of a column ranks rows part and part + 4
+    uint64_t key = ~0ull;
+    if (in) {
+        const uint32_t c0 = part < 2 ? (part ? acc[1] : acc[0]) : (part == 2 ? acc[2] : acc[3]);
+        const uint32_t c1 = part ? (part == 1 ? acc[5] : acc[6]) : acc[4];
+        const int q0 = cy + part - 3, q1 = q0 + 4;
+        if (q0 >= -lim && q0 <= lim) key = mv_key(c0, qx, q0);
+        if (part < 3 && q1 <= lim) {
+            const uint64_t k1 = mv_key(c1, qx, q1);
+            key = k1 < key ? k1 : key;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        if (o == 8) continue;  // lanes 8 apart hold the two phases
+        const uint64_t t = __shfl_xor(key, o, 64);
+        key = t < key ? t : key;
+    }
+    const uint64_t k0 = __shfl(key, 0, 64), k1 = __shfl(key, 8, 64);
+    bestp = k0 < bestp ? k0 : bestp;
+    bestm = k1 < bestm ? k1 : bestm;
+}
+
 template <int BS>
 __global__ void __launch_bounds__(64, BS >= 32 ? 3 : 8) k_mc_search(const int16_t* __restrict__ pred, const int16_t* __restrict__ ref,
                                                   int64_t n_pred, int64_t n_ref, int w, int h, int win, int subpel,
@@ -122,12 +212,14 @@ __global__ void __launch_bounds__(64, BS >= 32 ? 3 : 8) k_mc_search(const int16_
     const int16_t* R = ref + ri * plane;
 
     bool bad = false;
+    uint32_t wide = 0;  // bits above the 12 of [-2048, 2047]
     for (int e = lane; e < D * Dj; e += 64) {
         const int ry = e / Dj, j = e - ry * Dj;
         const int16_t* row = R + (int64_t)min(max(by0 - win + ry, 0), h - 1) * w;
         const int c0 = bx0 - win + 2 * j;
         const int v0 = row[min(max(c0, 0), w - 1)], v1 = row[min(max(c0 + 1, 0), w - 1)],
                   v2 = row[min(max(c0 + 2, 0), w - 1)];
+        wide |= (uint32_t)(v0 + 2048) | (uint32_t)(v1 + 2048) | (uint32_t)(v2 + 2048);
         E[e] = (uint32_t)(v0 + 32768) | ((uint32_t)(v1 + 32768) << 16);
         O[e] = (uint32_t)(v1 + 32768) | ((uint32_t)(v2 + 32768) << 16);
     }
@@ -135,11 +227,13 @@ __global__ void __launch_bounds__(64, BS >= 32 ? 3 : 8) k_mc_search(const int16_
         const int y = e / HB, i = e - y * HB;
         const int16_t* px = P + (int64_t)(by0 + y) * w + bx0 + 2 * i;
         const int p0 = px[0], p1 = px[1];
+        wide |= (uint32_t)(p0 + 2048) | (uint32_t)(p1 + 2048);
         bad |= p0 == -32768 || p1 == -32768;
         Pb[e] = (uint32_t)(p0 + 32768) | ((uint32_t)(p1 + 32768) << 16);
         Pn[e] = (uint32_t)(32768 - p0) | ((uint32_t)(32768 - p1) << 16);
     }
     bad = __ballot(bad) != 0;
+    const bool narrow = __ballot(wide > 4095u) == 0;
     __syncthreads();
 
     // ---- integer displacements, both phases in one pass ----
@@ -199,7 +293,9 @@ __global__ void __launch_bounds__(64, BS >= 32 ? 3 : 8) k_mc_search(const int16_
     // ---- quarter-pel refinement: 48 offsets around each phase's best ----
     // 96 candidates x 2 row halves = 3 rounds of the wave; lanes 2m and 2m + 1
     // take the two halves of one candidate
-    if (subpel && win > 0) {
+    if (subpel && win > 0 && narrow) {
+        refine_narrow<BS>(E, O, Pb, Pn, Dj, win, lane, bestp, bestm);
+    } else if (subpel && win > 0) {
         const int lim = 4 * win;
         const int cxp = key_mx(bestp), cyp = key_my(bestp), cxm = key_mx(bestm), cym = key_my(bestm);
         uint64_t kq0 = ~0ull, kq1 = ~0ull;
