@@ -175,6 +175,9 @@ lf_status lf_decode_pixels(const lf_handle* h, const int32_t* d_coords, int64_t 
 lf_status lf_decode_pixels_lod(const lf_handle* h, int32_t level, const int32_t* d_coords, int64_t n,
                                uint8_t* d_rgb, void* stream);
 
+/* Fewest requests that lf_decode_pixels_ordered orders. */
+#define LF_DECODE_ORDER_MIN 114688
+
 /* Device scratch lf_decode_pixels_ordered takes for n requests (16 bytes a
  * request and small tables), or 0 where ordering does not pay: few requests,
  * small fields, and handles other than dense 4:4:4 ones.  Host-only. */
@@ -295,7 +298,7 @@ lf_status lf_backward_workspace(const lf_handle* h, int32_t n_views, int32_t wid
 
 /* Adjoint of lf_render_relaxed: given d_grad_out = dL/d(out) (same layout
  * as the output), writes dL/d(residual) and dL/d(shift) (overwritten, not
- * accumulated).  Deterministic and free of atomics: the forward's ray
+ * accumulated).  Deterministic (no float atomics): the forward's ray
  * geometry is recomputed, never stored.  d_workspace: caller-owned,
  * 256-byte aligned, >= lf_backward_workspace bytes.  Errors: LF_EINVAL,
  * LF_ENOMEM (workspace too small), LF_EDEVICE. */

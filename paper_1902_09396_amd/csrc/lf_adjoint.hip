@@ -12,7 +12,8 @@
 // blend of the renderer.  Within a block every pixel has the same bilinear
 // fraction (floor(x + dx) = x + floor(dx)), which both directions use.
 //
-// Adjoint, deterministic and without atomics:
+// Adjoint, deterministic (the sort counts its digits by integer atomics in
+// LDS; nothing else is atomic):
 //  1. views whose homographies separate by axis get per-view tables of the
 //     columns and rows that reach each light-field column, row and view;
 //  2. if some view does not separate, its rays emit one record per
@@ -816,7 +817,7 @@ __global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_scatter(const int* __rest
     if (!all_general && !*general) return;
     constexpr int W = AD_SORT_T / 64;
     __shared__ uint32_t base[256];          // next output place of each digit
-    __shared__ uint32_t cnt[W][256];        // this round's digit counts per wave
+    __shared__ uint32_t cnt[W][256];        // this step's digit counts per wave
     __shared__ uint32_t wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // digit d: records of it in the workgroups before this one, and in all

@@ -953,7 +953,7 @@ static lf_status lf_decode(const lf_handle* h, int32_t level, const int32_t* d_c
     // are bound by cache lines, and its table and vectors are half the bytes
     // of the descriptors (2^18 scattered requests 125 us against 172, 98,304 75
     // against 61).
-    if (!h->L.sparse && (d_scratch || n < 114688))
+    if (!h->L.sparse && (d_scratch || n < LF_DECODE_ORDER_MIN))
         return lf_launch_decode_dense(h, level, d_coords, n, d_rgb, lf_clamp_counter(h), d_scratch, (hipStream_t)stream);
     const int64_t blocks = (n + 255) / 256;
     if (blocks > 0x7FFFFFFF) return lf_fail(LF_EINVAL, "too many samples");

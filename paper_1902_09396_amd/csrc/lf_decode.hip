@@ -17,7 +17,6 @@
 #define DEC_CHUNK 4096      // requests per workgroup of the ordering passes
 #define DEC_L 2             // levels read together (more cost registers that hold waves: 66 us against 59 for 2^20 consecutive samples at 4)
 #define DEC_T 1024          // threads of it
-#define DEC_MIN 114688      // fewest requests worth ordering
 #define DEC_MAX (1 << 26)   // most requests ordered in one call (1 GiB of scratch)
 
 // Words 2 e, 2 e + 1 of int16 elements from an even element on: 4-byte aligned.
@@ -305,7 +304,7 @@ static int64_t order_layout(const LfGeom& g, int64_t n, uint8_t* base, DecOrder*
 int64_t lf_decode_scratch(const lf_handle* h, int64_t n)
 {
     const LfGeom& g = h->L.g;
-    if (h->L.sparse || h->L.chroma420 || n < DEC_MIN || n > DEC_MAX) return 0;
+    if (h->L.sparse || h->L.chroma420 || n < LF_DECODE_ORDER_MIN || n > DEC_MAX) return 0;
     if ((int64_t)g.na * g.nb * g.w * g.h < (1 << 22)) return 0;
     DecOrder o;
     return order_layout(g, n, nullptr, &o);

@@ -19,6 +19,7 @@ LIB_PATH = os.path.join(_PKG, "libhmlfc.so")
 LF_OK, LF_EINVAL, LF_ENOMEM, LF_EFORMAT, LF_EDEVICE = 0, -1, -2, -3, -4
 LF_LOAD_SPARSE_REFS = 1
 LF_LOAD_CSR_REFS = 2
+LF_DECODE_ORDER_MIN = 114688
 _NAMES = {LF_EINVAL: "LF_EINVAL", LF_ENOMEM: "LF_ENOMEM", LF_EFORMAT: "LF_EFORMAT", LF_EDEVICE: "LF_EDEVICE"}
 
 
@@ -119,7 +120,7 @@ class LightField:
     def __init__(self, stream, device=None, sparse_refs: bool = False, csr_refs: bool = False):
         """sparse_refs=True keeps only the significant reference blocks resident,
         csr_refs=True only the nonzero reference pixels as compressed sparse rows
-        (same results; rendered one thread per ray)."""
+        (same results; the latter is rendered one thread per ray)."""
         require_gpu()
         self.device = torch.device(device) if device is not None else torch.device("cuda", torch.cuda.current_device())
         host = np.ascontiguousarray(np.frombuffer(bytes(stream), np.uint8) if isinstance(stream, (bytes, bytearray))
@@ -166,17 +167,31 @@ class LightField:
 
     def decode_pixels(self, coords: torch.Tensor) -> torch.Tensor:
         """coords: int32 [n, 4] (b, a, y, x) on the device -> uint8 [n, 3] RGB."""
-        return self.decode_nodes(0, coords)
+        coords = _dev(coords, torch.int32, "coords").reshape(-1, 4)
+        out = torch.empty((coords.shape[0], 3), dtype=torch.uint8, device=coords.device)
+        if coords.shape[0] >= LF_DECODE_ORDER_MIN:
+            return self._decode_ordered(0, coords, out)
+        check(lib().lf_decode_pixels(self._h, _ptr(coords), coords.shape[0], _ptr(out), _stream()))
+        return out
 
     def decode_nodes(self, level: int, coords: torch.Tensor) -> torch.Tensor:
         """Progressive decode: coords int32 [n, 4] (B, A, y, x) of level-`level`
         nodes on the device -> uint8 [n, 3] RGB of their reconstructed images."""
         coords = _dev(coords, torch.int32, "coords").reshape(-1, 4)
-        n = coords.shape[0]
-        out = torch.empty((n, 3), dtype=torch.uint8, device=coords.device)
-        need = C.c_int64()
+        out = torch.empty((coords.shape[0], 3), dtype=torch.uint8, device=coords.device)
+        if coords.shape[0] >= LF_DECODE_ORDER_MIN:
+            return self._decode_ordered(level, coords, out)
+        check(lib().lf_decode_pixels_lod(self._h, level, _ptr(coords), coords.shape[0], _ptr(out), _stream()))
+        return out
+
+    def _decode_ordered(self, level, coords, out):
+        n, need = coords.shape[0], C.c_int64()
         check(lib().lf_decode_workspace(self._h, n, C.byref(need)))
-        ws = torch.empty(need.value, dtype=torch.uint8, device=coords.device)
+        try:
+            ws = torch.empty(need.value, dtype=torch.uint8, device=coords.device)
+        except torch.OutOfMemoryError:  # the unordered decode needs no scratch
+            check(lib().lf_decode_pixels_lod(self._h, level, _ptr(coords), n, _ptr(out), _stream()))
+            return out
         check(lib().lf_decode_pixels_ordered(self._h, level, _ptr(coords), n, _ptr(out), _ptr(ws), ws.numel(), _stream()))
         return out
 
