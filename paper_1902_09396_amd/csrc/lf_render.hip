@@ -330,11 +330,17 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
 // taken when the load has settled the range of every level and of the motion
 // vectors (nothing is refused there).  The root
 // level is sixteen plain reads per ray: no tiles.  CSR handles search a row
-// per tap: no tiles.
+// per tap: no tiles.  Nor at the level below the root from level 2 on, or
+// where its nodes are a single row or column: a ray's four views are mostly
+// one node there, often a reference, which is less than a tile's plan (25
+// views of 271x211 over 2x1 nodes 29 us per ray, 65 through the tiles; 2 of
+// 986x429 over 3x2 nodes from one point 56 and 82; a path through 3x3 nodes 31
+// and 27).  4:2:0 chroma is dearer per ray (342 us against 39).
 static bool lf_tiles_apply(const lf_handle* h, int level)
 {
     const LfLayout& L = h->L;
     if (L.g.bs < 4 || level >= L.g.H || L.sparse == LF_RES_CSR) return false;
+    if (level > 0 && level + 1 == L.g.H && !L.chroma420 && (level > 1 || L.g.na_l[level] == 1 || L.g.nb_l[level] == 1)) return false;
     if (L.sparse || L.chroma420) return L.packed_levels != 0;
     return level == 0 || L.packed_levels;
 }
