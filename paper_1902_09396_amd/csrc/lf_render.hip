@@ -119,27 +119,36 @@ __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGe
 }
 
 // Per-ray rendering of the (view, tile) pairs the batched kernel marked.
-// Workgroup b owns pairs [b * per_wg, (b + 1) * per_wg): it checks up to NT
-// of them at once (one per thread), compacts the marked ones, and renders
-// them one tile at a time, so a launch whose views are mostly marked (tiles
-// far minified) still spreads them over the whole grid.
+// Workgroup b checks pairs b, b + G, b + 2 G, ... of a grid of G, up to NT of
+// them at once (one per thread), compacts the marked ones and renders them one
+// tile at a time.  G is a prime near the number of CUs (one workgroup is
+// resident on each), so that marked rows, columns or views of tiles spread
+// over all of them, and a launch that marks nothing costs few waves.  A ray is
+// three threads in different waves, one per channel of its 16 samples: the
+// chain of dependent loads of a channel bounds the pass, and marked tiles are
+// often too few to fill the chip.  The channels meet in LDS and each thread
+// blends one colour.  3 views of 157x750, far minified, 16x16 blocks: 558 ->
+// 437 us for the call; 11 of 253x1032 2.37 -> 0.38 ms; 2 of 80x144 in 4:2:0
+// 0.92 -> 0.44 ms (one thread a ray, a contiguous range a workgroup before).
+// 37 views of 340x202 at 4x4 blocks, enough marked tiles to fill the chip,
+// take 4% more: two thirds of the waves fit.
 template <bool C420, int RES>
-__global__ void __launch_bounds__(NT) k_render_fallback(LfGeom g, LfPtrs p, LfGeom gc, LfPtrs pc,
-                                                        const float* __restrict__ cams, int nv, int wo, int ho,
-                                                        int tiles_x, int tiles_y, int per_wg, float* __restrict__ out,
-                                                        int lod)
+__global__ void __launch_bounds__(3 * NT) k_render_fallback(LfGeom g, LfPtrs p, LfGeom gc, LfPtrs pc,
+                                                            const float* __restrict__ cams, int nv, int wo, int ho,
+                                                            int tiles_x, int tiles_y, float* __restrict__ out,
+                                                            int lod)
 {
     __shared__ int marked[NT];
     __shared__ int wcount[NT / 64];
+    __shared__ int sample[3][16][NT];
     const int64_t n_pairs = (int64_t)nv * tiles_x * tiles_y;
     const int64_t npix = (int64_t)wo * ho;
-    const int64_t begin = (int64_t)blockIdx.x * per_wg;
-    const int64_t end = min(begin + per_wg, n_pairs);
-    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int64_t base = begin; base < end; base += NT) {
-        const int64_t pr = base + threadIdx.x;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int c = wid / (NT / 64), t = (int)threadIdx.x - c * NT;
+    for (int64_t base = blockIdx.x; base < n_pairs; base += (int64_t)NT * gridDim.x) {
+        const int64_t pr = base + (int64_t)threadIdx.x * gridDim.x;
         int mine = 0;
-        if (pr < end) {
+        if (c == 0 && pr < n_pairs) {
             const int v = (int)(pr / ((int64_t)tiles_x * tiles_y));
             const int tt = (int)(pr - (int64_t)v * tiles_x * tiles_y);
             const int tyi = tt / tiles_x, txi = tt - tyi * tiles_x;
@@ -147,7 +156,7 @@ __global__ void __launch_bounds__(NT) k_render_fallback(LfGeom g, LfPtrs p, LfGe
         }
         // compact the marked pairs in thread order
         const uint64_t bal = __ballot(mine);
-        if (lane == 0) wcount[wid] = __popcll(bal);
+        if (c == 0 && lane == 0) wcount[wid] = __popcll(bal);
         __syncthreads();
         int off = 0, total = 0;
         for (int w = 0; w < NT / 64; w++) {
@@ -157,22 +166,45 @@ __global__ void __launch_bounds__(NT) k_render_fallback(LfGeom g, LfPtrs p, LfGe
         if (mine) marked[off + __popcll(bal & ((1ull << lane) - 1ull))] = (int)threadIdx.x;
         __syncthreads();
         for (int k = 0; k < total; k++) {
-            const int64_t q = base + marked[k];
+            const int64_t q = base + (int64_t)marked[k] * gridDim.x;
             const int v = (int)(q / ((int64_t)tiles_x * tiles_y));
             const int tt = (int)(q - (int64_t)v * tiles_x * tiles_y);
             const int tyi = tt / tiles_x, txi = tt - tyi * tiles_x;
-            const int i = txi * TW + (int)threadIdx.x % TW, j = tyi * TH + (int)threadIdx.x / TW;
-            if (i < wo && j < ho) {
-                float o[3];
-                if (C420)
-                    lf_render_one420(g, p, gc, pc, cams + 18 * v, i, j, o, lod);
-                else
-                    lf_render_one<RES>(g, p, cams + 18 * v, i, j, o, lod);
+            const int i = txi * TW + t % TW, j = tyi * TH + t / TW;
+            const bool in = i < wo && j < ho;
+            Ray r;
+            if (in) {
+                r = lf_ray_setup(g, cams + 18 * v, i, j);
+                if (C420) {
+#pragma unroll 1
+                    for (int m = 0; m < 16; m++) {
+                        const int b = (m & 8) ? r.b1 : r.b0, a = (m & 4) ? r.a1 : r.a0;
+                        const int y = (m & 2) ? r.y1 : r.y0, x = (m & 1) ? r.x1 : r.x0;
+                        sample[c][m][t] = c == 0 ? lf_decode_channel(g, p, 0, b, a, y, x, lod)
+                                                 : lf_chroma_up(gc, pc, c - 1, b, a, y, x, lod);
+                    }
+                } else {
+                    int acc[16];
+                    lf_ray_channel<RES>(g, p, r, c, lod, acc);
 #pragma unroll
-                for (int c = 0; c < 3; c++) out[((int64_t)v * 3 + c) * npix + (int64_t)j * wo + i] = o[c];
+                    for (int m = 0; m < 16; m++) sample[c][m][t] = acc[m];
+                }
             }
+            __syncthreads();
+            if (in) {
+                const BlendW w = lf_blend_weights(r);
+                float sm[16];
+#pragma unroll
+                for (int m = 0; m < 16; m++) {
+                    int rgb[3];
+                    lf_ycocg_to_rgb(sample[0][m][t], sample[1][m][t], sample[2][m][t], rgb[0], rgb[1], rgb[2]);
+                    sm[m] = (float)(c == 0 ? rgb[0] : (c == 1 ? rgb[1] : rgb[2]));
+                }
+                out[((int64_t)v * 3 + c) * npix + (int64_t)j * wo + i] = lf_blend16(sm, w);
+            }
+            __syncthreads();  // the next tile rewrites the samples; marked[] and wcount[] are rewritten by the next round
         }
-        __syncthreads();  // marked[] and wcount[] are rewritten by the next round
+        __syncthreads();
     }
 }
 
@@ -311,15 +343,17 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
     const LfGeom gl = cut ? lf_cut_geometry(h->L.g, lod) : h->L.g, gcl = cut && c420 ? lf_cut_geometry(gc, lod) : gc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), lds, s, gl, h->p, gcl, pc, d_cams, nv, wo, ho, tx, ty,
                        chunk, fpg, n_full, sp, d_out, LodGrid{h->L.g.na, h->L.g.nb, lod});
-    // marked pairs: workgroups each check a contiguous range.  With 16x16
-    // blocks few tiles exceed the staging budget and 1024 workgroups keep the
-    // pass short; smaller blocks mark many more tiles, which need the wider grid.
+    // G of the per-ray pass: 256 workgroups more that find nothing cost 1.3 us,
+    // so one on each CU does where few tiles are marked (16x16 blocks: one
+    // 512x512 view 44.6 us, 46.0 with 509) and one look per thread covers the
+    // pairs.  Smaller blocks mark more tiles, whose costs differ: two views of
+    // 74x928, all marked, 131 us with 509, 200 with 251; 32 of 211x117 711 with
+    // 1021, 838 with 509.
     const int64_t pairs = (int64_t)tx * ty * nv;
-    const int64_t fb_grid = std::min<int64_t>(pairs, h->L.g.bs >= 16 ? 1024 : 8192);
-    const int64_t per_wg = (pairs + fb_grid - 1) / fb_grid;
-    if (per_wg > 0x7FFFFFFF) return lf_fail(LF_EINVAL, "too many tiles");
+    const int most = h->L.g.bs >= 16 ? (pairs <= 251 * NT ? 251 : 509) : (pairs <= 2048 ? 509 : 1021);
     const auto rest = c420 ? k_render_fallback<true, D> : (tiles ? k_render_fallback<false, T> : k_render_fallback<false, D>);
-    hipLaunchKernelGGL(rest, dim3((unsigned)fb_grid), dim3(NT), 0, s, h->L.g, h->p, gc, pc, d_cams, nv, wo, ho, tx, ty, (int)per_wg, d_out, lod);
+    hipLaunchKernelGGL(rest, dim3((unsigned)std::min<int64_t>(pairs, most)), dim3(3 * NT), 0, s, h->L.g, h->p, gc, pc,
+                       d_cams, nv, wo, ho, tx, ty, d_out, lod);
     return lf_check_launch("render_batch");
 }
 
