@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGe
 }
 
 // Per-ray rendering of the (view, tile) pairs the batched kernel marked.
-// Workgroup b checks pairs b, b + G, b + 2 G, ... of a grid of G, up to NT of
+// Workgroup b checks pairs b, b + G, b + 2 G, ... of a grid of G, up to 3 NT of
 // them at once (one per thread), compacts the marked ones and renders them one
 // tile at a time.  G is a prime near the number of CUs (one workgroup is
 // resident on each), so that marked rows, columns or views of tiles spread
@@ -138,17 +138,17 @@ __global__ void __launch_bounds__(3 * NT) k_render_fallback(LfGeom g, LfPtrs p, 
                                                             int tiles_x, int tiles_y, float* __restrict__ out,
                                                             int lod)
 {
-    __shared__ int marked[NT];
-    __shared__ int wcount[NT / 64];
+    __shared__ int marked[3 * NT];
+    __shared__ int wcount[3 * NT / 64];
     __shared__ int sample[3][16][NT];
     const int64_t n_pairs = (int64_t)nv * tiles_x * tiles_y;
     const int64_t npix = (int64_t)wo * ho;
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int c = wid / (NT / 64), t = (int)threadIdx.x - c * NT;
-    for (int64_t base = blockIdx.x; base < n_pairs; base += (int64_t)NT * gridDim.x) {
+    for (int64_t base = blockIdx.x; base < n_pairs; base += (int64_t)3 * NT * gridDim.x) {
         const int64_t pr = base + (int64_t)threadIdx.x * gridDim.x;
         int mine = 0;
-        if (c == 0 && pr < n_pairs) {
+        if (pr < n_pairs) {
             const int v = (int)(pr / ((int64_t)tiles_x * tiles_y));
             const int tt = (int)(pr - (int64_t)v * tiles_x * tiles_y);
             const int tyi = tt / tiles_x, txi = tt - tyi * tiles_x;
@@ -156,10 +156,10 @@ __global__ void __launch_bounds__(3 * NT) k_render_fallback(LfGeom g, LfPtrs p, 
         }
         // compact the marked pairs in thread order
         const uint64_t bal = __ballot(mine);
-        if (c == 0 && lane == 0) wcount[wid] = __popcll(bal);
+        if (lane == 0) wcount[wid] = __popcll(bal);
         __syncthreads();
         int off = 0, total = 0;
-        for (int w = 0; w < NT / 64; w++) {
+        for (int w = 0; w < 3 * NT / 64; w++) {
             off += w < wid ? wcount[w] : 0;
             total += wcount[w];
         }
@@ -345,12 +345,11 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
                        chunk, fpg, n_full, sp, d_out, LodGrid{h->L.g.na, h->L.g.nb, lod});
     // G of the per-ray pass: 256 workgroups more that find nothing cost 1.3 us,
     // so one on each CU does where few tiles are marked (16x16 blocks: one
-    // 512x512 view 44.6 us, 46.0 with 509) and one look per thread covers the
-    // pairs.  Smaller blocks mark more tiles, whose costs differ: two views of
+    // 512x512 view 44.6 us, 46.0 with 509).  Smaller blocks mark more tiles, whose costs differ: two views of
     // 74x928, all marked, 131 us with 509, 200 with 251; 32 of 211x117 711 with
     // 1021, 838 with 509.
     const int64_t pairs = (int64_t)tx * ty * nv;
-    const int most = h->L.g.bs >= 16 ? (pairs <= 251 * NT ? 251 : 509) : (pairs <= 2048 ? 509 : 1021);
+    const int most = h->L.g.bs >= 16 ? 251 : (pairs <= 2048 ? 509 : 1021);
     const auto rest = c420 ? k_render_fallback<true, D> : (tiles ? k_render_fallback<false, T> : k_render_fallback<false, D>);
     hipLaunchKernelGGL(rest, dim3((unsigned)std::min<int64_t>(pairs, most)), dim3(3 * NT), 0, s, h->L.g, h->p, gc, pc,
                        d_cams, nv, wo, ho, tx, ty, d_out, lod);
