@@ -1211,13 +1211,16 @@ struct AdTaps {
         const int xs = X - q.ix, ys = Y0 - q.iy - 1;
         const bool x0 = (unsigned)(xs - bx) < (unsigned)g.bs, x1 = (unsigned)(xs - 1 - bx) < (unsigned)g.bs;
         const int first = ys * g.w + xs;
+        // a row outside the block reads the plane's first two elements, unused;
+        // a plane of one element the one before it and its own
+        const int outside = g.w * g.h > 1 ? 0 : -1;
 #pragma unroll
         for (int t = 0; t < 5; t++) {
             const bool y = (unsigned)(ys + t - by) < (unsigned)g.bs;
             // both columns in one load: (xs - 1, xs), or (xs - 2, xs - 1) when
             // xs is past the block (a predictive plane is never the buffer's
             // first, so an element before it is still inside the buffer)
-            const int at = y && (x0 || x1) ? first + t * g.w - (x0 ? 1 : 2) : 0;
+            const int at = y && (x0 || x1) ? first + t * g.w - (x0 ? 1 : 2) : outside;
             const ad_f2 a = *reinterpret_cast<const ad_f2*>(gp + at);
             s0[t] = y && x0 ? a.y : 0.0f;
             s1[t] = y && x1 ? (x0 ? a.x : a.y) : 0.0f;
