@@ -53,6 +53,13 @@ __device__ __forceinline__ int lf_small_div(int n, int d)
 
 __device__ __forceinline__ float ad_lerp(float p, float q, float f) { return fmaf(f, q - p, p); }
 
+// Integer part of a shift component along an axis of n pixels, f its floor:
+// clamped to [-n - 1, n], which leaves every clamped tap where it was and
+// keeps pixel + shift + 1 an ordinary integer for every float (out of range,
+// the conversion and the sum are undefined, and the address made of them is
+// wild).
+__device__ __forceinline__ int ad_whole(float f, int n) { return (int)fminf(fmaxf(f, (float)(-n - 1)), (float)n); }
+
 // four (two) consecutive floats at any 4-byte aligned address, one load
 typedef float ad_f4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float ad_f2 __attribute__((ext_vector_type(2), aligned(4)));
@@ -166,7 +173,7 @@ __device__ __forceinline__ void ad_srv_quad(const LfGeom& g, const LfPtrs& p, co
     }
 #pragma unroll
     for (int k = 0; k < 4; k++) {
-        const int x0 = xs[k & 1] + (int)floorf(d[k].x), y0 = ys[k >> 1] + (int)floorf(d[k].y);
+        const int x0 = xs[k & 1] + ad_whole(floorf(d[k].x), g.w), y0 = ys[k >> 1] + ad_whole(floorf(d[k].y), g.h);
         const int q = max(min(lf_clampi(x0, 0, g.w - 1), g.w - 2), 0);
         ta[k] = *reinterpret_cast<const ad_f2*>(R + lf_clampi(y0, 0, g.h - 1) * g.w + q);
         tb[k] = *reinterpret_cast<const ad_f2*>(R + lf_clampi(y0 + 1, 0, g.h - 1) * g.w + q);
@@ -174,7 +181,7 @@ __device__ __forceinline__ void ad_srv_quad(const LfGeom& g, const LfPtrs& p, co
 #pragma unroll
     for (int k = 0; k < 4; k++) {
         const float fdx = floorf(d[k].x), fx = d[k].x - fdx, fy = d[k].y - floorf(d[k].y);
-        const int x0 = xs[k & 1] + (int)fdx;
+        const int x0 = xs[k & 1] + ad_whole(fdx, g.w);
         const int xa = lf_clampi(x0, 0, g.w - 1), xb = lf_clampi(x0 + 1, 0, g.w - 1), q = max(min(xa, g.w - 2), 0);
         const float t = ad_lerp(ad_lerp(xa > q ? ta[k].y : ta[k].x, xb > q ? ta[k].y : ta[k].x, fx),
                                 ad_lerp(xa > q ? tb[k].y : tb[k].x, xb > q ? tb[k].y : tb[k].x, fx), fy);
@@ -254,7 +261,7 @@ __device__ __forceinline__ void ad_srv_nodes(const LfGeom& g, const LfPtrs& p, c
 #pragma unroll
             for (int c = 0; c < 3; c++) {
                 const float* R = level + ((int64_t)c * g.n_nodes + (B[n] & ~1) * g.na_l[l] + (A[n] & ~1)) * plane;
-                const int x0 = x + (int)floorf(d[n][c].x), y0 = y + (int)floorf(d[n][c].y);
+                const int x0 = x + ad_whole(floorf(d[n][c].x), g.w), y0 = y + ad_whole(floorf(d[n][c].y), g.h);
                 const int q = max(min(lf_clampi(x0, 0, g.w - 1), g.w - 2), 0);
                 ta[n][c] = ad_ld<ad_f2>(R, (uint32_t)(lf_clampi(y0, 0, g.h - 1) * g.w + q));
                 tb[n][c] = ad_ld<ad_f2>(R, (uint32_t)(lf_clampi(y0 + 1, 0, g.h - 1) * g.w + q));
@@ -265,7 +272,7 @@ __device__ __forceinline__ void ad_srv_nodes(const LfGeom& g, const LfPtrs& p, c
 #pragma unroll
             for (int c = 0; c < 3; c++) {
                 const float fdx = floorf(d[n][c].x), fx = d[n][c].x - fdx, fy = d[n][c].y - floorf(d[n][c].y);
-                const int x0 = x + (int)fdx;
+                const int x0 = x + ad_whole(fdx, g.w);
                 const int xa = lf_clampi(x0, 0, g.w - 1), xb = lf_clampi(x0 + 1, 0, g.w - 1), q = max(min(xa, g.w - 2), 0);
                 const float v = ad_lerp(ad_lerp(xa > q ? ta[n][c].y : ta[n][c].x, xb > q ? ta[n][c].y : ta[n][c].x, fx),
                                         ad_lerp(xa > q ? tb[n][c].y : tb[n][c].x, xb > q ? tb[n][c].y : tb[n][c].x, fx), fy);
@@ -1113,9 +1120,8 @@ __device__ __forceinline__ void ad_tap_range(int X, int n, int fd, int o, int k0
     }
 }
 
-// Phase and split shift of one predictive block: integer part (clamped to
-// [-w-1, w] / [-h-1, h], which leaves every clamped tap where it was) and
-// fractional part.
+// Phase and split shift of one predictive block: integer part (clamped, see
+// ad_whole) and fractional part.
 struct AdRec {
     int sg, ix, iy;
     float fx, fy;
@@ -1139,8 +1145,8 @@ __device__ __forceinline__ AdRec ad_split(const LfGeom& g, int sg, float2 s)
         const float fdx = floorf(s.x), fdy = floorf(s.y);
         d.fx = s.x - fdx;
         d.fy = s.y - fdy;
-        d.ix = (int)fminf(fmaxf(fdx, (float)(-g.w - 1)), (float)g.w);
-        d.iy = (int)fminf(fmaxf(fdy, (float)(-g.h - 1)), (float)g.h);
+        d.ix = ad_whole(fdx, g.w);
+        d.iy = ad_whole(fdy, g.h);
     }
     return d;
 }

@@ -59,3 +59,43 @@ def test_planes_of_one_pixel_wide_blocks(na, nb, levels, w, h):
     got = field.render_backward(res, sh, torch.from_numpy(cams).cuda(), 6, 5, torch.from_numpy(g).cuda())
     ref = o.relaxed_grad(res.cpu().numpy(), sh.cpu().numpy(), cams, 6, 5, g.astype(np.float64))
     assert _close(got[0], ref[0], 1e-6) and _close(got[1], ref[1], 1e-5)
+
+
+def _shifted(torch, wo, ho, levels=1, w=48, h=32):
+    """A 2x2 field whose views are all rendered, its parameters with small
+    shifts, and the record of block `blk` of channel 0, view (b, a)."""
+    from paper_1902_09396_amd import lf
+
+    stream = _noise(2, 2, w, h, levels, 8, seed=5)
+    field = lf.LightField(stream)
+    res, sh = field.export_params()
+    st = lfscene.cameras.full_frame_st(w, h, wo, ho)
+    cams = np.stack([lfscene.cameras.fixed_uv_camera(u, v, st) for u, v in ((0.4, 0.3), (0.7, 0.6))])
+    nblk = (w // 8) * (h // 8)
+    code = {(0, 1): 0, (1, 0): 1, (1, 1): 2}
+    return oracle.OracleLF(stream), field, res, sh, torch.from_numpy(cams).cuda(), lambda b, a, blk: code[b, a] * nblk + blk
+
+
+@pytest.mark.parametrize("wo,ho", [(48, 32), (8, 8)])  # tiles staged in LDS, and ray by ray
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("value", [1e6, -1e6, 3e9, -3e9, 3e38, np.inf, -np.inf, np.nan])
+def test_forward_of_any_shift(value, axis, wo, ho):
+    """Shifts past every integer and no number at all: finite ones read the
+    border sample, the others make their block's own samples NaN and no more."""
+    import torch
+
+    _, field, res, sh, cams, rec = _shifted(torch, wo, ho)
+    changed, limit = sh.clone(), sh.clone()
+    for blk in (0, 5, 23):
+        for view in ((0, 1), (1, 0), (1, 1)):
+            changed[rec(*view, blk), axis] = value
+            limit[rec(*view, blk), axis] = 1000.0 if value > 0 else -1000.0
+    got = field.render_relaxed(res, changed, cams, wo, ho)
+    ref = field.render_relaxed(res, limit, cams, wo, ho)
+    if np.isfinite(value):
+        assert torch.equal(got, ref)
+    else:
+        bad = torch.isnan(got)
+        assert bad.any() and torch.equal(got[~bad], ref[~bad])
+        same = field.render_relaxed(res, sh, cams, wo, ho)
+        assert torch.equal(same[~bad], got[~bad])  # rays that read no changed block
