@@ -583,7 +583,7 @@ static lf_status bwd_layout(const lf_handle* h, int nv, int wo, int ho, BwdLayou
     B->o_vout = take(B->n_recs * 4);
     B->o_hist = take(AD_SORT_WG * 256 * 4);
     B->o_start = take(B->n_samples * 4);
-    B->o_max = take(256);  // largest shift, then the flag "some view does not separate"
+    B->o_max = take(256);  // AdFlags
     B->o_parts = take(AD_MAX_PARTS * 4);
     B->o_rayf = take(B->n_recs / 4 * 16);  // one float4 per ray
     B->o_brec = take(h->L.n_rec * 16);     // one split shift per predictive block
@@ -1068,38 +1068,51 @@ __global__ void k_ad_tree(LfGeom g, int l, float* __restrict__ gres)
     }
 }
 
-// largest |shift| component: AD_MAX_PARTS workgroups write partial maxima,
-// then one workgroup reduces them (a maximum is exact in any order)
+// largest |shift| component, NaN left out: AD_MAX_PARTS workgroups write
+// partial maxima, negative (or -0) where a component is NaN, then one
+// workgroup reduces them (a maximum is exact in any order)
 __global__ void k_ad_maxshift(const float2* __restrict__ shift, int64_t n, float* __restrict__ out)
 {
     __shared__ float red[256];
     float m = 0.0f;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x)
-        m = fmaxf(m, fmaxf(fabsf(shift[t].x), fabsf(shift[t].y)));
+    bool nan = false;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+        const float2 s = shift[t];
+        m = fmaxf(m, fmaxf(fabsf(s.x), fabsf(s.y)));
+        nan |= s.x != s.x || s.y != s.y;
+    }
     red[threadIdx.x] = m;
-    __syncthreads();
+    nan = __syncthreads_or(nan);
     for (int s = 128; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) out[blockIdx.x] = nan ? -red[0] : red[0];
 }
 
-__global__ void k_ad_maxparts(const float* __restrict__ parts, int n, float* __restrict__ out)
+// The words at o_max of the workspace.
+struct AdFlags {
+    float maxshift;
+    int general;    // 1: some view does not separate (set by k_ad_axes)
+    int nan_shift;  // 1: some shift component is NaN
+};
+
+__global__ void k_ad_maxparts(const float* __restrict__ parts, int n, AdFlags* __restrict__ out)
 {
     __shared__ float red[256];
     float m = 0.0f;
-    for (int t = threadIdx.x; t < n; t += blockDim.x) m = fmaxf(m, parts[t]);
+    bool nan = false;
+    for (int t = threadIdx.x; t < n; t += blockDim.x) {
+        m = fmaxf(m, fabsf(parts[t]));
+        nan |= __float_as_int(parts[t]) < 0;
+    }
     red[threadIdx.x] = m;
-    __syncthreads();
+    nan = __syncthreads_or(nan);
     for (int s = 128; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        out[0] = red[0];
-        reinterpret_cast<int*>(out)[1] = 0;  // "some view does not separate", set by k_ad_axes
-    }
+    if (threadIdx.x == 0) *out = AdFlags{red[0], 0, nan};
 }
 
 // pixel range [lo, hi] of [k0, k1] whose tap (x + fd + o), clamped to [0, n-1], equals X
@@ -1293,7 +1306,7 @@ struct AdTaps {
 // 9x9 views of 256x256, three views: 0.288 -> 0.040 ms.  Four tiles per wave
 // in sequence: 0.55 and 0.059 ms (too few waves on the small field).
 __global__ void __launch_bounds__(256) k_ad_reference(LfGeom g, const int4* __restrict__ brec,
-                                                      const float* __restrict__ maxshift, float* gres)
+                                                      const AdFlags* __restrict__ flags, float* gres)
 {
     const int plane = g.w * g.h;  // at most 2^28
     const int tiles_x = (g.w + AD_TILE - 1) / AD_TILE, tiles_y = (g.h + AD_TILE - 1) / AD_TILE;
@@ -1306,7 +1319,7 @@ __global__ void __launch_bounds__(256) k_ad_reference(LfGeom g, const int4* __re
     const int T = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
     if (T >= n_tiles) return;  // uniform per wave
     const int lane = threadIdx.x & 63;
-    const int reach = __builtin_amdgcn_readfirstlane((int)ceilf(fminf(maxshift[0], (float)(g.w + g.h))) + 2);
+    const int reach = __builtin_amdgcn_readfirstlane((int)ceilf(fminf(flags->maxshift, (float)(g.w + g.h))) + 2);
     const int rp = T / per_plane, tt = T - rp * per_plane;
     const int c = rp / g.n_refs, r = rp - c * g.n_refs;
     int l = 0;
@@ -1324,9 +1337,10 @@ __global__ void __launch_bounds__(256) k_ad_reference(LfGeom g, const int4* __re
     const int ty0 = trow * AD_TILE, ty1 = min(ty0 + AD_TILE - 1, g.h - 1);
     const int cky0 = max(0, ty0 - reach) >> g.bsl, nky = min(g.h - 1, ty1 + reach) / g.bs - cky0 + 1;
     const int Y0 = ty0 + (lane >> 4) * 4;
-    // shifts too far for the sets of outside positions: a border pixel walks
-    // the source pixels of every tap clamped onto it instead
-    const bool far = reach > AD_FAR;
+    // shifts too far for the sets of outside positions, or NaN, which the
+    // reach leaves out: a border pixel walks the source pixels of every tap
+    // clamped onto it instead
+    const bool far = reach > AD_FAR || __builtin_amdgcn_readfirstlane(flags->nan_shift);
     const int nv = (reach + AD_TILE - 1) / AD_TILE;
     const int tx0 = (tt - trow * tiles_x) * AD_TILE, tx1 = min(tx0 + AD_TILE - 1, g.w - 1);
     const int ckx0 = max(0, tx0 - reach) >> g.bsl, nkx = (min(g.w - 1, tx1 + reach) >> g.bsl) - ckx0 + 1;
@@ -1590,13 +1604,13 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     if (((uintptr_t)d_workspace) & 255) return lf_fail(LF_EINVAL, "workspace must be 256-byte aligned");
     hipStream_t s = (hipStream_t)stream;
     uint8_t* W = (uint8_t*)d_workspace;
-    float* mxs = (float*)(W + Bl.o_max);
+    AdFlags* flags = (AdFlags*)(W + Bl.o_max);
     float* parts = (float*)(W + Bl.o_parts);
     hipLaunchKernelGGL(k_ad_maxshift, dim3(AD_MAX_PARTS), dim3(256), 0, s, (const float2*)d_shift, h->L.n_rec, parts);
-    hipLaunchKernelGGL(k_ad_maxparts, dim3(1), dim3(256), 0, s, parts, AD_MAX_PARTS, mxs);
+    hipLaunchKernelGGL(k_ad_maxparts, dim3(1), dim3(256), 0, s, parts, AD_MAX_PARTS, flags);
     AdAxes t;
     t.sep = (int*)(W + Bl.o_sep);
-    t.general = (int*)(W + Bl.o_max) + 1;
+    t.general = &flags->general;
     t.col = (float4*)(W + Bl.o_col);
     t.row = (float4*)(W + Bl.o_row);
     t.rx = (int2*)(W + Bl.o_rx);
@@ -1671,6 +1685,6 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     const int64_t n_tiles = 3 * (int64_t)g.n_refs * ((g.w + AD_TILE - 1) / AD_TILE) * ((g.h + AD_TILE - 1) / AD_TILE);
     if (h->L.n_rec > 0)  // without predictive blocks the references keep their own gradients
         hipLaunchKernelGGL(k_ad_reference, dim3((unsigned)((n_tiles + 31) / 32 * 8)), dim3(256), 0, s, g,
-                           (const int4*)brec, mxs, d_grad_residual);
+                           (const int4*)brec, flags, d_grad_residual);
     return lf_check_launch("render_backward");
 }

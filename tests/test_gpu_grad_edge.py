@@ -61,12 +61,12 @@ def test_planes_of_one_pixel_wide_blocks(na, nb, levels, w, h):
     assert _close(got[0], ref[0], 1e-6) and _close(got[1], ref[1], 1e-5)
 
 
-def _shifted(torch, wo, ho, levels=1, w=48, h=32):
+def _shifted(torch, wo, ho, seed=5, levels=1, w=48, h=32):
     """A 2x2 field whose views are all rendered, its parameters with small
     shifts, and the record of block `blk` of channel 0, view (b, a)."""
     from paper_1902_09396_amd import lf
 
-    stream = _noise(2, 2, w, h, levels, 8, seed=5)
+    stream = _noise(2, 2, w, h, levels, 8, seed)
     field = lf.LightField(stream)
     res, sh = field.export_params()
     st = lfscene.cameras.full_frame_st(w, h, wo, ho)
@@ -99,3 +99,28 @@ def test_forward_of_any_shift(value, axis, wo, ho):
         assert bad.any() and torch.equal(got[~bad], ref[~bad])
         same = field.render_relaxed(res, sh, cams, wo, ho)
         assert torch.equal(same[~bad], got[~bad])  # rays that read no changed block
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+def test_backward_of_a_nan_shift(axis):
+    """The taps of a NaN shift count as clamped to the first column (row), as
+    those of a shift far beyond it: NaN in the gradients of the reference's
+    pixels there and of the block's shift, and nowhere else."""
+    import torch
+
+    _, field, res, sh, cams, rec = _shifted(torch, 48, 32, seed=6)
+    g = torch.ones(2, 3, 32, 48, device="cuda")
+    far = sh.clone()
+    base = field.render_backward(res, sh, cams, 48, 32, g)
+    k = next(rec(*view, 0) for view in ((0, 1), (1, 0), (1, 1)) if base[1][rec(*view, 0)].any())  # a block with a phase
+    far[k, axis] = -1000.0
+    ref = field.render_backward(res, far, cams, 48, 32, g)
+    far[k, axis] = float("nan")
+    got = field.render_backward(res, far, cams, 48, 32, g)
+    bad = torch.isnan(got[0])
+    where = torch.zeros_like(bad)  # reference node: the first of the four of level 0
+    # along the other axis: eight pixels, a shift of at most two and the second tap
+    (where[0, 0, :11, 0] if axis == 0 else where[0, 0, 0, :11])[:] = True
+    assert bad.any() and not (bad & ~where).any()
+    assert torch.isnan(got[1][k]).any() and not torch.isnan(torch.cat([got[1][:k], got[1][k + 1:]])).any()
+    assert torch.allclose(got[0][~where], ref[0][~where], rtol=1e-5, atol=1e-7)
