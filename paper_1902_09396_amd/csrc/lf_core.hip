@@ -48,7 +48,7 @@ lf_status lf_check_launch(const char* what)
 static uint32_t rd32(const uint8_t* p) { uint32_t v; memcpy(&v, p, 4); return v; }
 static uint64_t rd64(const uint8_t* p) { uint64_t v; memcpy(&v, p, 8); return v; }
 
-void lf_parallel(int parts, const std::function<void(int)>& work)
+void lf_parallel(int parts, LfWork work)
 {
     std::vector<std::thread> threads;
     int started = 1;

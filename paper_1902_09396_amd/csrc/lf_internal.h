@@ -3,7 +3,6 @@
 
 #include <cstdarg>
 #include <cstdint>
-#include <functional>
 
 #include "../../include/hmlfc.h"
 #include "lf_geom.h"
@@ -56,10 +55,23 @@ lf_status lf_fail(lf_status s, const char* fmt, ...);
 lf_status lf_check_launch(const char* what);
 lf_status lf_parse(const uint8_t* s, size_t n, LfLayout* L);
 
+// A callable of one int, not owned and not copied to the heap.
+class LfWork {
+    const void* f;
+    void (*call)(const void*, int);
+
+public:
+    template <class F>
+    LfWork(const F& work) : f(&work), call([](const void* p, int k) { (*static_cast<const F*>(p))(k); })
+    {
+    }
+    void operator()(int k) const { call(f, k); }
+};
+
 // work(0) .. work(parts - 1), each on a thread of its own while threads can be
 // started (work(0) and the rest on the caller's); returns when all are done.
-// work must not throw.
-void lf_parallel(int parts, const std::function<void(int)>& work);
+// work must not throw; nothing else is thrown.
+void lf_parallel(int parts, LfWork work);
 
 // Samples of level `lod` from a dense handle (lf_decode.hip); d_scratch: null,
 // or lf_decode_scratch(h, n) > 0 bytes in which the requests are ordered first.
