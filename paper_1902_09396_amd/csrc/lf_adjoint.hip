@@ -1653,8 +1653,19 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     // level-0 gradients (every sample written) and up to two levels above
     const int64_t plane = (int64_t)g.w * g.h;
     AdGather ga{t, Bl.use_axes, all_general, rayf, d_grad_out, ki, vi, start, Bl.n_recs, n_views, width, height};
-    const int D = std::min(g.H - 1, 2);
-    const int clusters = ((g.na + (1 << D) - 1) >> D) * ((g.nb + (1 << D) - 1) >> D);
+    // D levels above from a thread's registers: a level less to read back, but
+    // up to 16 times fewer threads.  Waves of clusters at D = 2 and the call's
+    // time at D = 2 and 0: 102,400 (17x17 of 512x512), 24 views of 512x512
+    // 1.67 and 2.15 ms; 25,600 (17x17 of 256x256), two of 64x64 382 and 514 us,
+    // of 1280x720 706 and 722; 9,216 (9x9 of 256x256), 64x64 146 and 186 us,
+    // 1280x720 (1.4 records a sample) 466 and 403, 320x180 (0.09) 155 and 182;
+    // 2,304 (9x9 of 128x128), 320x180 153 and 117; 256 (5x5 of 64x64), 369 and
+    // 132, projective ones of 1280x720 34.3 and 7.5 ms.
+    auto clusters_of = [&](int d) { return ((g.na + (1 << d) - 1) >> d) * ((g.nb + (1 << d) - 1) >> d); };
+    int D = std::min(g.H - 1, 2);
+    const int64_t waves = clusters_of(D) * plane / 64;
+    if (waves < 4096 || (waves < 16384 && 4 * Bl.n_recs > Bl.n_samples)) D = 0;
+    const int clusters = clusters_of(D);
     hipLaunchKernelGGL(D == 0 ? k_ad_gather<0> : (D == 1 ? k_ad_gather<1> : k_ad_gather<2>),
                        dim3((unsigned)((plane + 255) / 256), (unsigned)std::min(clusters, 65535)), dim3(256), 0, s, g, ga, clusters,
                        d_grad_residual);
