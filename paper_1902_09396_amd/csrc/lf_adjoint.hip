@@ -12,12 +12,12 @@
 // blend of the renderer.  Within a block every pixel has the same bilinear
 // fraction (floor(x + dx) = x + floor(dx)), which both directions use.
 //
-// Adjoint, deterministic (the sort counts its digits by integer atomics in
-// LDS; nothing else is atomic):
+// Adjoint, deterministic (the sort counts its digits, and the tables the views
+// to walk, by integer atomics; nothing else is atomic):
 //  1. views whose homographies separate by axis get per-view tables of the
 //     columns and rows that reach each light-field column, row and view;
-//  2. if some view does not separate, its rays emit one record per
-//     light-field view they blend, keyed by the sample at the top-left of
+//  2. if some view does not separate, or the tables would cost more, its rays
+//     emit one record per light-field view they blend, keyed by the sample at the top-left of
 //     their 2x2 pixel footprint (ray * 4 + view corner), which a stable radix
 //     sort groups by key;
 //  3. every sample gathers the rays that reach it, view by view from the
@@ -564,10 +564,10 @@ static lf_status bwd_layout(const lf_handle* h, int nv, int wo, int ho, BwdLayou
     while (eb < 32 && ((int64_t)1 << eb) <= B->n_samples) eb++;
     B->passes = (eb + 7) / 8;
     // The separable views' gather walks, per sample, the views that reach its
-    // light-field view: worth it while a view's pixels outnumber a light-field
-    // view's samples / 256 (a walked view costs a wave of 64 samples about 20
-    // cycles, a sorted record about 45 ps), and while the tables stay
-    // smaller than the records.
+    // light-field view: never worth it where a view's pixels are fewer than a
+    // light-field view's samples / 256 (a view reaches four light-field views
+    // or more), nor made where the tables would be larger than the records.
+    // What the views of a call reach is known on the device (ad_by_records).
     const int64_t tables = (int64_t)nv * (16 * ((int64_t)wo + ho) + 8 * ((int64_t)g.w + g.h + g.na + g.nb) +
                                           4 * (int64_t)g.na * g.nb + 4);
     B->use_axes = (int64_t)wo * ho * 256 >= (int64_t)g.w * g.h && tables <= 16 * B->n_recs + (1 << 20);
@@ -613,6 +613,15 @@ extern "C" lf_status lf_backward_workspace(const lf_handle* h, int32_t n_views, 
     return LF_OK;
 }
 
+// The words at o_max of the workspace.
+struct AdFlags {
+    float maxshift;
+    int general;    // 1: some view does not separate (set by k_ad_axes)
+    int nan_shift;  // 1: some shift component is NaN
+    int pad;
+    unsigned long long walked;  // sum over the light-field views of the separating views that reach them (k_ad_lists)
+};
+
 // ---- rays whose axes separate ----
 //
 // With every third row (0, 0, 1) and no cross terms, a camera's (u, s) depend
@@ -623,12 +632,28 @@ extern "C" lf_status lf_backward_workspace(const lf_handle* h, int32_t n_views, 
 // Such views need no records and no sort: per view, tables of the columns and
 // rows and of the intervals that reach each x, y, a and b.
 struct AdAxes {
-    int* sep;               // [nv] 1: the view's axes separate
-    int* general;           // [1] 1: some view's do not
+    AdFlags* flags;
+    int all_general;  // 1: no tables, every view goes by records
+    uint64_t most;    // largest flags->walked with which the tables pay
+    int* sep;         // [nv] 1: the view's axes separate
     float4 *col, *row;      // [nv][wo], [nv][ho]: (x0 | a0 << 16, fs, fu), (y0 | b0 << 16, ft, fv)
     int2 *rx, *ry, *ra, *rb;  // [nv][w], [nv][h], [nv][na], [nv][nb]: first and past-the-last column or row
     int *count, *list;      // [nb na], [nb na][nv]: separating views that reach light-field view (b, a), in order
 };
+
+// Views that go by records: none (0), those that do not separate (1), or all
+// (2).  The tables' gather walks, per sample, every view that reaches its
+// light-field view, most of them for nothing when small frames span many
+// light-field views: 35 ps per wave of 64 samples and view, where a record
+// costs about 50 ps and the record route 8 ps per sample.  Over 17x17 of
+// 512x512, 32x32 views that each span the whole grid: 100 of them 4.50 ms by
+// the tables and 1.76 by records, 1500 85.2 and 3.8; views from one point
+// each: 100 1.99 and 2.64, 1500 7.24 and 8.87.
+__device__ __forceinline__ int ad_by_records(const AdAxes& t)
+{
+    if (t.all_general || t.flags->walked > t.most) return 2;
+    return t.flags->general;
+}
 
 __device__ __forceinline__ bool ad_separates(const float* __restrict__ cam)
 {
@@ -689,7 +714,7 @@ __device__ __forceinline__ void ad_axes_entry(const LfGeom& g, const float* __re
     const bool sep = ad_separates(cam);
     if (e == 0) {
         t.sep[v] = sep;
-        if (!sep) *t.general = 1;  // cleared by an earlier kernel; every writer stores 1
+        if (!sep) t.flags->general = 1;  // cleared by an earlier kernel; every writer stores 1
     }
     if (!sep) return;
     float fc, fu;
@@ -747,15 +772,18 @@ __global__ void __launch_bounds__(256) k_ad_lists(LfGeom g, int nv, AdAxes t)
         if (hit) t.list[(int64_t)k * nv + n + __popcll(m & ((1ull << lane) - 1ull))] = v;
         n += __popcll(m);
     }
-    if (lane == 0) t.count[k] = n;
+    if (lane == 0) {
+        t.count[k] = n;
+        if (n) atomicAdd(&t.flags->walked, (unsigned long long)n);
+    }
 }
 
 // ---- the other rays: records sorted by the sample they reach ----
 //
 // A stable least-significant-digit radix sort of (key, record), 8 bits a
-// pass, AD_SORT_WG workgroups each owning one contiguous range of the
+// pass, workgroups each owning one contiguous range of the
 // records: count the range's digits, then scatter in order.  Every kernel
-// returns at once when all views separate.
+// returns at once when no view goes by records.
 struct AdSort {
     uint32_t *kin, *kout, *vin, *vout;  // ping-pong; the sorted records end in kin, vin after an even number of passes
     uint32_t* hist;                     // [AD_SORT_WG][256]
@@ -769,13 +797,15 @@ __device__ __forceinline__ void ad_sort_count(uint32_t (&h)[256], const uint32_t
     for (int64_t i = begin + threadIdx.x; i < end; i += AD_SORT_T) atomicAdd(&h[(keys[i] >> shift) & 255u], 1u);
 }
 
-// Records and blend fractions of every ray (a view that separates gets the
-// key past every sample), the first digit's counts, and the empty key table.
+// Records and blend fractions of every ray (a view that goes by the tables
+// gets the key past every sample), the first digit's counts, and the empty key
+// table.
 __global__ void __launch_bounds__(AD_SORT_T) k_ad_records(LfGeom g, const float* __restrict__ cams, int nv, int wo, int ho,
-                                                          AdAxes t, int all_general, AdSort s, float4* __restrict__ rayf,
+                                                          AdAxes t, AdSort s, float4* __restrict__ rayf,
                                                           uint32_t* __restrict__ start, int64_t n_samples)
 {
-    if (!all_general && !*t.general) return;
+    const int by = ad_by_records(t);
+    if (!by) return;
     __shared__ uint32_t h[256];
     if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
@@ -784,7 +814,7 @@ __global__ void __launch_bounds__(AD_SORT_T) k_ad_records(LfGeom g, const float*
     for (int64_t r = begin + threadIdx.x; r < end; r += AD_SORT_T) {
         const int v = (int)(r / npix);
         const int64_t px = r - (int64_t)v * npix;
-        const bool use = all_general || !t.sep[v];
+        const bool use = by == 2 || !t.sep[v];
         const AdRay ry = ad_ray(g, cams + 18 * (int64_t)v, (int)(px % wo), (int)(px / wo));
         rayf[r] = make_float4(ry.fu, ry.fv, ry.fs, ry.ft);  // the blend fractions, for the gather pass
         uint32_t key[4];
@@ -804,10 +834,10 @@ __global__ void __launch_bounds__(AD_SORT_T) k_ad_records(LfGeom g, const float*
     if (threadIdx.x < 256) s.hist[blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
 }
 
-__global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_count(const int* __restrict__ general, int all_general, AdSort s,
+__global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_count(AdAxes t, AdSort s,
                                                              const uint32_t* __restrict__ keys, int shift)
 {
-    if (!all_general && !*general) return;
+    if (!ad_by_records(t)) return;
     __shared__ uint32_t h[256];
     if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
@@ -817,11 +847,11 @@ __global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_count(const int* __restri
     if (threadIdx.x < 256) s.hist[blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
 }
 
-__global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_scatter(const int* __restrict__ general, int all_general, AdSort s,
+__global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_scatter(AdAxes t, AdSort s,
                                                                const uint32_t* __restrict__ ki, const uint32_t* __restrict__ vi,
                                                                uint32_t* __restrict__ ko, uint32_t* __restrict__ vo, int shift)
 {
-    if (!all_general && !*general) return;
+    if (!ad_by_records(t)) return;
     constexpr int W = AD_SORT_T / 64;
     __shared__ uint32_t base[256];          // next output place of each digit
     __shared__ uint32_t cnt[W][256];        // this step's digit counts per wave
@@ -849,8 +879,8 @@ __global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_scatter(const int* __rest
         inc = all;  // inclusive scan over the 256 digits
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
-            if (lane >= o) inc += t;
+            const uint32_t up = (uint32_t)__shfl_up((int)inc, o, 64);
+            if (lane >= o) inc += up;
         }
         if (lane == 63) wsum[wv] = inc;
     }
@@ -898,10 +928,10 @@ __global__ void __launch_bounds__(AD_SORT_T) k_ad_sort_scatter(const int* __rest
 }
 
 // first record of every key present
-__global__ void k_ad_heads(const int* __restrict__ general, int all_general, const uint32_t* __restrict__ keys, int64_t n,
+__global__ void k_ad_heads(AdAxes t, const uint32_t* __restrict__ keys, int64_t n,
                            int64_t n_samples, uint32_t* __restrict__ start)
 {
-    if (!all_general && !*general) return;
+    if (!ad_by_records(t)) return;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t k = keys[i];
         if ((int64_t)k < n_samples && (i == 0 || keys[i - 1] != k)) start[k] = (uint32_t)i;
@@ -910,7 +940,6 @@ __global__ void k_ad_heads(const int* __restrict__ general, int all_general, con
 
 struct AdGather {
     AdAxes t;
-    int use_axes, all_general;
     const float4* rayf;
     const float* grad_out;
     const uint32_t *keys, *vals, *start;
@@ -920,16 +949,16 @@ struct AdGather {
 
 // Gradient of the RGB sample (b, a, y, x): over the separating views that
 // reach view (b, a), the rectangle of their pixels that reach (y, x); then,
-// if some view does not separate, the sorted records keyed at the sample and
-// at its left, upper and upper-left neighbours.  A record keyed at the
+// if some view goes by records (by > 0), those keyed at the sample and at its
+// left, upper and upper-left neighbours.  A record keyed at the
 // footprint corner (y0, x0) reaches pixel corner (cy, cx) at (y0 + cy, x0 +
 // cx), except along an axis of length 1, where both corners are pixel 0.
-__device__ __forceinline__ void ad_sample(const LfGeom& g, const AdGather& G, int b, int a, int y, int x, bool general,
+__device__ __forceinline__ void ad_sample(const LfGeom& g, const AdGather& G, int b, int a, int y, int x, int by,
                                           float (&acc)[3])
 {
     const int64_t npix = (int64_t)G.wo * G.ho;
     acc[0] = acc[1] = acc[2] = 0.0f;
-    if (G.use_axes) {
+    if (by < 2) {
         const int k = b * g.na + a, n = G.t.count[k];
         for (int q = 0; q < n; q++) {
             const int v = __builtin_amdgcn_readfirstlane(G.t.list[(int64_t)k * G.nv + q]);
@@ -955,7 +984,7 @@ __device__ __forceinline__ void ad_sample(const LfGeom& g, const AdGather& G, in
             }
         }
     }
-    if (!general) return;
+    if (!by) return;
     const int64_t S = (((int64_t)b * g.na + a) * g.h + y) * g.w + x;
     for (int cy = 0; cy < 2; cy++) {
         const int dy = g.h >= 2 ? cy : 0;
@@ -997,7 +1026,7 @@ __global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int clu
     const int plane = g.w * g.h;
     if (px >= plane) return;
     const int y = px / g.w, x = px - y * g.w;
-    const bool general = G.all_general || *G.t.general;
+    const int by = ad_by_records(G.t);
     const int nac = (g.na + (1 << D) - 1) >> D;
     const int64_t cstride = (int64_t)g.n_nodes * plane;
     auto put = [&](int l, int Bl, int Al, const float (&v)[3]) {
@@ -1008,7 +1037,7 @@ __global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int clu
     };
     auto leaf = [&](int b, int a, float (&o)[3]) {
         float acc[3];
-        ad_sample(g, G, b, a, y, x, general, acc);
+        ad_sample(g, G, b, a, y, x, by, acc);
         // colour transpose of R = Y + Co/2 - Cg/2, G = Y + Cg/2, B = Y - Co/2 - Cg/2
         o[0] = acc[0] + acc[1] + acc[2];
         o[1] = 0.5f * (acc[0] - acc[2]);
@@ -1090,13 +1119,6 @@ __global__ void k_ad_maxshift(const float2* __restrict__ shift, int64_t n, float
     if (threadIdx.x == 0) out[blockIdx.x] = nan ? -red[0] : red[0];
 }
 
-// The words at o_max of the workspace.
-struct AdFlags {
-    float maxshift;
-    int general;    // 1: some view does not separate (set by k_ad_axes)
-    int nan_shift;  // 1: some shift component is NaN
-};
-
 __global__ void k_ad_maxparts(const float* __restrict__ parts, int n, AdFlags* __restrict__ out)
 {
     __shared__ float red[256];
@@ -1112,7 +1134,7 @@ __global__ void k_ad_maxparts(const float* __restrict__ parts, int n, AdFlags* _
         if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out = AdFlags{red[0], 0, nan};
+    if (threadIdx.x == 0) *out = AdFlags{red[0], 0, nan, 0, 0};
 }
 
 // pixel range [lo, hi] of [k0, k1] whose tap (x + fd + o), clamped to [0, n-1], equals X
@@ -1610,7 +1632,9 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     hipLaunchKernelGGL(k_ad_maxparts, dim3(1), dim3(256), 0, s, parts, AD_MAX_PARTS, flags);
     AdAxes t;
     t.sep = (int*)(W + Bl.o_sep);
-    t.general = &flags->general;
+    t.flags = flags;
+    t.all_general = !Bl.use_axes;
+    t.most = (uint64_t)(16 * (int64_t)g.na * g.nb + 128 * Bl.n_recs / ((int64_t)g.w * g.h));
     t.col = (float4*)(W + Bl.o_col);
     t.row = (float4*)(W + Bl.o_row);
     t.rx = (int2*)(W + Bl.o_rx);
@@ -1619,7 +1643,6 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     t.rb = (int2*)(W + Bl.o_rb);
     t.count = (int*)(W + Bl.o_count);
     t.list = (int*)(W + Bl.o_list);
-    const int all_general = !Bl.use_axes;
     if (Bl.use_axes) {
         const int64_t items = n_views * ((int64_t)width + height + g.w + g.h + g.na + g.nb);
         hipLaunchKernelGGL(k_ad_axes, dim3((unsigned)std::min<int64_t>((items + 255) / 256, 1 << 20)), dim3(256), 0, s, g, d_cams, n_views, width,
@@ -1637,22 +1660,22 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     float4* rayf = (float4*)(W + Bl.o_rayf);
     uint32_t* start = (uint32_t*)(W + Bl.o_start);
     hipLaunchKernelGGL(k_ad_records, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, g, d_cams, n_views, width, height, t,
-                       all_general, srt, rayf, start, Bl.n_samples);
+                       srt, rayf, start, Bl.n_samples);
     uint32_t *ki = srt.kin, *vi = srt.vin, *ko = srt.kout, *vo = srt.vout;
     for (int ps = 0; ps < Bl.passes; ps++) {
         if (ps > 0)
-            hipLaunchKernelGGL(k_ad_sort_count, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, t.general, all_general, srt, ki,
+            hipLaunchKernelGGL(k_ad_sort_count, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, t, srt, ki,
                                8 * ps);
-        hipLaunchKernelGGL(k_ad_sort_scatter, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, t.general, all_general, srt, ki, vi,
+        hipLaunchKernelGGL(k_ad_sort_scatter, dim3(AD_SORT_WG), dim3(AD_SORT_T), 0, s, t, srt, ki, vi,
                            ko, vo, 8 * ps);
         std::swap(ki, ko);
         std::swap(vi, vo);
     }
     hipLaunchKernelGGL(k_ad_heads, dim3((unsigned)std::min<int64_t>((Bl.n_recs + 255) / 256, 8192)), dim3(256), 0, s,
-                       t.general, all_general, ki, Bl.n_recs, Bl.n_samples, start);
+                       t, ki, Bl.n_recs, Bl.n_samples, start);
     // level-0 gradients (every sample written) and up to two levels above
     const int64_t plane = (int64_t)g.w * g.h;
-    AdGather ga{t, Bl.use_axes, all_general, rayf, d_grad_out, ki, vi, start, Bl.n_recs, n_views, width, height};
+    AdGather ga{t, rayf, d_grad_out, ki, vi, start, Bl.n_recs, n_views, width, height};
     // D levels above from a thread's registers: a level less to read back, but
     // up to 16 times fewer threads.  Waves of clusters at D = 2 and the call's
     // time at D = 2 and 0: 102,400 (17x17 of 512x512), 24 views of 512x512

@@ -84,3 +84,39 @@ def test_tree_height_of_a_small_field():
         res, sh = field.export_params()
         times.append(_time(lambda: field.render_backward(res, sh, dc, 1280, 720, g)))
     assert times[1] < 2 * times[0], times
+
+
+def _wide(views, n, h, wo):
+    """Separable views that each span every light-field view of an n x n grid."""
+    return lfscene.random_pinhole_cameras(views, n, n, h, h, wo, wo, seed=5, ez_range=(-9.0, -8.0), zoom_range=(0.95, 1.0))
+
+
+@pytest.mark.parametrize("views,warped", [(10, 0), (24, 0), (24, 5)])
+def test_small_frames_over_many_views(views, warped):
+    """Enough of them that the tables would be walked mostly for nothing: all
+    go by records (from 17 views on; with 10 the tables serve)."""
+    from paper_1902_09396_amd import lf
+
+    s = _stream(9, 9, 192, 192, 16, 3)
+    cams = _wide(views, 9, 192, 13)
+    if warped:
+        cams[:warped] = lfscene.projective_warp(cams[:warped], 1e-2, -5e-3)
+    _compare(lf.LightField(s), oracle.OracleLF(s), cams, 13, 13, views)
+
+
+def test_cost_of_small_frames_over_many_views():
+    """Views over the whole grid cost about what views from one point each do
+    (six times that when every sample walks every view)."""
+    import torch
+
+    from paper_1902_09396_amd import lf
+
+    light = np.tile(lf_for("tiny"), (3, 3, 4, 4, 1))[:17, :17]
+    field = lf.LightField(lf.encode(np.ascontiguousarray(light), lfscene.get_config("path512")["enc"]))
+    res, sh = field.export_params()
+    g = torch.ones(400, 3, 32, 32, device="cuda")
+    times = []
+    for cams in (lfscene.random_fixed_uv_cameras(400, 17, 17, 256, 256, 32, 32, 5), _wide(400, 17, 256, 32)):
+        dc = torch.from_numpy(cams).cuda()
+        times.append(_time(lambda: field.render_backward(res, sh, dc, 32, 32, g)))
+    assert times[1] < 3 * times[0], times
