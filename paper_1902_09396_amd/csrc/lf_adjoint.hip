@@ -938,6 +938,10 @@ __global__ void k_ad_heads(AdAxes t, const uint32_t* __restrict__ keys, int64_t 
     }
 }
 
+// Sample gradients and sums in one launch, or in two where records are to be
+// gathered: the sample gradients alone first, then the sums.
+enum AdPass { AD_WHOLE, AD_LEAVES, AD_SUMS };
+
 struct AdGather {
     AdAxes t;
     const float4* rayf;
@@ -1020,13 +1024,15 @@ __device__ __forceinline__ void ad_sample(const LfGeom& g, const AdGather& G, in
 // views (records for every ray, a library radix sort, one thread per sample
 // and a pass per tree level: 2.05 ms).
 template <int D>
-__global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int clusters, float* __restrict__ gres)
+__global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int clusters, AdPass pass, float* __restrict__ gres)
 {
+    const int by = ad_by_records(G.t);
+    if (pass == AD_LEAVES && !by) return;
+    const bool there = pass == AD_SUMS && by;  // the sample gradients are in gres
     const int px = (int)(blockIdx.x * 256 + threadIdx.x);
     const int plane = g.w * g.h;
     if (px >= plane) return;
     const int y = px / g.w, x = px - y * g.w;
-    const int by = ad_by_records(G.t);
     const int nac = (g.na + (1 << D) - 1) >> D;
     const int64_t cstride = (int64_t)g.n_nodes * plane;
     auto put = [&](int l, int Bl, int Al, const float (&v)[3]) {
@@ -1036,6 +1042,13 @@ __global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int clu
         o[2 * cstride] = v[2];
     };
     auto leaf = [&](int b, int a, float (&o)[3]) {
+        if (D > 0 && there) {
+            const float* in = gres + (int64_t)(g.node_base[0] + b * g.na + a) * plane + px;
+            o[0] = in[0];
+            o[1] = in[cstride];
+            o[2] = in[2 * cstride];
+            return;
+        }
         float acc[3];
         ad_sample(g, G, b, a, y, x, by, acc);
         // colour transpose of R = Y + Co/2 - Cg/2, G = Y + Cg/2, B = Y - Co/2 - Cg/2
@@ -1634,7 +1647,7 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     t.sep = (int*)(W + Bl.o_sep);
     t.flags = flags;
     t.all_general = !Bl.use_axes;
-    t.most = (uint64_t)(16 * (int64_t)g.na * g.nb + 128 * Bl.n_recs / ((int64_t)g.w * g.h));
+    t.most = (uint64_t)(16 * (int64_t)g.na * g.nb + 64 * Bl.n_recs / ((int64_t)g.w * g.h));
     t.col = (float4*)(W + Bl.o_col);
     t.row = (float4*)(W + Bl.o_row);
     t.rx = (int2*)(W + Bl.o_rx);
@@ -1679,19 +1692,30 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     // D levels above from a thread's registers: a level less to read back, but
     // up to 16 times fewer threads.  Waves of clusters at D = 2 and the call's
     // time at D = 2 and 0: 102,400 (17x17 of 512x512), 24 views of 512x512
-    // 1.67 and 2.15 ms; 25,600 (17x17 of 256x256), two of 64x64 382 and 514 us,
-    // of 1280x720 706 and 722; 9,216 (9x9 of 256x256), 64x64 146 and 186 us,
-    // 1280x720 (1.4 records a sample) 466 and 403, 320x180 (0.09) 155 and 182;
-    // 2,304 (9x9 of 128x128), 320x180 153 and 117; 256 (5x5 of 64x64), 369 and
-    // 132, projective ones of 1280x720 34.3 and 7.5 ms.
+    // 1.67 and 2.15 ms; 25,600 (17x17 of 256x256), 16 views 527..690 and
+    // 611..733 us; 9,216 (9x9 of 256x256), eight views of 256x256 (0.4 records
+    // a sample) 161..190 and 189..203, 16 of 512x512 (3.2) 382..489 and
+    // 317..382; 2,304 (9x9 of 128x128), two of 320x180 153 and 117; 256 (5x5 of
+    // 64x64) 369 and 132.
     auto clusters_of = [&](int d) { return ((g.na + (1 << d) - 1) >> d) * ((g.nb + (1 << d) - 1) >> d); };
+    auto gather = [&](int d, AdPass pass) {
+        const int clusters = clusters_of(d);
+        const int64_t wx = (plane + 255) / 256;
+        // the launch that may find nothing to do is kept to 8,192 workgroups
+        const int64_t wy = pass == AD_LEAVES ? std::max<int64_t>(8192 / wx, 1) : 65535;
+        hipLaunchKernelGGL(d == 0 ? k_ad_gather<0> : (d == 1 ? k_ad_gather<1> : k_ad_gather<2>),
+                           dim3((unsigned)wx, (unsigned)std::min<int64_t>(clusters, wy)), dim3(256), 0, s, g, ga, clusters, pass,
+                           d_grad_residual);
+    };
     int D = std::min(g.H - 1, 2);
     const int64_t waves = clusters_of(D) * plane / 64;
-    if (waves < 4096 || (waves < 16384 && 4 * Bl.n_recs > Bl.n_samples)) D = 0;
-    const int clusters = clusters_of(D);
-    hipLaunchKernelGGL(D == 0 ? k_ad_gather<0> : (D == 1 ? k_ad_gather<1> : k_ad_gather<2>),
-                       dim3((unsigned)((plane + 255) / 256), (unsigned)std::min(clusters, 65535)), dim3(256), 0, s, g, ga, clusters,
-                       d_grad_residual);
+    if (waves < 4096 || (waves < 16384 && Bl.n_recs > 2 * Bl.n_samples)) D = 0;
+    // Records take a chain of dependent loads each and are spread unevenly:
+    // they want a thread a sample on larger fields too (17x17 of 256x256, two
+    // projective views of 1280x720 2.20 and 1.92 ms; 5x5 of 64x64 34.3 and 7.5).
+    const bool ahead = D > 0 && waves < 32768 && 4 * Bl.n_recs > Bl.n_samples;
+    if (ahead) gather(0, AD_LEAVES);
+    gather(D, ahead ? AD_SUMS : AD_WHOLE);
     for (int l = D + 1; l < g.H; l++)
         hipLaunchKernelGGL(k_ad_tree, dim3(8192), dim3(256), 0, s, g, l, d_grad_residual);
     // the shift pass reads the predictive nodes' gradients, which the

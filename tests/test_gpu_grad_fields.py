@@ -59,6 +59,7 @@ def _time(f):
 @pytest.mark.parametrize("na,nb,h,w,levels,views,wo,ho", [
     (9, 9, 192, 208, 3, 2, 40, 30),  # enough clusters for the chip and few rays: two levels in registers
     (9, 9, 112, 96, 2, 2, 40, 30),  # one level
+    (9, 9, 112, 96, 2, 1, 700, 500), (13, 9, 192, 208, 3, 1, 1100, 700),  # leaves ahead of the sums where records are gathered
     (9, 9, 192, 208, 3, 1, 1200, 800),  # more records than a quarter of the samples
     (5, 3, 64, 48, 4, 2, 20, 30)])  # few clusters
 def test_levels_in_registers(kind, na, nb, h, w, levels, views, wo, ho):
