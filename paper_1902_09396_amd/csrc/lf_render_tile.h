@@ -554,6 +554,41 @@ __device__ __forceinline__ uint2 lf_quad_finish(const LfGeom& g, const LfPtrs& p
     return make_uint2(lf_as_u32(r01 + sg * q01), lf_as_u32(r23 + sg * q23));
 }
 
+// One ray whose four views are node (r.b0, r.a0) of the geometry's leaf level,
+// a reference on a path of references: the root and the reference planes at
+// its four pixels, blended in lf_render_one's order (the four views' (s, t)
+// sums are the same).
+template <int RES>
+__device__ __forceinline__ void lf_reference_ray(const LfGeom& g, const LfPtrs& p, const Ray& r, float (&out)[3])
+{
+    const size_t plane = (size_t)g.w * g.h;
+    int v[3][4];
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const int16_t* rt = p.root + ((size_t)(c * g.root_nb + (r.b0 >> g.H)) * g.root_na + (r.a0 >> g.H)) * plane;
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[c][k] = rt[((k & 2) ? r.y1 : r.y0) * g.w + ((k & 1) ? r.x1 : r.x0)];
+    }
+    for (int l = 0; l < g.H; l++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const uint32_t rp = lf_ref_index(g, c, l, r.b0 >> (l + 1), r.a0 >> (l + 1));
+#pragma unroll
+            for (int k = 0; k < 4; k++) v[c][k] += lf_ref_tap<RES>(g, p, rp, (k & 2) ? r.y1 : r.y0, (k & 1) ? r.x1 : r.x0);
+        }
+    const BlendW w = lf_blend_weights(r);
+    int px[4][3];
+#pragma unroll
+    for (int k = 0; k < 4; k++) lf_ycocg_to_rgb(v[0][k], v[1][k], v[2][k], px[k][0], px[k][1], px[k][2]);
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        float sm[16];
+#pragma unroll
+        for (int k = 0; k < 16; k++) sm[k] = (float)px[k & 3][c];
+        out[c] = lf_blend16(sm, w);
+    }
+}
+
 // floor(n / d) for n, d < 2^16: m = ceil(2^32 / d) for d >= 2 (exact in that
 // range); d = 1 would need m = 2^32, so it is encoded as m = 0 (identity)
 __device__ __forceinline__ uint32_t lf_magic(uint32_t d)
@@ -854,6 +889,27 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
     // successes in a row
     int f = 0, n = GROUP_FIRST(gmax), ceil_n = gmax + 1, streak = 0;
     while (f < nf) {
+        if constexpr (LOD && !C420) {
+            // A view that meets one node here, a reference on a path of
+            // references, is twelve plane reads a ray and level, less than a
+            // tile's plan and stages while few views share those: two views of
+            // 986x429 from one point, 8x8 blocks, level 1 of 2 42 us, 74
+            // through the stages (19 in a launch of one thread per ray, whose
+            // workgroups need no LDS); eight of 512x512, four a workgroup, 49
+            // and 73; 16, eight a workgroup, 76 and 80, at level 1 of 4 113
+            // and 86.
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)fbox[f][0]),
+                           hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)fbox[f][1]);
+            if (nf <= 4 && lo == hi && ((lo | (lo >> 16)) & ((1u << g.H) - 1u)) == 0u) {
+                float o[3];
+                lf_reference_ray<RES>(g, p, lf_ray_setup<LOD>(g, grid, cams + 18 * (v0 + f), ii, jj), o);
+                if (live)
+#pragma unroll
+                    for (int c = 0; c < 3; c++) out[((int64_t)(v0 + f) * 3 + c) * npix_out + (int64_t)j * wo + i] = o[c];
+                f += 1;
+                continue;
+            }
+        }
         n = min(n, nf - f);
         // plan the group [f, f + n) (wave 0); a plan that fails stops at the
         // first check that fails
