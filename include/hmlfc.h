@@ -232,8 +232,10 @@ lf_status lf_render_views_per_ray(const lf_handle* h, const float* d_cams, int32
  * (b, a, y, x) is read from the level-`level` node image of (b >> level,
  * a >> level), i.e. every view of a 2^level x 2^level cluster shows its
  * reconstructed RKV.  Runs the staged tile kernel on the tree above the level
- * where lf_render_views would, the root level (level = H) and the other
- * handles one thread per ray.  level = 0 equals lf_render_views and
+ * where lf_render_views would and the decoded values of that level, too, are
+ * bounded by its 16-bit lanes; the root level (level = H), 4:4:4 renders of a
+ * few views or over a single row or column of nodes at the level below it, and
+ * the other handles run one thread per ray.  level = 0 equals lf_render_views and
  * lf_render_views_per_ray bit for bit.  LF_EINVAL for level outside 0 .. H. */
 lf_status lf_render_views_lod(const lf_handle* h, int32_t level, const float* d_cams, int32_t n_views,
                               int32_t width, int32_t height, float* d_out, void* stream);

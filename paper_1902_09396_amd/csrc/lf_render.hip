@@ -355,17 +355,25 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
 // taken when the load has settled the range of every level and of the motion
 // vectors (nothing is refused there).  The root
 // level is sixteen plain reads per ray: no tiles.  CSR handles search a row
-// per tap: no tiles.  Nor at the level below the root from level 2 on, or
-// where its nodes are a single row or column: a ray's four views are mostly
-// one node there, often a reference, which is less than a tile's plan (25
-// views of 271x211 over 2x1 nodes 29 us per ray, 65 through the tiles; 2 of
-// 986x429 over 3x2 nodes from one point 56 and 82; a path through 3x3 nodes 31
-// and 27).  4:2:0 chroma is dearer per ray (342 us against 39).
-static bool lf_tiles_apply(const lf_handle* h, int level)
+// per tap: no tiles.  Nor do renders from the level below the root where its
+// nodes are a single row or column, or, from level 2 on, where a workgroup
+// would take fewer than five views: a ray's four views are often one node
+// there, and where that is a reference a ray is a few reads, which the stages
+// only beat shared among views.  Over 1x2 nodes two views of 986x429 44 us per
+// ray and 84 through the tiles, 25 of 271x211 77 and 117; over 1x1 19 and 42.
+// Over 8x8 nodes, 4x4 blocks, two of 986x429 from one point each 53 and 83
+// (over 4x4 123 and 84), 16 of 512x512 on a path, eight a workgroup, 477 and
+// 104 (over 2x2 to 8x8 nodes 306..523 and 73..105).  4:2:0 chroma is dearer
+// per ray (342 us against 39).
+static bool lf_tiles_apply(const lf_handle* h, int level, int nv, int wo, int ho)
 {
     const LfLayout& L = h->L;
     if (L.g.bs < 4 || level >= L.g.H || L.sparse == LF_RES_CSR) return false;
-    if (level > 0 && level + 1 == L.g.H && !L.chroma420 && (level > 1 || L.g.na_l[level] == 1 || L.g.nb_l[level] == 1)) return false;
+    if (level > 0 && level + 1 == L.g.H && !L.chroma420) {
+        if (L.g.na_l[level] == 1 || L.g.nb_l[level] == 1) return false;
+        const int tiles = ((wo + TW - 1) / TW) * ((ho + TH - 1) / TH);
+        if (level > 1 && std::min(frames_per_chunk(nv, tiles), nv) < 5) return false;
+    }
     if (L.sparse || L.chroma420) return L.packed_levels != 0;
     return level == 0 || L.packed_levels;
 }
@@ -376,7 +384,7 @@ extern "C" lf_status lf_render_views(const lf_handle* h, const float* d_cams, in
     if (!h || n_views < 0 || width < 1 || height < 1) return lf_fail(LF_EINVAL, "bad argument");
     if (n_views == 0) return LF_OK;
     if (!d_cams || !d_out) return lf_fail(LF_EINVAL, "null buffer");
-    if (lf_tiles_apply(h, 0)) return lf_launch_render_batch(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream);
+    if (lf_tiles_apply(h, 0, n_views, width, height)) return lf_launch_render_batch(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream);
     return lf_launch_render_rays(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream);
 }
 
@@ -398,7 +406,7 @@ extern "C" lf_status lf_render_views_lod(const lf_handle* h, int32_t level, cons
     if (!d_cams || !d_out) return lf_fail(LF_EINVAL, "null buffer");
     // 16 views of 512x512 at level 2 of 17x17x512x512: 0.098 ms through the
     // tiles, 1.09 ms one thread per ray
-    if (lf_tiles_apply(h, level))
+    if (lf_tiles_apply(h, level, n_views, width, height))
         return lf_launch_render_batch(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream, level);
     return lf_launch_render_rays(h, d_cams, n_views, width, height, d_out, (hipStream_t)stream, level);
 }

@@ -69,3 +69,24 @@ def test_cost_of_one_reference():
             best = min(best, a.elapsed_time(b))
         times.append(best)
     assert times[0] < 0.6 * times[1], times
+
+
+@pytest.mark.parametrize("na,nb,levels", [(8, 8, 3), (17, 9, 4), (8, 4, 3)])
+def test_level_below_the_root_by_views(na, nb, levels):
+    """40 views in one call (five and more a workgroup: tiles, except over a
+    single row of nodes) and in calls of four (one thread per ray)."""
+    import torch
+
+    from paper_1902_09396_amd import lf
+
+    cfg = lfscene.get_config("tiny", levels=levels, step=[4] * levels, win=[4] * levels, t_ref=[0] * levels,
+                             t_pred=[0] * levels, block=8)
+    light = np.tile(lf_for("tiny"), (2, 3, 1, 1, 1))[:nb, :na]
+    field = lf.LightField(lf.encode(np.ascontiguousarray(light), cfg["enc"]))
+    wo, ho = 512, 128
+    assert lf.render_config(40, wo, ho)[1] >= 5 > lf.render_config(4, wo, ho)[1]
+    cams = np.concatenate([lfscene.camera_path_orbit(20, na, nb, 64, 64, wo, ho, radius=1.2),
+                           lfscene.random_pinhole_cameras(20, na, nb, 64, 64, wo, ho, seed=na)])
+    dc = torch.from_numpy(cams).cuda()
+    got = field.render_views_lod(levels - 1, dc, wo, ho)
+    assert torch.equal(got, torch.cat([field.render_views_lod(levels - 1, dc[k:k + 4], wo, ho) for k in range(0, 40, 4)]))
