@@ -949,11 +949,7 @@ static lf_status lf_decode(const lf_handle* h, int32_t level, const int32_t* d_c
     if (!d_coords || !d_rgb) return lf_fail(LF_EINVAL, "null buffer");
     if (((uintptr_t)d_coords) & 15) return lf_fail(LF_EINVAL, "coords must be 16-byte aligned");
     if (h->L.chroma420) return lf_launch_decode420(h, level, d_coords, n, d_rgb, stream);
-    // Without scratch, many requests keep the one-thread walk: scattered, they
-    // are bound by cache lines, and its table and vectors are half the bytes
-    // of the descriptors (2^18 scattered requests 125 us against 172, 98,304 75
-    // against 61).
-    if (!h->L.sparse && (d_scratch || n < LF_DECODE_ORDER_MIN))
+    if (!h->L.sparse && (d_scratch || lf_decode_unordered(h, n)))
         return lf_launch_decode_dense(h, level, d_coords, n, d_rgb, lf_clamp_counter(h), d_scratch, (hipStream_t)stream);
     const int64_t blocks = (n + 255) / 256;
     if (blocks > 0x7FFFFFFF) return lf_fail(LF_EINVAL, "too many samples");

@@ -18,6 +18,7 @@
 #define DEC_L 2             // levels read together (more cost registers that hold waves: 66 us against 59 for 2^20 consecutive samples at 4)
 #define DEC_T 1024          // threads of it
 #define DEC_MAX (1 << 26)   // most requests ordered in one call (1 GiB of scratch)
+#define DEC_SMALL 163840    // fewest unordered requests of a small field that keep the one-thread walk
 
 // Words 2 e, 2 e + 1 of int16 elements from an even element on: 4-byte aligned.
 typedef uint32_t lf_w2 __attribute__((ext_vector_type(2), aligned(4)));
@@ -293,6 +294,20 @@ static int64_t order_layout(const LfGeom& g, int64_t n, uint8_t* base, DecOrder*
     return at;
 }
 
+// Fields that L2 holds: requests are not ordered.
+static bool dec_small_field(const LfGeom& g) { return (int64_t)g.na * g.nb * g.w * g.h < (1 << 22); }
+
+// Whether k_decode_dense takes n unordered requests of a dense handle; more go
+// to the one-thread walk, whose table and vectors are half the bytes of the
+// descriptors: scattered over 17x17x512x512, 98,304 take 61 us here and 75
+// there, 2^18 172 and 125.  Over 9x9x192x192, 163,840 take 57 and 56 in 4x4
+// blocks, 42 and 56 in 16x16, 2^18 92 and 75, 67 and 66; consecutive ones 12
+// and 21, 2^18 12 and 23.
+bool lf_decode_unordered(const lf_handle* h, int64_t n)
+{
+    return n < (dec_small_field(h->L.g) ? DEC_SMALL : LF_DECODE_ORDER_MIN);
+}
+
 // Scratch that ordering n requests takes; 0 where requests are not ordered:
 // few or more than 2^26 of them, and small fields, which L2 holds anyway.
 // Over 17x17x512x512, scattered requests: 2^17 80 -> 50 us, 2^18 125 -> 75,
@@ -305,7 +320,7 @@ int64_t lf_decode_scratch(const lf_handle* h, int64_t n)
 {
     const LfGeom& g = h->L.g;
     if (h->L.sparse || h->L.chroma420 || n < LF_DECODE_ORDER_MIN || n > DEC_MAX) return 0;
-    if ((int64_t)g.na * g.nb * g.w * g.h < (1 << 22)) return 0;
+    if (dec_small_field(g)) return 0;
     DecOrder o;
     return order_layout(g, n, nullptr, &o);
 }

@@ -76,6 +76,7 @@ void lf_parallel(int parts, LfWork work);
 // Samples of level `lod` from a dense handle (lf_decode.hip); d_scratch: null,
 // or lf_decode_scratch(h, n) > 0 bytes in which the requests are ordered first.
 int64_t lf_decode_scratch(const lf_handle* h, int64_t n);
+bool lf_decode_unordered(const lf_handle* h, int64_t n);
 lf_status lf_launch_decode_dense(const lf_handle* h, int lod, const int32_t* d_coords, int64_t n, uint8_t* d_rgb,
                                  unsigned long long* clamps, void* d_scratch, hipStream_t s);
 
