@@ -140,41 +140,37 @@ __global__ void __launch_bounds__(192) k_decode_dense(LfGeom g, LfPtrs p, int lo
     __shared__ int vals[3][64];
     const int lane = threadIdx.x & 63, c = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const bool ordered = ORDERED && o.total[DEC_KEYS + o.wgs] != 0;
-    // one run of 64 requests a workgroup, except in launches of more than 2^24
-    const int64_t runs = ordered ? (int64_t)gridDim.x : (n + 63) / 64;
-    for (int64_t run = blockIdx.x; run < runs; run += gridDim.x) {
-        // ordered: each XCD takes a contiguous range, whose lines stay in its
-        // L2 (the launch has a multiple of 8 workgroups, at least one a run,
-        // and the last of a range may be past the end)
-        const int64_t k = (ordered ? (run & 7) * (int64_t)(gridDim.x >> 3) + (run >> 3) : run) * 64 + lane;
-        const bool in = k < n;
-        int64_t at = k;
-        if (in) {
-            int4 r;
-            if (ordered) {
-                const uint4 q = o.rec[k];
-                at = q.x;
-                r = make_int4((int)(q.y & 0xFFFFu), (int)(q.y >> 16), (int)(q.z & 0xFFFFu), (int)(q.z >> 16));
-            } else {
-                bool clamped;
-                r = dec_request(g, lod, coords[k], clamped);
-                // counted by the ordering's first pass when there is one
-                if (!ORDERED && c == 0) {
-                    const unsigned long long m = __ballot(clamped);
-                    if (m && lane == __ffsll((long long)m) - 1) atomicAdd(clamps, (unsigned long long)__popcll(m));
-                }
+    // one run of 64 requests a workgroup; ordered: each XCD takes a contiguous
+    // range of them, whose lines stay in its L2 (the launch has a multiple of 8
+    // workgroups, at least one a run, and the last of a range may be past the end)
+    const int64_t run = ordered ? (blockIdx.x & 7) * (int64_t)(gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const int64_t k = run * 64 + lane;
+    const bool in = k < n;
+    int64_t at = k;
+    if (in) {
+        int4 r;
+        if (ordered) {
+            const uint4 q = o.rec[k];
+            at = q.x;
+            r = make_int4((int)(q.y & 0xFFFFu), (int)(q.y >> 16), (int)(q.z & 0xFFFFu), (int)(q.z >> 16));
+        } else {
+            bool clamped;
+            r = dec_request(g, lod, coords[k], clamped);
+            // counted by the ordering's first pass when there is one
+            if (!ORDERED && c == 0) {
+                const unsigned long long m = __ballot(clamped);
+                if (m && lane == __ffsll((long long)m) - 1) atomicAdd(clamps, (unsigned long long)__popcll(m));
             }
-            vals[c][lane] = dec_channel(g, p, c, r.x << lod, r.y << lod, r.z, r.w, lod);
         }
-        __syncthreads();
-        if (c == 0 && in) {
-            int R, G, B;
-            lf_ycocg_to_rgb(vals[0][lane], vals[1][lane], vals[2][lane], R, G, B);
-            rgb[3 * at] = (uint8_t)R;
-            rgb[3 * at + 1] = (uint8_t)G;
-            rgb[3 * at + 2] = (uint8_t)B;
-        }
-        __syncthreads();  // the next run rewrites vals
+        vals[c][lane] = dec_channel(g, p, c, r.x << lod, r.y << lod, r.z, r.w, lod);
+    }
+    __syncthreads();
+    if (c == 0 && in) {
+        int R, G, B;
+        lf_ycocg_to_rgb(vals[0][lane], vals[1][lane], vals[2][lane], R, G, B);
+        rgb[3 * at] = (uint8_t)R;
+        rgb[3 * at + 1] = (uint8_t)G;
+        rgb[3 * at + 2] = (uint8_t)B;
     }
 }
 
@@ -328,8 +324,7 @@ int64_t lf_decode_scratch(const lf_handle* h, int64_t n)
 lf_status lf_launch_decode_dense(const lf_handle* h, int lod, const int32_t* d_coords, int64_t n, uint8_t* d_rgb,
                                  unsigned long long* clamps, void* d_scratch, hipStream_t s)
 {
-    // an ordered launch has a workgroup per run (n is at most 2^26 there)
-    const int64_t wgs = std::min<int64_t>((n + 63) / 64, 1 << 24);
+    const int64_t wgs = (n + 63) / 64;  // at most 2^20: n is at most DEC_MAX with scratch, below DEC_SMALL without
     const int4* coords = (const int4*)d_coords;
     DecOrder o = {};
     if (!d_scratch) {
