@@ -1199,50 +1199,31 @@ __device__ __forceinline__ AdRec ad_split(const LfGeom& g, int sg, float2 s)
     return d;
 }
 
-// What reference pixel (X, Y) pulls from one predictive block (row ky,
-// column kx) with gradient plane gp: the bilinear weights of the block's taps
-// that land on the pixel times the gradients of their pixels, phase-signed,
-// added to acc.
-template <class Get>
-__device__ __forceinline__ float ad_block_pull(const LfGeom& g, Get get, int X, int Y, int ky, int kx, const AdRec& d,
-                                               float acc)
+// What pixel (X, Y) on the border of a reference pulls from one predictive
+// block (row ky, column kx) with gradient plane gp: the bilinear weights of the
+// block's taps that are clamped onto the pixel or land there times the
+// gradients of their pixels, phase-signed.
+__device__ __forceinline__ float ad_border_pull(const LfGeom& g, const float* gp, int X, int Y, int ky, int kx, const AdRec& d)
 {
-    float blk_acc = 0.0f;
+    float acc = 0.0f;
     const int bx0 = kx * g.bs, by0 = ky * g.bs;
-    if (X > 0 && X < g.w - 1 && Y > 0 && Y < g.h - 1) {
-        // away from the image border no tap is clamped: the tap (oy, ox)
-        // landing on the pixel comes from source pixel (Y - iy - oy, X - ix - ox)
-        // alone, when that pixel lies in the block
-#pragma unroll
-        for (int oy = 0; oy < 2; oy++) {
-            const int ys = Y - d.iy - oy;
-            const float wy = oy ? d.fy : 1.0f - d.fy;
-#pragma unroll
-            for (int ox = 0; ox < 2; ox++) {
-                const int xs = X - d.ix - ox;
-                if (ys >= by0 && ys < by0 + g.bs && xs >= bx0 && xs < bx0 + g.bs)
-                    blk_acc = fmaf(wy * (ox ? d.fx : 1.0f - d.fx), get(ys, xs), blk_acc);
-            }
-        }
-    } else {
-        for (int oy = 0; oy < 2; oy++) {
-            int ylo, yhi;
-            ad_tap_range(Y, g.h, d.iy, oy, by0, by0 + g.bs - 1, ylo, yhi);
-            if (ylo > yhi) continue;
-            const float wy = oy ? d.fy : 1.0f - d.fy;
-            for (int ox = 0; ox < 2; ox++) {
-                int xlo, xhi;
-                ad_tap_range(X, g.w, d.ix, ox, bx0, bx0 + g.bs - 1, xlo, xhi);
-                if (xlo > xhi) continue;
-                const float wxy = wy * (ox ? d.fx : 1.0f - d.fx);
-                float sum = 0.0f;
-                for (int y = ylo; y <= yhi; y++)
-                    for (int x = xlo; x <= xhi; x++) sum += get(y, x);
-                blk_acc = fmaf(wxy, sum, blk_acc);
-            }
+    for (int oy = 0; oy < 2; oy++) {
+        int ylo, yhi;
+        ad_tap_range(Y, g.h, d.iy, oy, by0, by0 + g.bs - 1, ylo, yhi);
+        if (ylo > yhi) continue;
+        const float wy = oy ? d.fy : 1.0f - d.fy;
+        for (int ox = 0; ox < 2; ox++) {
+            int xlo, xhi;
+            ad_tap_range(X, g.w, d.ix, ox, bx0, bx0 + g.bs - 1, xlo, xhi);
+            if (xlo > xhi) continue;
+            const float wxy = wy * (ox ? d.fx : 1.0f - d.fx);
+            float sum = 0.0f;
+            for (int y = ylo; y <= yhi; y++)
+                for (int x = xlo; x <= xhi; x++) sum += gp[y * g.w + x];
+            acc = fmaf(wxy, sum, acc);
         }
     }
-    return acc + (d.sg > 0 ? blk_acc : -blk_acc);
+    return d.sg > 0 ? acc : -acc;
 }
 
 // One kept block of the reference pull: its record and place (scalar, from
@@ -1312,8 +1293,7 @@ struct AdTaps {
 #pragma unroll 1
         for (int k = 0; k < 4; k++) {
             if (!live[k] || inner[k]) continue;
-            const float t = ad_block_pull(g, [&](int y, int x) { return gp[y * g.w + x]; }, X, Y0 + k, by >> g.bsl,
-                                          bx >> g.bsl, q, 0.0f);
+            const float t = ad_border_pull(g, gp, X, Y0 + k, by >> g.bsl, bx >> g.bsl, q);
             if (k == 0) acc[0] += t;
             if (k == 1) acc[1] += t;
             if (k == 2) acc[2] += t;
