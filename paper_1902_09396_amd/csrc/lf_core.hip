@@ -621,11 +621,11 @@ __global__ void k_load_desc(LfGeom g, LfPtrs p, uint4* __restrict__ desc, int* _
 // modulo 2^16, and its colour inverse (two halvings, sums of at most three
 // terms) stays inside int16 from such values, so its result then equals the
 // int32 decode.  Decoded values of 8-bit content are within 255 + step / 2
-// of the source.  One thread per sample of every leaf view, all channels;
-// run only when the bound from the block table and the root (the largest root
-// magnitude plus, per level, the largest values its block modes can hold)
-// does not settle it: 6.2 ms for 17x17x512x512, where streams of 8-bit
-// content have bounds of 1000 to 4000.
+// of the source.  One thread per sample of every leaf view, all channels of
+// the geometry; run only when the bound from the block table and the root (the
+// largest root magnitude plus, per level, the largest values its block modes
+// can hold) does not settle it: 6.2 ms for 17x17x512x512, where streams of
+// 8-bit content have bounds of 1000 to 4000.
 __global__ void k_load_check(LfGeom g, LfPtrs p, int* __restrict__ status)
 {
     const int64_t plane = (int64_t)g.w * g.h;
@@ -635,12 +635,35 @@ __global__ void k_load_check(LfGeom g, LfPtrs p, int* __restrict__ status)
         const int64_t view = t / plane, px = t - view * plane;
         const int b = (int)(view / g.na), a = (int)(view - (int64_t)b * g.na);
         const int y = (int)(px / g.w), x = (int)(px - (int64_t)y * g.w);
-        for (int c = 0; c < 3; c++) {
+        for (int c = 0; c < g.nch; c++) {
             const int v = lf_decode_channel<LF_RES_DENSE>(g, p, c, b, a, y, x);
             bad |= v < -LF_SAMPLE_LIMIT || v > LF_SAMPLE_LIMIT;
         }
     }
     if (bad) atomicOr(status, LF_ST_SAMPLE);
+}
+
+// 4:2:0: motion vectors beyond 12 signed bits, where the sequences' widths
+// leave it open (dense handles: k_load_desc).
+__global__ void k_load_vectors(LfGeom g, LfPtrs p, int* __restrict__ status)
+{
+    const int64_t total = (int64_t)g.nch * g.n_nodes * g.nblk;
+    bool bad = false;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
+        const int blk = (int)(t % g.nblk);
+        const int node = (int)((t / g.nblk) % g.n_nodes);
+        const int c = (int)(t / ((int64_t)g.nblk * g.n_nodes));
+        int l = 0;
+        while (l + 1 < g.H && node < g.node_base[l]) l++;  // levels are stored H-1 first
+        const int local = node - g.node_base[l];
+        const int B = local / g.na_l[l], A = local % g.na_l[l];
+        if ((A | B) & 1) {
+            int mx, my, sg;
+            lf_motion(g, p, c, l, (uint32_t)(pred_ordinal(g.na_l[l], B, A) * g.nblk + blk), mx, my, sg);
+            bad |= mx < -2047 || mx > 2047 || my < -2047 || my > 2047;
+        }
+    }
+    if (bad) atomicOr(status, LF_ST_MV);
 }
 
 extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbytes, int32_t flags, void* d_arena,
@@ -800,11 +823,19 @@ extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbyte
         // when that does not settle the sample range are the samples decoded
         int64_t bound = 0;
         for (int c = 0; c < 3; c++) bound = std::max(bound, (int64_t)words[4 + c] + L.srv_bound[c]);
-        h->L.packed_levels = bound <= LF_SAMPLE_LIMIT && L.packed_vectors;
-        if (bound > LF_SAMPLE_LIMIT && !L.sparse && !L.chroma420) {
-            const int64_t ns = (int64_t)L.g.na * L.g.nb * L.g.w * L.g.h;
-            const int64_t cblocks = std::min<int64_t>((ns + 255) / 256, 65536);
-            hipLaunchKernelGGL(k_load_check, dim3((unsigned)cblocks), dim3(256), 0, s, L.g, h->p, status);
+        const bool samples = bound > LF_SAMPLE_LIMIT && !L.sparse, vectors = L.chroma420 && !L.packed_vectors;
+        if (samples || vectors) {
+            for (int gi = 0; gi < (L.chroma420 ? 2 : 1); gi++) {
+                const LfGeom& g = gi ? L.gc : L.g;
+                const LfPtrs& p = gi ? h->pc : h->p;
+                const int64_t ns = (int64_t)g.na * g.nb * g.w * g.h, nd = (int64_t)g.nch * g.n_nodes * g.nblk;
+                if (samples)
+                    hipLaunchKernelGGL(k_load_check, dim3((unsigned)std::min<int64_t>((ns + 255) / 256, 65536)), dim3(256), 0, s,
+                                       g, p, status);
+                if (vectors)
+                    hipLaunchKernelGGL(k_load_vectors, dim3((unsigned)std::min<int64_t>((nd + 255) / 256, 65536)), dim3(256), 0, s,
+                                       g, p, status);
+            }
             st = lf_check_launch("load_check");
             if (st == LF_OK && (hipMemcpyAsync(&flag, status, sizeof flag, hipMemcpyDeviceToHost, s) != hipSuccess ||
                                 hipStreamSynchronize(s) != hipSuccess))
@@ -814,6 +845,10 @@ extern "C" lf_status lf_load_compressed_ex(const void* host_stream, size_t nbyte
                 return st;
             }
         }
+        const bool lanes = L.chroma420 ? !(flag & LF_ST_MV) : L.packed_vectors != 0;
+        h->L.packed_levels = bound <= LF_SAMPLE_LIMIT && lanes;
+        h->L.packed_leaves = h->L.packed_levels || (L.chroma420 && !flag);
+        if (L.chroma420) flag = 0;  // such streams are rendered one thread per ray, not refused
     }
     if (flag) {
         delete h;

@@ -20,6 +20,8 @@ struct LfLayout {
     // set by the load: those bounds and the root keep every level's samples,
     // not the leaf views' alone, inside the range of the packed 16-bit decode
     int32_t packed_levels;
+    // 4:2:0, set by the load: the leaf views' samples are, if not every level's
+    int32_t packed_leaves;
     // arena offsets
     int64_t a_root, a_table, a_payload, a_mv, a_refs, a_desc, a_status, arena;
     // sparse reference residency (LF_LOAD_SPARSE_REFS): a_refs holds n_tiles

@@ -353,7 +353,7 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
 // handles: the load refuses leaf samples beyond the lanes' range, and settles
 // the coarser levels' at once or not at all.  4:2:0 and block-sparse handles:
 // taken when the load has settled the range of every level and of the motion
-// vectors (nothing is refused there).  The root
+// vectors (nothing is refused there), or of a 4:2:0 handle's leaf views.  The root
 // level is sixteen plain reads per ray: no tiles.  CSR handles search a row
 // per tap: no tiles.  Nor do renders from the level below the root where its
 // nodes are a single row or column, or, from level 2 on, where a workgroup
@@ -374,7 +374,7 @@ static bool lf_tiles_apply(const lf_handle* h, int level, int nv, int wo, int ho
         const int tiles = ((wo + TW - 1) / TW) * ((ho + TH - 1) / TH);
         if (level > 1 && std::min(frames_per_chunk(nv, tiles), nv) < 5) return false;
     }
-    if (L.sparse || L.chroma420) return L.packed_levels != 0;
+    if (L.sparse || L.chroma420) return L.packed_levels || (level == 0 && L.packed_leaves);
     return level == 0 || L.packed_levels;
 }
 
