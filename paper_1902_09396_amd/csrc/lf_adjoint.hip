@@ -938,9 +938,9 @@ __global__ void k_ad_heads(AdAxes t, const uint32_t* __restrict__ keys, int64_t 
     }
 }
 
-// Sample gradients and sums in one launch, or in two where records are to be
-// gathered: the sample gradients alone first, then the sums.
-enum AdPass { AD_WHOLE, AD_LEAVES, AD_SUMS };
+// Sample gradients and sums in one launch, or in two, always or where records
+// are to be gathered: the sample gradients alone first, then the sums.
+enum AdPass { AD_WHOLE, AD_LEAVES, AD_SUMS, AD_RECORD_LEAVES, AD_RECORD_SUMS };
 
 struct AdGather {
     AdAxes t;
@@ -1027,8 +1027,8 @@ template <int D>
 __global__ void __launch_bounds__(256) k_ad_gather(LfGeom g, AdGather G, int clusters, AdPass pass, float* __restrict__ gres)
 {
     const int by = ad_by_records(G.t);
-    if (pass == AD_LEAVES && !by) return;
-    const bool there = pass == AD_SUMS && by;  // the sample gradients are in gres
+    if (pass == AD_RECORD_LEAVES && !by) return;
+    const bool there = pass == AD_SUMS || (pass == AD_RECORD_SUMS && by);  // the sample gradients are in gres
     const int px = (int)(blockIdx.x * 256 + threadIdx.x);
     const int plane = g.w * g.h;
     if (px >= plane) return;
@@ -1669,9 +1669,11 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
     // level-0 gradients (every sample written) and up to two levels above
     const int64_t plane = (int64_t)g.w * g.h;
     AdGather ga{t, rayf, d_grad_out, ki, vi, start, Bl.n_recs, n_views, width, height};
-    // D levels above from a thread's registers: a level less to read back, but
-    // up to 16 times fewer threads.  Waves of clusters at D = 2 and the call's
-    // time at D = 2 and 0: 102,400 (17x17 of 512x512), 24 views of 512x512
+    // Up to two levels above from a thread's registers, which gathers the
+    // samples below (one pass, but up to 16 times fewer threads to gather with)
+    // or reads their gradients back (two).  Waves of clusters of two levels, and
+    // the call's time with one pass and with the samples by themselves (and a
+    // pass a level): 102,400 (17x17 of 512x512), 24 views of 512x512
     // 1.67 and 2.15 ms; 25,600 (17x17 of 256x256), 16 views 527..690 and
     // 611..733 us; 9,216 (9x9 of 256x256), eight views of 256x256 (0.4 records
     // a sample) 161..190 and 189..203, 16 of 512x512 (3.2) 382..489 and
@@ -1682,20 +1684,24 @@ extern "C" lf_status lf_render_backward(const lf_handle* h, const float* d_resid
         const int clusters = clusters_of(d);
         const int64_t wx = (plane + 255) / 256;
         // the launch that may find nothing to do is kept to 8,192 workgroups
-        const int64_t wy = pass == AD_LEAVES ? std::max<int64_t>(8192 / wx, 1) : 65535;
+        const int64_t wy = pass == AD_RECORD_LEAVES ? std::max<int64_t>(8192 / wx, 1) : 65535;
         hipLaunchKernelGGL(d == 0 ? k_ad_gather<0> : (d == 1 ? k_ad_gather<1> : k_ad_gather<2>),
                            dim3((unsigned)wx, (unsigned)std::min<int64_t>(clusters, wy)), dim3(256), 0, s, g, ga, clusters, pass,
                            d_grad_residual);
     };
-    int D = std::min(g.H - 1, 2);
+    const int D = std::min(g.H - 1, 2);
     const int64_t waves = clusters_of(D) * plane / 64;
-    if (waves < 4096 || (waves < 16384 && Bl.n_recs > 2 * Bl.n_samples)) D = 0;
+    const bool apart = waves < 4096 || (waves < 16384 && Bl.n_recs > 2 * Bl.n_samples);
     // Records take a chain of dependent loads each and are spread unevenly:
     // they want a thread a sample on larger fields too (17x17 of 256x256, two
     // projective views of 1280x720 2.20 and 1.92 ms; 5x5 of 64x64 34.3 and 7.5).
-    const bool ahead = D > 0 && waves < 32768 && 4 * Bl.n_recs > Bl.n_samples;
-    if (ahead) gather(0, AD_LEAVES);
-    gather(D, ahead ? AD_SUMS : AD_WHOLE);
+    const bool records_apart = waves < 32768 && 4 * Bl.n_recs > Bl.n_samples;
+    if (D > 0 && (apart || records_apart)) {
+        gather(0, apart ? AD_LEAVES : AD_RECORD_LEAVES);
+        gather(D, apart ? AD_SUMS : AD_RECORD_SUMS);
+    } else {
+        gather(D, AD_WHOLE);
+    }
     for (int l = D + 1; l < g.H; l++)
         hipLaunchKernelGGL(k_ad_tree, dim3(8192), dim3(256), 0, s, g, l, d_grad_residual);
     // the shift pass reads the predictive nodes' gradients, which the
