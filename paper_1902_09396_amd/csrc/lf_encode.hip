@@ -1071,14 +1071,18 @@ static_assert(offsetof(StreamHeader, step) == 48 && offsetof(StreamHeader, win) 
 static_assert(offsetof(StreamHeader, root_off) == 112 && offsetof(StreamHeader, dir) == 176, "header layout");
 static_assert(offsetof(StreamHeader, chroma_format) == LF_HDR_CHROMA, "header layout");
 
-// malloc'ed memory for a stream (contents unset).  A large one is touched by
-// several threads first, in huge pages where the system grants them: copying
-// 116 MB from the device into fresh 4 KiB pages took 27 ms, into pages that
-// are there 6.7.
+// malloc'ed memory for a stream (contents unset).  From 32 MiB on, where malloc
+// maps fresh pages on each call, it is touched by several threads first, in
+// huge pages where the system grants them: copying 116 MB from the device into
+// fresh 4 KiB pages took 27 ms, into pages that are there 6.7 (an encode of 46
+// MB 9.7 ms, 18.1 without).  Smaller memory comes back to malloc with its
+// pages, and threads started for it stand in the way of the program's own: an
+// encode of 9.4 MB with a copy by torch's threads after it 1.92 ms, 4.00 with
+// the touching, of 29 MB 5.9 and 8.0.
 uint8_t* stream_alloc(size_t bytes)
 {
     constexpr size_t HUGE_PAGE = 2u << 20, PAGE = 4096;
-    if (bytes < 4 * HUGE_PAGE) return (uint8_t*)malloc(bytes);
+    if (bytes < 16 * HUGE_PAGE) return (uint8_t*)malloc(bytes);
     void* m = nullptr;
     if (posix_memalign(&m, HUGE_PAGE, bytes) != 0) return nullptr;
     madvise(m, bytes, MADV_HUGEPAGE);  // a hint: refused on systems without them
