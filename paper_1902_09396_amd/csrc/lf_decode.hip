@@ -311,7 +311,10 @@ bool lf_decode_unordered(const lf_handle* h, int64_t n)
 // walk fetches 31 cache lines a sample, 6.6 TB/s).  Consecutive ones, left in
 // order: 2^18 34 -> 24 us, 2^20 87 -> 59.  The line: below it the three
 // launches cost consecutive requests more than they had taken (98,304: 17.4
-// us, 18.3 with them), and scattered ones run in 61 against 75 without.
+// us, 18.3 with them), and scattered ones run in 61 against 75 without.  Over
+// fields of two or three levels, whose samples are cheaper, consecutive ones
+// still pay for the launches there: 114,688 11..16 -> 20..22 us, 2^18 14..21 ->
+// 20..22, even at 2^19; scattered 34..73 -> 25..56 and 48..143 -> 38..111.
 int64_t lf_decode_scratch(const lf_handle* h, int64_t n)
 {
     const LfGeom& g = h->L.g;

@@ -130,8 +130,15 @@ __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGe
 // blends one colour.  3 views of 157x750, far minified, 16x16 blocks: 558 ->
 // 437 us for the call; 11 of 253x1032 2.37 -> 0.38 ms; 2 of 80x144 in 4:2:0
 // 0.92 -> 0.44 ms (one thread a ray, a contiguous range a workgroup before).
-// 37 views of 340x202 at 4x4 blocks, enough marked tiles to fill the chip,
-// take 4% more: two thirds of the waves fit.
+// Calls of small blocks that mark most of some thousand tiles are up to a
+// fifth slower than with one thread a ray in tile order: 37 views of 340x202
+// on a path over 17x17 of 512x512 in 8x8 blocks 2.05 -> 2.34 ms, 65 of 137x139
+// over 15x12 of 120x360 in 4x4 1.26 -> 1.51 (10 unrelated ones of 340x202 0.45
+// -> 0.25).  Neighbouring tiles no longer run side by side.  Not better: a
+// range of tiles per 251 workgroups (the first 2.08 to 2.25, the last 0.30 to
+// 0.35 or 8 us more for every call), contiguous runs per XCD (2.19, others
+// 1.3 times slower), one thread a ray where a workgroup holds three marked
+// tiles (2.47).
 template <bool C420, int RES>
 __global__ void __launch_bounds__(3 * NT) k_render_fallback(LfGeom g, LfPtrs p, LfGeom gc, LfPtrs pc,
                                                             const float* __restrict__ cams, int nv, int wo, int ho,
@@ -337,9 +344,9 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
                        chunk, fpg, n_full, sp, d_out, LodGrid{h->L.g.na, h->L.g.nb, lod});
     // G of the per-ray pass: 256 workgroups more that find nothing cost 1.3 us,
     // so one on each CU does where few tiles are marked (16x16 blocks: one
-    // 512x512 view 44.6 us, 46.0 with 509).  Smaller blocks mark more tiles, whose costs differ: two views of
-    // 74x928, all marked, 131 us with 509, 200 with 251; 32 of 211x117 711 with
-    // 1021, 838 with 509.
+    // 512x512 view 44.6 us, 46.0 with 509).  Smaller blocks mark more tiles,
+    // whose costs differ: two views of 74x928, all marked, 131 us with 509, 200
+    // with 251; 32 of 211x117 711 with 1021, 838 with 509.
     const int64_t pairs = (int64_t)tx * ty * nv;
     const int most = h->L.g.bs >= 16 ? 251 : (pairs <= 2048 ? 509 : 1021);
     const auto rest = c420 ? k_render_fallback<true, D> : (tiles ? k_render_fallback<false, T> : k_render_fallback<false, D>);
