@@ -72,7 +72,7 @@ lf_status lf_launch_render_rays(const lf_handle* h, const float* d_cams, int nv,
 // C420: a 4:2:0 stream, chroma geometry gc, pc (unused otherwise).  LOD: the
 // samples of a coarser tree level, g and gc cut off below it (grid unused
 // otherwise).
-template <bool SMALL_BLOCKS, bool C420, bool LOD, int RES>
+template <bool SMALL_BLOCKS, bool C420, bool LOD, int RES, bool DIRECT = false>
 __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGeom gc, LfPtrs pc,
                                                      const float* __restrict__ cams, int nv, int wo, int ho,
                                                      int tiles_x, int tiles_y, int chunk, int fpg, int64_t n_full,
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(NT, 3) k_render_batch(LfGeom g, LfPtrs p, LfGe
         nf = min(per, c1 - v0);
         if (nf <= 0) return;
     }
-    lf_tile_views<false, SMALL_BLOCKS, C420, LOD, RES>(g, p, gc, pc, cams, v0, nf, fpg, wo, ho, txi, tyi, out, S, grid);
+    lf_tile_views<false, SMALL_BLOCKS, C420, LOD, RES, DIRECT>(g, p, gc, pc, cams, v0, nf, fpg, wo, ho, txi, tyi, out, S, grid);
 }
 
 // Per-ray rendering of the (view, tile) pairs the batched kernel marked.
@@ -321,16 +321,20 @@ lf_status lf_launch_render_batch(const lf_handle* h, const float* d_cams, int nv
     using BatchKernel = void (*)(LfGeom, LfPtrs, LfGeom, LfPtrs, const float*, int, int, int, int, int, int, int,
                                  int64_t, int, float*, LodGrid);
     const bool cut = lod > 0, tiles = h->L.sparse == LF_RES_TILES;
-    // [small blocks][dense, coarser level, 4:2:0, 4:2:0 coarser level, block-sparse of any level]
+    // [small blocks][dense, coarser level, 4:2:0, 4:2:0 coarser level, block-sparse of any level, coarser level and
+    // block-sparse coarser level of at most four views a chunk]
     constexpr int D = LF_RES_DENSE, T = LF_RES_TILES;
-    static const BatchKernel kernels[2][5] = {
+    static const BatchKernel kernels[2][7] = {
         {k_render_batch<false, false, false, D>, k_render_batch<false, false, true, D>, k_render_batch<false, true, false, D>,
-         k_render_batch<false, true, true, D>, k_render_batch<false, false, true, T>},
+         k_render_batch<false, true, true, D>, k_render_batch<false, false, true, T>,
+         k_render_batch<false, false, true, D, true>, k_render_batch<false, false, true, T, true>},
         {k_render_batch<true, false, false, D>, k_render_batch<true, false, true, D>, k_render_batch<true, true, false, D>,
-         k_render_batch<true, true, true, D>, k_render_batch<true, false, true, T>}};
-    const int kind = tiles ? 4 : 2 * c420 + cut;
+         k_render_batch<true, true, true, D>, k_render_batch<true, false, true, T>,
+         k_render_batch<true, false, true, D, true>, k_render_batch<true, false, true, T, true>}};
+    int kind = tiles ? 4 : 2 * c420 + cut;
+    if (cut && !c420 && chunk <= 4) kind = tiles ? 6 : 5;
     const BatchKernel kern = kernels[small][kind];
-    static bool attr_set[2][5] = {};
+    static bool attr_set[2][7] = {};
     if (lds > 65536 && !attr_set[small][kind]) {
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return lf_fail(LF_EDEVICE, "cannot reserve %zu bytes of LDS", lds);

@@ -771,8 +771,10 @@ __device__ __forceinline__ void lf_stage_quads(const LfGeom& g, const LfPtrs& p,
 // cache across groups and the blend are shared.
 // LOD: the samples of a coarser tree level (grid); g (and gc) are then the
 // geometry cut off below that level, whose nodes take the leaf views' place.
-// RES: dense or block-sparse reference residency.
-template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false, bool LOD = false, int RES = LF_RES_DENSE>
+// RES: dense or block-sparse reference residency.  DIRECT (LOD): views over one
+// reference node read its planes.
+template <bool INLINE_FALLBACK, bool SMALL_BLOCKS = false, bool C420 = false, bool LOD = false, int RES = LF_RES_DENSE,
+          bool DIRECT = false>
 __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc, const LfPtrs& pc,
                               const float* __restrict__ cams, int v0, int nf, int gmax, int wo, int ho, int txi,
                               int tyi, float* __restrict__ out, const TileLds& S, const LodGrid& grid = LodGrid{})
@@ -886,7 +888,7 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
     // successes in a row
     int f = 0, n = GROUP_FIRST(gmax), ceil_n = gmax + 1, streak = 0;
     while (f < nf) {
-        if constexpr (LOD && !C420) {
+        if constexpr (DIRECT) {
             // A view that meets one node here, a reference on a path of
             // references, is twelve plane reads a ray and level, less than a
             // tile's plan and stages while few views share those: two views of
@@ -894,10 +896,11 @@ __device__ bool lf_tile_views(const LfGeom& g, const LfPtrs& p, const LfGeom& gc
             // through the stages (19 in a launch of one thread per ray, whose
             // workgroups need no LDS); eight of 512x512, four a workgroup, 49
             // and 73; 16, eight a workgroup, 76 and 80, at level 1 of 4 113
-            // and 86.
+            // and 86.  An instance of its own for chunks of that size: its code
+            // costs other launches 1 to 3%.
             const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)fbox[f][0]),
                            hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)fbox[f][1]);
-            if (nf <= 4 && lo == hi && ((lo | (lo >> 16)) & ((1u << g.H) - 1u)) == 0u) {
+            if (lo == hi && ((lo | (lo >> 16)) & ((1u << g.H) - 1u)) == 0u) {
                 float o[3];
                 lf_reference_ray<RES>(g, p, lf_ray_setup<LOD>(g, grid, cams + 18 * (v0 + f), ii, jj), o);
                 if (live)
