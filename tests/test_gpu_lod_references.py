@@ -68,7 +68,7 @@ def test_cost_of_one_reference():
             b.synchronize()
             best = min(best, a.elapsed_time(b))
         times.append(best)
-    assert times[0] < 0.6 * times[1], times
+    assert times[0] < 0.7 * times[1], times
 
 
 @pytest.mark.parametrize("na,nb,levels", [(8, 8, 3), (17, 9, 4), (8, 4, 3)])
